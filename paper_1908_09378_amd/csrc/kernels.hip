@@ -57,7 +57,7 @@ __global__ __launch_bounds__(NT) void k_sssp(SsspParams p) {
   extern __shared__ __align__(16) unsigned char dyn[];
   __shared__ TeamShared<NT / 64> ts;
   __shared__ HeapState st_lds;
-  DevTeam<NT> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
+  DevTeam<NT, false, false> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
   sssp_query<NT, false, SPEC>(t, (HeapState PBH_LDS*)&st_lds, dyn, p);
 }
 
@@ -198,7 +198,9 @@ __global__ __launch_bounds__(NT) void k_mlp_infer(const float* X, u32 n, const f
   float f[NFEAT];
 #pragma unroll
   for (int i = 0; i < NFEAT; ++i) f[i] = X[(u64)r * NFEAT + i];
-  const float v = mlp_forward(t, blob, f);
+  MlpRegs<DevTeam<NT>> w;
+  w.load(t, blob);
+  const float v = mlp_forward(t, blob, f, w);
   if (threadIdx.x == 0) y[r] = v;
 }
 

@@ -16,9 +16,9 @@ __global__ __launch_bounds__(NT) void k_sssp_full(SsspParams p) {
   extern __shared__ __align__(16) unsigned char dyn[];
   __shared__ TeamShared<NT / 64> ts;
   __shared__ HeapState st_lds;
-  DevTeam<NT, true> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
+  DevTeam<NT, true, true> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
   if (blockIdx.x == 0)
-    sssp_query<NT, true>(t, (HeapState PBH_LDS*)&st_lds, dyn, p);
+    sssp_query<NT, true, true, true>(t, (HeapState PBH_LDS*)&st_lds, dyn, p);
   else if (p.deep && p.deep_lim + (int)blockIdx.x - 1 < p.g.q)
     deep_worker(t, (HeapState PBH_LDS*)&st_lds, dyn, p, p.deep_lim + (int)blockIdx.x - 1);
 }
@@ -32,7 +32,7 @@ __global__ __launch_bounds__(NT) void k_sssp_multi(const SsspParams* qs, u32 nq,
   __shared__ TeamShared<NT / 64> ts;
   __shared__ HeapState st_lds;
   __shared__ u32 qnext;
-  DevTeam<NT, true> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
+  DevTeam<NT, true, false> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
   for (;;) {
     if (threadIdx.x == 0) qnext = atomicAdd(counter, 1u);
     t.sync();

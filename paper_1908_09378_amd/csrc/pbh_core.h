@@ -61,7 +61,8 @@ PBH_HD inline u64 nomB(u32 d, int i) { return (u64)d << (2 * i + 1); }
 PBH_HD inline u64 capS(u32 d, int i) { return (u64)d << (2 * i + 1); }
 PBH_HD inline u64 capB(u32 d, int i) { return (u64)d << (2 * i + 2); }
 PBH_HD inline u64 lvl_size(u32 d, int i) { return (16ull * d) << (2 * i); }
-PBH_HD inline u64 lvl_off(u32 d, int i) { return 16ull * d * (((1ull << (2 * i)) - 1ull) / 3ull); }
+// (4^i - 1) / 3 = 1 + 4 + ... + 4^(i-1)
+PBH_HD inline u64 lvl_off(u32 d, int i) { return 16ull * d * (0x5555555555555555ull & ((1ull << (2 * i)) - 1ull)); }
 
 struct Geom {
   u32 d;
@@ -119,7 +120,6 @@ struct HeapState {
   u64 live;      // elements in the heap (queue size)
   u64 progress;  // resumable progress of a multi-piece operation
   u64 aux[5];
-  u32 prof_on;   // time accounting on (SSSP kernels only)
   // Levels resolved by their own workers (the deep-level service of the SSSP
   // kernel): this team's copies of their states are not kept up to date, so
   // the deepest level known to hold elements (-1: none) and the number of
@@ -145,7 +145,7 @@ PBH_INL u64 pbh_clock() {
 // time of a step includes its slowest wavefront.
 template <class T, class SP>
 PBH_INL void prof_lap(const T& t, SP st, int cat) {
-  if (t.tid() == 0 && st->prof_on) {
+  if (t.prof && t.tid() == 0) {
     const u64 now = pbh_clock();
     st->prof[cat] += now - st->prof_last;
     st->prof_last = now;
@@ -165,7 +165,6 @@ PBH_HD inline void state_init(SP st, u32 d, int q) {
   st->q = q;
   st->elems = st->live = st->progress = 0;
   for (int i = 0; i < 5; ++i) st->aux[i] = 0;
-  st->prof_on = 0;
   st->deep_floor = -1;
   st->deep_n = 0;
   st->prof_last = st->prof_res = 0;
@@ -184,6 +183,20 @@ PBH_INL Lvl lvl_load(SP st, int i) {
   a.pk = st->L[i].pk;
   a.pv = st->L[i].pv;
   a.cnt = st->L[i].cnt;
+  return a;
+}
+// The same for a team: the values are the same in every thread, and saying so
+// keeps them in scalar registers, with scalar branches on them.
+template <class T, class SP>
+PBH_INL Lvl lvl_uni(const T& t, SP st, int i) {
+  Lvl a = lvl_load(st, i);
+  a.nB = t.uni(a.nB);
+  a.nS = t.uni(a.nS);
+  a.bsel = t.uni(a.bsel);
+  a.ssel = t.uni(a.ssel);
+  a.pk = t.uni64(a.pk);
+  a.pv = t.uni(a.pv);
+  a.cnt = t.uni(a.cnt);
   return a;
 }
 template <class SP>
@@ -212,17 +225,53 @@ struct HostPolicy {
 
 // ---------------------------------------------------------------- primitives
 
+// Where an array lives.
+template <class A>
+struct in_lds {
+  static constexpr bool v = false;
+};
+template <>
+struct in_lds<ArrT<u64 PBH_LDS*, u32 PBH_LDS*>> {
+  static constexpr bool v = true;
+};
+
+template <class A, class B>
+struct same_arr {
+  static constexpr bool v = false;
+};
+template <class A>
+struct same_arr<A, A> {
+  static constexpr bool v = true;
+};
+
 // Merge-path split (Green, McColl, Bader 2012): how many of the first `diag`
-// elements of merge(A, B) by id come from A (A first on equal ids).
-template <class VA, class VB>
+// elements of merge(A, B) by id come from A (A first on equal ids).  QUAD: each
+// step tests three split points, whose six reads are in flight together; the
+// search is a chain of dependent reads, so half as many steps is half its time
+// for one wavefront on LDS (about 60 ns a step, seven steps -> four on 128
+// elements).  Where many lanes' scattered reads load the LDS or the L1, the
+// plain search's fewer reads are faster.
+template <bool QUAD, class VA, class VB>
 PBH_INL u32 merge_path(VA av, u32 na, VB bv, u32 nb, u32 diag) {
   u32 lo = diag > nb ? diag - nb : 0u, hi = diag < na ? diag : na;
-  while (lo < hi) {
-    u32 mid = (lo + hi) >> 1;
-    if (av[mid] <= bv[diag - 1 - mid])
-      lo = mid + 1;
-    else
-      hi = mid;
+  if constexpr (QUAD) {
+    while (lo < hi) {
+      const u32 len = hi - lo;
+      const u32 m1 = lo + (len >> 2), m2 = lo + (len >> 1), m3 = lo + ((3u * (len >> 1)) >> 1);
+      const bool t1 = av[m1] <= bv[diag - 1 - m1], t2 = av[m2] <= bv[diag - 1 - m2],
+                 t3 = av[m3] <= bv[diag - 1 - m3];
+      // true on a prefix: t3 implies t2 implies t1
+      lo = t3 ? m3 + 1 : (t2 ? m2 + 1 : (t1 ? m1 + 1 : lo));
+      hi = t3 ? hi : (t2 ? m3 : (t1 ? m2 : m1));
+    }
+  } else {
+    while (lo < hi) {
+      const u32 mid = (lo + hi) >> 1;
+      if (av[mid] <= bv[diag - 1 - mid])
+        lo = mid + 1;
+      else
+        hi = mid;
+    }
   }
   return lo;
 }
@@ -237,73 +286,135 @@ PBH_INL u32 merge_path(VA av, u32 na, VB bv, u32 nb, u32 diag) {
 // into B_0, so that B_0 holds only live elements).
 enum { PREFER_LIVE = 0, PREFER_A = 1, PREFER_B = 2 };
 
+
+// The next E elements of A and of B from a thread's split, held in registers:
+// all their reads are in flight together, and the walk over the outputs shifts
+// the two windows instead of reading element by element (a chain of reads).
+// walk() merges E outputs (`valid` of them), decides duplicates and liveness
+// and returns the mask of kept outputs.  Which copy of a pair lives is looked
+// up after the walk, for all of the thread's pairs at once.
+template <int E>
+struct MergeWin {
+  // vectors, not arrays: a choice between two elements of an array becomes a
+  // load from a chosen address, which puts the array into scratch memory
+  typedef u64 VK __attribute__((ext_vector_type(E)));
+  typedef u32 VV __attribute__((ext_vector_type(E)));
+  VK ak, bk, ko;
+  VV av, bv, vo;
+  u32 prev;  // A's element before the window (VINF: none; ids are below VINF)
+
+  // A[i, ...) of na elements, B[j, ...) of nb
+  template <class AA, class AB>
+  PBH_INL void load(AA A, u32 i, u32 na, AB B, u32 j, u32 nb) {
+#pragma unroll
+    for (int s = 0; s < E; ++s) {
+      const bool ia = i + s < na, ib = j + s < nb;
+      av[s] = ia ? A.v[i + s] : VINF;
+      bv[s] = ib ? B.v[j + s] : VINF;
+      ak[s] = ia ? A.k[i + s] : 0ull;
+      bk[s] = ib ? B.k[j + s] : 0ull;
+    }
+    prev = i > 0 ? A.v[i - 1] : VINF;
+  }
+
+  template <class T>
+  PBH_INL u32 walk(const T& t, u32 valid, const u64* cur, bool filterB, int prefer) {
+    u64 alt[E];  // the other copy's key where the current key decides
+    u32 keep = 0, ask = 0, askb = 0;
+#pragma unroll
+    for (int s = 0; s < E; ++s) {
+      const bool in = (u32)s < valid, takeA = av[0] <= bv[0], dup = av[0] == bv[0];
+      const u64 ka = ak[0], kb = bk[0];
+      u64 k = takeA ? ka : kb;
+      bool kp = in;
+      alt[s] = kb;
+      if (takeA) {
+        if (dup && ka != kb) {
+          if (prefer == PREFER_B)
+            k = kb;
+          else if (prefer == PREFER_LIVE) {
+            if (cur)
+              ask |= (u32)in << s;
+            else
+              k = kb < ka ? kb : ka;
+          }
+        }
+      } else {
+        kp = in && prev != bv[0];
+        if (filterB) askb |= (u32)kp << s;
+      }
+      ko[s] = k;
+      vo[s] = takeA ? av[0] : bv[0];
+      keep |= (u32)kp << s;
+      prev = takeA ? av[0] : prev;
+#pragma unroll
+      for (int x = 0; x + 1 < E; ++x) {
+        if (x + 1 >= E - s) continue;  // what no later output reads
+        av[x] = takeA ? av[x + 1] : av[x];
+        ak[x] = takeA ? ak[x + 1] : ak[x];
+        bv[x] = takeA ? bv[x] : bv[x + 1];
+        bk[x] = takeA ? bk[x] : bk[x + 1];
+      }
+    }
+    if (ask | askb) {
+      u64 c[E];
+#pragma unroll
+      for (int s = 0; s < E; ++s) c[s] = ((ask | askb) >> s) & 1u ? t.load_cur(cur + vo[s]) : 0ull;
+#pragma unroll
+      for (int s = 0; s < E; ++s) {
+        const bool q = ((ask | askb) >> s) & 1u;
+        const bool other = q && ko[s] != c[s];
+        const bool second = other && ((ask >> s) & 1u) && alt[s] == c[s];
+        ko[s] = second ? alt[s] : ko[s];
+        if (other && !second) keep &= ~(1u << s);
+      }
+    }
+    return keep;
+  }
+};
+
+// What a merge counts of its outputs on the way: how many are <= p.
+struct CountLe {
+  KV p;
+  u32 n;
+};
+
+// Places a thread's kept outputs (a prefix sum over the team) and counts those
+// <= le->p; returns the tile's output count.
+template <class T, int E, class AC>
+PBH_INL u32 merge_store(const T& t, const MergeWin<E>& w, u32 keep, AC C, u32 out, CountLe* le) {
+  u32 x = (u32)__builtin_popcount(keep), tot;
+  if (le) {
+    u32 c = 0;
+#pragma unroll
+    for (int s = 0; s < E; ++s) c += ((keep >> s) & 1u) && kv_le(KV{w.ko[s], w.vo[s]}, le->p) ? 1u : 0u;
+    x |= c << 16;  // a tile has at most 2^15 outputs
+  }
+  u32 o = out + (t.scan_excl(x, &tot) & 0xFFFFu);
+#pragma unroll
+  for (int s = 0; s < E; ++s)
+    if ((keep >> s) & 1u) {
+      C.k[o] = w.ko[s];
+      C.v[o] = w.vo[s];
+      ++o;
+    }
+  if (le) le->n += tot >> 16;
+  return tot & 0xFFFFu;
+}
+
 template <class T, int E, class AA, class AB, class AC>
-PBH_INL u32 merge_dedup_e(const T& t, AA A, u32 na, AB B, u32 nb, AC C, const u64* cur, bool filterB, int prefer) {
+PBH_INL u32 merge_dedup_e(const T& t, AA A, u32 na, AB B, u32 nb, AC C, const u64* cur, bool filterB, int prefer,
+                          CountLe* le) {
   const u32 total = na + nb;
   u32 out = 0;
   for (u32 base = 0; base < total; base += (u32)T::kNT * E) {
     u32 d0 = base + (u32)t.tid() * E;
     d0 = d0 < total ? d0 : total;
-    u32 d1 = d0 + E < total ? d0 + E : total;
-    u32 i = merge_path(A.v, na, B.v, nb, d0), j = d0 - i;
-    u64 ko[E];
-    u32 vo[E];
-    u32 keep = 0;
-#pragma unroll
-    for (int s = 0; s < E; ++s) {
-      ko[s] = 0;
-      vo[s] = 0;
-      if (d0 + s < d1) {
-        bool takeA = i < na && (j >= nb || A.v[i] <= B.v[j]);
-        if (takeA) {
-          u64 ka = A.k[i];
-          u32 va = A.v[i];
-          bool kp = true;
-          if (j < nb && B.v[j] == va) {
-            u64 kb = B.k[j];
-            if (prefer == PREFER_B) {
-              ka = kb;
-            } else if (prefer == PREFER_A) {
-            } else if (kb != ka) {
-              if (cur) {
-                u64 c = t.load_cur(cur + va);
-                if (ka == c) {
-                } else if (kb == c) {
-                  ka = kb;
-                } else {
-                  kp = false;
-                }
-              } else if (kb < ka) {
-                ka = kb;
-              }
-            }
-          }
-          ko[s] = ka;
-          vo[s] = va;
-          keep |= (u32)kp << s;
-          ++i;
-        } else {
-          u64 kb = B.k[j];
-          u32 vb = B.v[j];
-          bool kp = !(i > 0 && A.v[i - 1] == vb);
-          if (kp && filterB && t.load_cur(cur + vb) != kb) kp = false;
-          ko[s] = kb;
-          vo[s] = vb;
-          keep |= (u32)kp << s;
-          ++j;
-        }
-      }
-    }
-    u32 tot;
-    u32 w = out + t.scan_excl((u32)__builtin_popcount(keep), &tot);
-#pragma unroll
-    for (int s = 0; s < E; ++s)
-      if ((keep >> s) & 1u) {
-        C.k[w] = ko[s];
-        C.v[w] = vo[s];
-        ++w;
-      }
-    out += tot;
+    const u32 i = merge_path<T::kNT == 64 && in_lds<AA>::v && in_lds<AB>::v>(A.v, na, B.v, nb, d0);
+    MergeWin<E> w;
+    w.load(A, i, na, B, d0 - i, nb);
+    const u32 keep = w.walk(t, total - d0, cur, filterB, prefer);
+    out += merge_store<T, E>(t, w, keep, C, out, le);
   }
   t.sync();
   return out;
@@ -333,7 +444,7 @@ PBH_INL void stage_setup(T& t, BP base) {
 // merge-path searches and walks run on LDS.
 template <class T, class AA, class AB, class AC>
 PBH_INL u32 merge_dedup_staged(const T& t, AA A, u32 na, AB B, u32 nb, AC C, const u64* cur, bool filterB,
-                               int prefer) {
+                               int prefer, CountLe* le) {
   constexpr int E = T::kE;
   constexpr u32 TILE = (u32)T::kNT * E;
   constexpr u32 W = TILE + 2u;
@@ -349,7 +460,7 @@ PBH_INL u32 merge_dedup_staged(const T& t, AA A, u32 na, AB B, u32 nb, AC C, con
     ntile = ntile < (u32)T::kNT ? ntile : (u32)T::kNT;
     for (u32 j = (u32)t.tid(); j <= ntile; j += (u32)T::kNT) {
       const u64 dg = (u64)cbase + (u64)j * TILE;
-      sp[j] = merge_path(A.v, na, B.v, nb, dg < total ? (u32)dg : total);
+      sp[j] = merge_path<false>(A.v, na, B.v, nb, dg < total ? (u32)dg : total);
     }
     t.sync();
     for (u32 k = 0; k < ntile; ++k) {
@@ -392,69 +503,16 @@ PBH_INL u32 merge_dedup_staged(const T& t, AA A, u32 na, AB B, u32 nb, AC C, con
         }
       }
       t.sync();
-      // this thread's outputs [e0, e1) of the tile, relative to d0
+      // this thread's outputs of the tile, from e0 (relative to d0)
       u32 e0 = (u32)t.tid() * E;
       e0 = e0 < d1 - d0 ? e0 : d1 - d0;
-      const u32 e1 = e0 + E < d1 - d0 ? e0 + E : d1 - d0;
-      u32 i = a0 + merge_path(va + (a0 - abase), a1 - a0, vb, b1 - b0, e0), j = d0 + e0 - i;
-      u64 ko[E];
-      u32 vo[E];
-      u32 keep = 0;
-#pragma unroll
-      for (int s = 0; s < E; ++s) {
-        ko[s] = 0;
-        vo[s] = 0;
-        if (e0 + s < e1) {
-          const bool takeA = i < na && (j >= nb || va[i - abase] <= vb[j - b0]);
-          if (takeA) {
-            u64 kx = ka[i - abase];
-            const u32 vx = va[i - abase];
-            bool kp = true;
-            if (j < nb && vb[j - b0] == vx) {
-              const u64 ky = kb[j - b0];
-              if (prefer == PREFER_B) {
-                kx = ky;
-              } else if (prefer == PREFER_A) {
-              } else if (ky != kx) {
-                if (cur) {
-                  const u64 c = t.load_cur(cur + vx);
-                  if (kx == c) {
-                  } else if (ky == c) {
-                    kx = ky;
-                  } else {
-                    kp = false;
-                  }
-                } else if (ky < kx) {
-                  kx = ky;
-                }
-              }
-            }
-            ko[s] = kx;
-            vo[s] = vx;
-            keep |= (u32)kp << s;
-            ++i;
-          } else {
-            const u64 ky = kb[j - b0];
-            const u32 vy = vb[j - b0];
-            bool kp = !(i > 0 && va[i - 1 - abase] == vy);
-            if (kp && filterB && t.load_cur(cur + vy) != ky) kp = false;
-            ko[s] = ky;
-            vo[s] = vy;
-            keep |= (u32)kp << s;
-            ++j;
-          }
-        }
-      }
-      u32 tot;
-      u32 w = out + t.scan_excl((u32)__builtin_popcount(keep), &tot);
-#pragma unroll
-      for (int s = 0; s < E; ++s)
-        if ((keep >> s) & 1u) {
-          C.k[w] = ko[s];
-          C.v[w] = vo[s];
-          ++w;
-        }
-      out += tot;
+      const u32 i = merge_path<T::kNT == 64>(va + (a0 - abase), a1 - a0, vb, b1 - b0, e0), j = e0 - i;
+      // the windows as arrays that start at A[abase] and B[b0]
+      ArrT<decltype(t.stk), decltype(t.stv)> SA{ka, va}, SB{kb, vb};
+      MergeWin<E> w;
+      w.load(SA, a0 - abase + i, aend - abase, SB, j, bend - b0);
+      const u32 keep = w.walk(t, d1 - d0 - e0, cur, filterB, prefer);
+      out += merge_store<T, E>(t, w, keep, C, out, le);
       t.sync();  // the next tile overwrites the windows
     }
   }
@@ -462,55 +520,269 @@ PBH_INL u32 merge_dedup_staged(const T& t, AA A, u32 na, AB B, u32 nb, AC C, con
   return out;
 }
 
-// Arrays that live in LDS are merged in place; the others (HBM) go through
-// the staging area when the team has one.
-template <class A>
-struct in_lds {
-  static constexpr bool v = false;
-};
-template <>
-struct in_lds<ArrT<u64 PBH_LDS*, u32 PBH_LDS*>> {
-  static constexpr bool v = true;
-};
-
-// Merge with the per-thread walk length chosen by size: a long walk amortises
-// the merge-path search on big arrays, a short one keeps the chain of
-// dependent reads short on the small top levels.  Arrays in HBM larger than a
-// tile are merged through the LDS staging area when there is one.
-template <class T, class AA, class AB, class AC>
-PBH_INL u32 merge_dedup(const T& t, AA A, u32 na, AB B, u32 nb, AC C, const u64* cur, bool filterB,
-                        int prefer = PREFER_LIVE) {
-  if constexpr (T::kStage && !in_lds<AA>::v && !in_lds<AB>::v) {
-    if (t.stk && na + nb > (u32)T::kNT * T::kE)
-      return merge_dedup_staged(t, A, na, B, nb, C, cur, filterB, prefer);
-  }
-  if (T::kE > 2 && na + nb <= 2u * (u32)T::kNT)
-    return merge_dedup_e<T, 2>(t, A, na, B, nb, C, cur, filterB, prefer);
-  return merge_dedup_e<T, T::kE>(t, A, na, B, nb, C, cur, filterB, prefer);
+// Merge + DeleteDuplicates of a short array P with an array Q of at most R * kW
+// elements, by one wavefront in registers: P sits in the lanes (one element
+// each), Q in rows of kW elements.  Each element of P in turn is compared with
+// all rows: ballots count Q's ids below it (its place), the lanes count P's
+// ids below theirs.  No search, no walk, and few instructions: one wavefront
+// spends 5 to 8 cycles on each instruction, so their number is its time.  A
+// pair of copies is decided at P's lane.  R = 1 covers arrays of up to one
+// element per lane without loops over rows.
+constexpr u32 SHORT = 16;
+template <class T>
+PBH_INL u32 small_rows(u32 na, u32 nb) {  // rows of the longer array, 0: too large for this form
+  const u32 p = na < nb ? na : nb, q = na < nb ? nb : na;
+  const u32 rows = (q + (u32)T::kW - 1) / (u32)T::kW;
+  return p <= SHORT && p <= (u32)T::kW && rows <= 4u && p * rows <= 24u ? (rows ? rows : 1u) : 0u;
 }
 
-// |{e in A : e <= p}|
+template <int R>
+struct SmallMerge {
+  u64 pk, qk[R];
+  u32 pv, qv[R];
+  u32 place;         // Q's ids below this lane's id of P
+  u32 below[R];      // P's ids below each of this lane's ids of Q
+  bool pin, qin[R];  // outputs: P's elements but dead pairs, Q's but copies
+  u32 dups, deads;   // P's elements with a copy in Q / with no live copy
+  u32 m;             // outputs
 
-template <class T, class AA>
-PBH_INL u32 count_le(const T& t, AA A, u32 n, KV p) {
-  if (p.k == KINF) return n;
-  u32 c = 0;
-  for (u32 base = 0; base < n; base += (u32)T::kNT * T::kRU) {
-    u64 k[T::kRU];
-    u32 v[T::kRU];
-#pragma unroll
-    for (int r = 0; r < T::kRU; ++r) {
-      const u32 x = base + (u32)r * (u32)T::kNT + (u32)t.tid();
-      k[r] = x < n ? A.k[x] : KINF;
-      v[r] = x < n ? A.v[x] : VINF;
+  template <class T, class AP, class AQ>
+  PBH_INL void run(const T& t, AP P, u32 np, AQ Q, u32 nq, bool p_is_a, const u64* cur, int prefer) {
+    constexpr u32 W = (u32)T::kW;
+    const u32 lane = (u32)t.lane();
+    // reads past the end are clamped to the last element, not branched around
+    pin = lane < np;
+    pk = 0;
+    pv = VINF;
+    if (np) {
+      const u32 pi = pin ? lane : np - 1;
+      pk = P.k[pi];
+      const u32 v = P.v[pi];
+      pv = pin ? v : VINF;
     }
 #pragma unroll
-    for (int r = 0; r < T::kRU; ++r) {
-      const u32 x = base + (u32)r * (u32)T::kNT + (u32)t.tid();
-      c += (x < n && kv_le(KV{k[r], v[r]}, p)) ? 1u : 0u;
+    for (int r = 0; r < R; ++r) {
+      qk[r] = 0;
+      qv[r] = VINF;
+      qin[r] = false;
+      below[r] = 0;
+      if ((u32)r * W >= nq) continue;
+      const u32 x = (u32)r * W + lane, xi = x < nq ? x : nq - 1;
+      qk[r] = Q.k[xi];
+      const u32 v = Q.v[xi];
+      qin[r] = x < nq;
+      qv[r] = qin[r] ? v : VINF;
+    }
+    place = 0;
+    dups = 0;
+    u64 other = 0;  // the copy's key in Q
+    for (u32 j = 0; j < np; ++j) {
+      const u32 s = t.lane_val(pv, (int)j);
+      u32 c = 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (r > 0 && (u32)r * W >= nq) continue;
+        c += (u32)__builtin_popcountll(t.ballot(qv[r] < s));
+        below[r] += qv[r] > s ? 1u : 0u;
+        const u64 e = t.ballot(qv[r] == s);
+        if (e) {
+          dups |= 1u << j;
+          qin[r] = qin[r] && qv[r] != s;
+          const u64 ko = t.lane_val64(qk[r], __builtin_ctzll(e));
+          other = lane == j ? ko : other;
+        }
+      }
+      place = lane == j ? c : place;
+    }
+    deads = 0;
+    if (dups && prefer != (p_is_a ? (int)PREFER_A : (int)PREFER_B)) {
+      const bool dup = pin && ((dups >> (lane & 31u)) & 1u);
+      if (prefer != PREFER_LIVE) {
+        pk = dup ? other : pk;
+      } else if (cur) {
+        u64 c = pk;
+        const bool ask = dup && pk != other;
+        if (ask) c = t.load_cur(cur + pv);
+        const bool second = ask && other == c, dead = ask && pk != c && other != c;
+        pk = second ? other : pk;
+        pin = pin && !dead;
+        deads = (u32)t.ballot(dead);
+      } else {
+        pk = dup && other < pk ? other : pk;
+      }
+    }
+    m = np + nq - (u32)__builtin_popcount(dups) - (u32)__builtin_popcount(deads);
+  }
+
+  // Outputs <= p.
+  template <class T>
+  PBH_INL u32 count_le(const T& t, KV p) const {
+    u32 c = (u32)__builtin_popcountll(t.ballot(pin && kv_le(KV{pk, pv}, p)));
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (r == 0 || t.any_lane(qin[r])) c += (u32)__builtin_popcountll(t.ballot(qin[r] && kv_le(KV{qk[r], qv[r]}, p)));
+    return c;
+  }
+
+  template <class T, class AC>
+  PBH_INL void store(const T& t, u32 nq, AC C) const {
+    constexpr u32 W = (u32)T::kW;
+    const u32 gone = dups | deads;
+    u32 o = (u32)t.lane() + place;
+    if (gone) o -= t.count_below(dups) + t.count_below(deads);
+    if (pin) {
+      C.k[o] = pk;
+      C.v[o] = pv;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (r > 0 && (u32)r * W >= nq) continue;
+      u32 x = (u32)r * W + (u32)t.lane() + below[r];
+      if (gone) {
+        const u32 lo = (1u << below[r]) - 1u;  // below <= SHORT
+        x -= (u32)__builtin_popcount(dups & lo) + (u32)__builtin_popcount(deads & lo);
+      }
+      if (qin[r]) {
+        C.k[x] = qk[r];
+        C.v[x] = qv[r];
+      }
     }
   }
-  return t.sum(c);
+
+  // The r-th smallest output, by taking out the smallest (or, if the rank is
+  // closer to the other end, the largest) one by one.
+  template <class T>
+  PBH_INL KV select(const T& t, u32 r) const {
+    const bool top = m - r + 1 < r;
+    const u64 fk = top ? KINF : 0ull;
+    const u32 fv = top ? VINF : 0u;
+    u64 bk = 0;
+    u32 bv = 0;
+    bool pl = pin, ql[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) ql[q] = qin[q];
+    for (u32 it = top ? m - r + 1 : r;; --it) {
+      bk = pl ? pk ^ fk : KINF;
+      bv = pl ? pv ^ fv : VINF;
+#pragma unroll
+      for (int q = 0; q < R; ++q) {
+        const u64 k = ql[q] ? qk[q] ^ fk : KINF;
+        const u32 v = ql[q] ? qv[q] ^ fv : VINF;
+        const bool lt = kv_less(KV{k, v}, KV{bk, bv});
+        bk = lt ? k : bk;
+        bv = lt ? v : bv;
+      }
+      t.minkv(bk, bv);
+      bk ^= fk;
+      bv ^= fv;
+      if (it == 1) return KV{bk, bv};
+      pl = pl && pv != bv;  // (ids are distinct)
+#pragma unroll
+      for (int q = 0; q < R; ++q) ql[q] = ql[q] && qv[q] != bv;
+    }
+  }
+
+  // Stable three-way split of the outputs (as partition3).
+  template <class T, class A0, class A1>
+  PBH_INL void split(const T& t, KV p1, KV p2, A0 O0, A1 O1, A1 O2, const u64* live0, u32* n0, u32* n1,
+                     u32* n2) const {
+    constexpr u32 W = (u32)T::kW;
+    const bool two = p2.k == KINF && p2.v == VINF;  // nothing above p2
+    auto cls = [&](bool in, u64 k, u32 v) -> u32 {
+      u32 c = kv_le(KV{k, v}, p1) ? 0u : 1u;
+      if (!two) c = c && !kv_le(KV{k, v}, p2) ? 2u : c;
+      if (live0) {
+        u64 l = k;
+        if (in && c == 0u) l = t.load_cur(live0 + v);
+        c = l != k ? 3u : c;
+      }
+      return in ? c : 3u;
+    };
+    const u32 cp = cls(pin, pk, pv);
+    const u32 p0 = (u32)t.ballot(cp == 0u), pb1 = (u32)t.ballot(cp == 1u), pb2 = two ? 0u : (u32)t.ballot(cp == 2u);
+    u32 c0 = 0, c1 = 0, c2 = 0;  // Q's outputs of the rows before
+    u32 of = t.count_below(cp == 0u ? p0 : (cp == 1u ? pb1 : pb2));
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (r > 0 && !t.any_lane(qin[r])) continue;
+      const u32 c = cls(qin[r], qk[r], qv[r]);
+      const u64 b0 = t.ballot(c == 0u), b1 = t.ballot(c == 1u), b2 = two ? 0ull : t.ballot(c == 2u);
+      {
+        const u32 lo = (1u << below[r]) - 1u;
+        const u32 pm = c == 0u ? p0 : (c == 1u ? pb1 : pb2);
+        const u32 o = (c == 0u ? c0 : (c == 1u ? c1 : c2)) + t.count_below(c == 0u ? b0 : (c == 1u ? b1 : b2)) +
+                      (u32)__builtin_popcount(pm & lo);
+        auto ok = c == 0u ? O0.k : (c == 1u ? O1.k : O2.k);
+        auto ov = c == 0u ? O0.v : (c == 1u ? O1.v : O2.v);
+        if (c < 3u) {
+          ok[o] = qk[r];
+          ov[o] = qv[r];
+        }
+      }
+      {  // P's elements: Q's outputs of their class before their place
+        const u64 bm = cp == 0u ? b0 : (cp == 1u ? b1 : b2);
+        const u32 y = place > (u32)r * W ? place - (u32)r * W : 0u;
+        of += (u32)__builtin_popcountll(y >= W ? bm : bm & ((1ull << y) - 1ull));
+      }
+      c0 += (u32)__builtin_popcountll(b0);
+      c1 += (u32)__builtin_popcountll(b1);
+      c2 += (u32)__builtin_popcountll(b2);
+    }
+    {
+      auto ok = cp == 0u ? O0.k : (cp == 1u ? O1.k : O2.k);
+      auto ov = cp == 0u ? O0.v : (cp == 1u ? O1.v : O2.v);
+      if (cp < 3u) {
+        ok[of] = pk;
+        ov[of] = pv;
+      }
+    }
+    *n0 = c0 + (u32)__builtin_popcount(p0);
+    *n1 = c1 + (u32)__builtin_popcount(pb1);
+    *n2 = c2 + (u32)__builtin_popcount(pb2);
+  }
+};
+
+template <int R, class T, class AA, class AB, class AC>
+PBH_INL u32 merge_small(const T& t, AA A, u32 na, AB B, u32 nb, AC C, const u64* cur, int prefer, CountLe* le) {
+  SmallMerge<R> s;
+  u32 nq = nb;
+  if constexpr (same_arr<AA, AB>::v) {
+    const bool pa = na <= nb;
+    nq = pa ? nb : na;
+    s.run(t, pa ? A : B, pa ? na : nb, pa ? B : A, nq, pa, cur, prefer);
+  } else if (na <= nb) {
+    s.run(t, A, na, B, nb, true, cur, prefer);
+  } else {
+    nq = na;
+    s.run(t, B, nb, A, na, false, cur, prefer);
+  }
+  s.store(t, nq, C);
+  if (le) le->n += s.count_le(t, le->p);
+  t.sync();
+  return s.m;
+}
+
+// Merge + DeleteDuplicates by whichever form suits the team and the sizes: one
+// wavefront takes a short array into registers (SmallMerge); otherwise every
+// thread walks from its merge-path split, for arrays in HBM of more than a
+// tile through the LDS staging area when the team has one.
+template <class T, class AA, class AB, class AC>
+PBH_INL u32 merge_dedup(const T& t, AA A, u32 na_, AB B, u32 nb_, AC C, const u64* cur, bool filterB,
+                        int prefer = PREFER_LIVE, CountLe* le = nullptr) {
+  const u32 na = t.uni(na_), nb = t.uni(nb_);
+  if constexpr (T::kNW == 1) {
+    const u32 rows = filterB ? 0u : small_rows<T>(na, nb);
+    if (rows == 1) return merge_small<1>(t, A, na, B, nb, C, cur, prefer, le);
+    if (rows) return merge_small<4>(t, A, na, B, nb, C, cur, prefer, le);
+  }
+  if constexpr (T::kStage && !in_lds<AA>::v && !in_lds<AB>::v) {
+    if (t.stk && na + nb > (u32)T::kNT * T::kE)
+      return merge_dedup_staged(t, A, na, B, nb, C, cur, filterB, prefer, le);
+  }
+  if constexpr (T::kNT >= 256) {
+    if (na + nb <= 2u * (u32)T::kNT) return merge_dedup_e<T, 2>(t, A, na, B, nb, C, cur, filterB, prefer, le);
+  }
+  return merge_dedup_e<T, T::kM>(t, A, na, B, nb, C, cur, filterB, prefer, le);
 }
 
 // Finds the histogram bin where the r-th element (1-based) falls.
@@ -548,7 +820,8 @@ PBH_INL void hist_pick(const T& t, u32 r, u32* D, u32* below, u32* cnt) {
 // repeated maxima) over at most 8 elements per thread held in registers; for
 // the small ranks that Resolve asks for when one element leaves B_0.
 template <class T, class AA>
-PBH_INL KV select_small(const T& t, AA A, u32 n, u32 r) {
+PBH_INL KV select_small(const T& t, AA A, u32 n_, u32 r_) {
+  const u32 n = t.uni(n_), r = t.uni(r_);
   const bool top = (n - r + 1) < r;
   u32 it = top ? n - r + 1 : r;
   u64 kk[8];
@@ -559,7 +832,7 @@ PBH_INL KV select_small(const T& t, AA A, u32 n, u32 r) {
     u32 x = (u32)t.tid() + (u32)j * (u32)T::kNT;
     kk[j] = 0;
     vv[j] = 0;
-    if (x < n) {
+    if ((u32)(j * T::kNT) < n && x < n) {
       kk[j] = top ? ~A.k[x] : A.k[x];
       vv[j] = top ? ~A.v[x] : A.v[x];
       live |= 1u << j;
@@ -572,7 +845,7 @@ PBH_INL KV select_small(const T& t, AA A, u32 n, u32 r) {
     bv = VINF;
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      if ((live >> j) & 1u) {
+      if ((u32)(j * T::kNT) < n && ((live >> j) & 1u)) {
         bool lt = kk[j] < bk || (kk[j] == bk && vv[j] < bv);
         bk = lt ? kk[j] : bk;
         bv = lt ? vv[j] : bv;
@@ -580,111 +853,132 @@ PBH_INL KV select_small(const T& t, AA A, u32 n, u32 r) {
     t.minkv(bk, bv);
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-      if (((live >> j) & 1u) && kk[j] == bk && vv[j] == bv) live &= ~(1u << j);
+      if ((u32)(j * T::kNT) < n && ((live >> j) & 1u) && kk[j] == bk && vv[j] == bv) live &= ~(1u << j);
   }
   return top ? KV{~bk, ~bv} : KV{bk, bv};
 }
 
-// r-th smallest of n <= 2 * team size elements by counting: every element
-// (at most two per thread) counts the elements below it; the one with r - 1
-// below is the answer ((key, id) pairs are distinct).
-template <class T, class AA>
-PBH_INL KV select_rank(const T& t, AA A, u32 n, u32 r) {
-  const u32 x0 = (u32)t.tid(), x1 = x0 + (u32)T::kNT;
-  const u64 k0 = x0 < n ? A.k[x0] : KINF, k1 = x1 < n ? A.k[x1] : KINF;
-  const u32 v0 = x0 < n ? A.v[x0] : VINF, v1 = x1 < n ? A.v[x1] : VINF;
-  u32 c0 = 0, c1 = 0;
-  for (u32 y = 0; y < n; ++y) {
-    const u64 ky = A.k[y];
-    const u32 vy = A.v[y];
-    c0 += (ky < k0 || (ky == k0 && vy < v0)) ? 1u : 0u;
-    c1 += (ky < k1 || (ky == k1 && vy < v1)) ? 1u : 0u;
-  }
-  t.sync();
-  if (x0 < n && c0 + 1 == r) {
-    t.sh->wk[0] = k0;
-    t.sh->wv[0] = v0;
-  }
-  if (x1 < n && c1 + 1 == r) {
-    t.sh->wk[0] = k1;
-    t.sh->wv[0] = v1;
-  }
-  t.sync();
-  const KV res{t.sh->wk[0], t.sh->wv[0]};
-  t.sync();
-  return res;
-}
-
-// Select over an array in HBM of at most RS elements per thread: every
-// element is read once into registers and the radix passes run there (the
-// same passes as select_kth, without re-reading the array for each byte).
-constexpr int RS = 16;
-
-template <class T, class AA>
-PBH_INL KV select_reg(const T& t, AA A, u32 n, u32 r) {
-  u64 k[RS];
-  u32 v[RS];
-  u64 lo = KINF, hi = 0;
+// Select over at most Q elements per thread, read once into registers: one
+// histogram of the eight bits below the highest one where the keys differ
+// usually leaves a few candidates, which go to LDS and are ranked by counting,
+// by every wavefront for itself.  More than SEL_FEW candidates go through
+// another eight bits (ids after the keys).  Every wavefront finds the bin by
+// itself (four bins per lane), so a pass has two barriers; 512 elements,
+// 256 threads: 8,800 cycles for three passes of the radix form, about 2,500
+// for this.
+constexpr u32 SEL_FEW = 32;
+template <int Q, class T, class AA>
+PBH_INL KV select_hist(const T& t, AA A, u32 n, u32 r) {
+  u64 k[Q];
+  u32 v[Q], act = 0;
+  const u64 k0 = A.k[0];
+  u64 df = 0;
 #pragma unroll
-  for (int q = 0; q < RS; ++q) {
+  for (int q = 0; q < Q; ++q) {
     const u32 x = (u32)t.tid() + (u32)q * (u32)T::kNT;
-    k[q] = x < n ? A.k[x] : KINF;
-    v[q] = x < n ? A.v[x] : VINF;
+    k[q] = k0;
+    v[q] = 0;
+    if ((u32)q * (u32)T::kNT >= n) continue;
+    const u32 xi = x < n ? x : n - 1;
+    k[q] = A.k[xi];
+    v[q] = A.v[xi];
+    act |= x < n ? 1u << q : 0u;
   }
 #pragma unroll
-  for (int q = 0; q < RS; ++q) {
-    const bool in = (u32)t.tid() + (u32)q * (u32)T::kNT < n;
-    lo = k[q] < lo ? k[q] : lo;
-    hi = (in && k[q] > hi) ? k[q] : hi;
+  for (int q = 0; q < Q; ++q) df |= k[q] ^ k0;
+  u32 dh = t.wave_or32((u32)(df >> 32)), dl = t.wave_or32((u32)df);
+  if constexpr (T::kNW > 1) {
+    if (t.lane() == 0) t.sh->wk[t.wave()] = ((u64)dh << 32) | dl;
   }
-  t.minmax64(lo, hi);
-  const u64 span = hi - lo;
-  const int nb = span ? 64 - __builtin_clzll(span) : 0;
-  const int top = (nb + 7) & ~7;
-  u64 prefix = 0;
-  u32 cnt = n;
-  for (int s = top - 8; s >= 0; s -= 8) {
+  for (u32 b = (u32)t.tid(); b < 256; b += (u32)T::kNT) t.sh->hist[b] = 0;
+  if (t.tid() == 0) t.sh->b32[0] = 0;
+  t.sync();
+  if constexpr (T::kNW > 1) {
+    u64 d = 0;
+#pragma unroll
+    for (int w = 0; w < T::kNW; ++w) d |= t.sh->wk[w];
+    dh = t.uni((u32)(d >> 32));
+    dl = t.uni((u32)d);
+  }
+  // digits of the 96-bit value (key, id) from bit `lo` up: the ids' 32 bits,
+  // then the key's
+  const int top = dh ? 96 - __builtin_clz(dh) : (dl ? 64 - __builtin_clz(dl) : 32);
+  int lo = top > 8 ? top - 8 : 0;
+  auto digit = [&](u64 kk, u32 vv) -> u32 {
+    const u64 w = lo >= 32 ? kk >> (lo - 32) : ((kk << 32) | vv) >> lo;
+    return (u32)w & 255u;
+  };
+  u32 cnt;
+  for (;;) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if ((u32)q * (u32)T::kNT < n && ((act >> q) & 1u)) t.hist_add(t.sh->hist, digit(k[q], v[q]));
+    t.sync();
+    // the bin of rank r: four bins per lane, scanned by every wavefront
+    u32 D = 0, below = 0;
+    cnt = 0;
+    if constexpr (T::kW == 1) {
+      for (u32 b = 0, run = 0; b < 256; run += t.sh->hist[b], ++b)
+        if (run < r && r <= run + t.sh->hist[b]) D = b, below = run, cnt = t.sh->hist[b];
+    } else {
+      u32 h[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) h[b] = t.sh->hist[4 * t.lane() + b];
+      const u32 s = h[0] + h[1] + h[2] + h[3], inc = t.wave_scan(s);
+      const int l = __builtin_ctzll(t.ballot(inc >= r));  // the first lane that reaches the rank
+      u32 run = t.lane_val(inc - s, l);
+      bool found = false;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const u32 x = t.lane_val(h[b], l);
+        if (!found && r <= run + x) {
+          D = 4u * (u32)l + (u32)b;
+          below = run;
+          cnt = x;
+          found = true;
+        }
+        run += x;
+      }
+    }
+    r -= below;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if ((u32)q * (u32)T::kNT < n && ((act >> q) & 1u) && digit(k[q], v[q]) != D) act &= ~(1u << q);
+    if (cnt <= SEL_FEW || lo == 0) break;
+    lo = lo > 8 ? lo - 8 : 0;
+    t.sync();  // every wavefront has read the histogram
     for (u32 b = (u32)t.tid(); b < 256; b += (u32)T::kNT) t.sh->hist[b] = 0;
     t.sync();
+  }
+  // the candidates (the values are distinct: one is left at the last bits)
 #pragma unroll
-    for (int q = 0; q < RS; ++q) {
-      const bool in = (u32)t.tid() + (u32)q * (u32)T::kNT < n;
-      const u64 dk = k[q] - lo;
-      const bool m = in && ((s + 8 >= 64) ? true : ((dk >> (s + 8)) == prefix));
-      if (m) t.hist_add(t.sh->hist, (u32)(dk >> s) & 255u);
+  for (int q = 0; q < Q; ++q)
+    if ((u32)q * (u32)T::kNT < n && ((act >> q) & 1u)) {
+      const u32 o = t.hist_next(&t.sh->b32[0]);
+      t.sh->ex0[o] = k[q];
+      t.sh->exd[o] = v[q];
     }
-    t.sync();
-    u32 D, below;
-    hist_pick(t, r, &D, &below, &cnt);
-    prefix = (prefix << 8) | D;
-    r -= below;
-  }
-  const u64 K = lo + prefix;
-  if (cnt == 1) {
-#pragma unroll
-    for (int q = 0; q < RS; ++q)
-      if ((u32)t.tid() + (u32)q * (u32)T::kNT < n && k[q] == K) t.sh->b32[3] = v[q];
-    t.sync();
-    const u32 id = t.sh->b32[3];
-    t.sync();
-    return KV{K, id};
-  }
-  u32 idp = 0;
-  for (int s = 24; s >= 0; s -= 8) {
-    for (u32 b = (u32)t.tid(); b < 256; b += (u32)T::kNT) t.sh->hist[b] = 0;
-    t.sync();
-#pragma unroll
-    for (int q = 0; q < RS; ++q) {
-      const bool in = (u32)t.tid() + (u32)q * (u32)T::kNT < n;
-      if (in && k[q] == K && (s == 24 || (v[q] >> (s + 8)) == idp)) t.hist_add(t.sh->hist, (v[q] >> s) & 255u);
+  t.sync();
+  KV e = kv_inf();
+  if constexpr (T::kW == 1) {
+    for (u32 x = 0; x < cnt; ++x) {
+      u32 c = 0;
+      for (u32 y = 0; y < cnt; ++y)
+        c += kv_less(KV{t.sh->ex0[y], t.sh->exd[y]}, KV{t.sh->ex0[x], t.sh->exd[x]}) ? 1u : 0u;
+      if (c + 1 == r) e = KV{t.sh->ex0[x], t.sh->exd[x]};
     }
-    t.sync();
-    u32 D, below, c2;
-    hist_pick(t, r, &D, &below, &c2);
-    idp = (idp << 8) | D;
-    r -= below;
+  } else {
+    const u32 x = (u32)t.lane() < cnt ? (u32)t.lane() : cnt - 1;
+    const u64 ck = t.sh->ex0[x];
+    const u32 cv = t.sh->exd[x];
+    u32 c = 0;
+    for (u32 y = 0; y < cnt; ++y)
+      c += kv_less(KV{t.lane_val64(ck, (int)y), t.lane_val(cv, (int)y)}, KV{ck, cv}) ? 1u : 0u;
+    const int l = __builtin_ctzll(t.ballot((u32)t.lane() < cnt && c + 1 == r));
+    e = KV{t.lane_val64(ck, l), t.lane_val(cv, l)};
   }
-  return KV{K, idp};
+  t.sync();  // the scratch is free again
+  return e;
 }
 
 // Select(A, r): the r-th smallest (key, id) of A, 1 <= r <= n.  Radix select,
@@ -692,15 +986,16 @@ PBH_INL KV select_reg(const T& t, AA A, u32 n, u32 r) {
 // range needs), then over the id among elements with the selected key.  The
 // paper sorted with a radix sort to select (Section 4.1); a radix select reads
 // the candidates once per byte and sorts nothing.  Ranks within two of either
-// end of a small array use select_small; other ranks in arrays of at most two
-// elements per thread use select_rank; arrays in HBM of at most RS elements
-// per thread use select_reg.
+// end of a small array use select_small; other ranks in arrays of at most four
+// elements per thread (in HBM: 16) use select_hist.
 template <class T, class AA>
-PBH_INL KV select_kth(const T& t, AA A, u32 n, u32 r) {
+PBH_INL KV select_kth(const T& t, AA A, u32 n_, u32 r_) {
+  const u32 n = t.uni(n_);
+  u32 r = t.uni(r_);
   if (n <= 8u * (u32)T::kNT && (r <= 2 || n - r + 1 <= 2)) return select_small(t, A, n, r);
-  if (n <= 2u * (u32)T::kNT) return select_rank(t, A, n, r);
-  if constexpr (T::kStage && !in_lds<AA>::v) {
-    if (n <= (u32)RS * (u32)T::kNT) return select_reg(t, A, n, r);
+  if (n <= 4u * (u32)T::kNT) return select_hist<4>(t, A, n, r);
+  if constexpr (!in_lds<AA>::v) {
+    if (n <= 16u * (u32)T::kNT) return select_hist<16>(t, A, n, r);
   }
   u64 lo = KINF, hi = 0;
   for (u32 base = 0; base < n; base += (u32)T::kNT * T::kRU) {
@@ -792,69 +1087,111 @@ PBH_INL KV select_kth(const T& t, AA A, u32 n, u32 r) {
 }
 
 // Stable three-way split of A (order by id is kept in each part):
-// e <= p1 -> O0, p1 < e <= p2 -> O1, e > p2 -> O2.
+// e <= p1 -> O0, p1 < e <= p2 -> O1, e > p2 -> O2.  With live0, class-0
+// elements that are not live are dropped.
+// A tile is E rows of one element per thread (consecutive threads read and
+// write consecutive elements: no LDS bank conflicts, coalesced in HBM); places
+// within a row come from ballots.  One wavefront adds up the rows in scalars;
+// a larger team exchanges the rows' counts through LDS, one barrier per tile
+// (two areas in turn), and every wavefront scans them by itself.  Rows past
+// the end are skipped by scalar branches.
 template <class T, class AA, class A0, class A1, class A2>
-PBH_INL void partition3(const T& t, AA A, u32 n, KV p1, KV p2, A0 O0, A1 O1, A2 O2, u32* n0, u32* n1,
+PBH_INL void partition3(const T& t, AA A, u32 n_, KV p1, KV p2, A0 O0, A1 O1, A2 O2, u32* n0, u32* n1,
                         u32* n2, const u64* live0 = nullptr) {
-  // twice the elements per thread from HBM: more loads in flight per tile
-  constexpr int E = (T::kStage && !in_lds<AA>::v) ? 2 * T::kE : T::kE;
-  u32 c0t = 0, c1t = 0, c2t = 0;
-  for (u32 base = 0; base < n; base += (u32)T::kNT * E) {
-    u32 x0 = base + (u32)t.tid() * E;
+  // twice the elements per thread from HBM: more loads in flight per tile;
+  // at most one count per lane of a wavefront
+  constexpr int EW = ((T::kStage || T::kNT >= 256) && !in_lds<AA>::v) ? 2 * T::kE : T::kE;
+  constexpr int E = (T::kNW > 1 && EW * T::kNW > 64) ? 64 / T::kNW : EW;
+  const u32 n = t.uni(n_);
+  u32 c0 = 0, c1 = 0, c2 = 0;
+  u32 par = 0;
+  for (u32 base = 0; base < n; base += (u32)T::kNT * E, par ^= 128u) {
     u64 kk[E];
-    u32 vv[E];
-    u32 cl[E];
-    u32 c0 = 0, c1 = 0, c2 = 0;
+    u32 vv[E], cl[E], at[E];
 #pragma unroll
     for (int s = 0; s < E; ++s) {
+      const u32 x = base + (u32)s * (u32)T::kNT + (u32)t.tid();
       kk[s] = 0;
       vv[s] = 0;
-      cl[s] = 3;
-      if (x0 + s < n) {
-        kk[s] = A.k[x0 + s];
-        vv[s] = A.v[x0 + s];
-        KV e{kk[s], vv[s]};
-        cl[s] = kv_le(e, p1) ? 0u : (kv_le(e, p2) ? 1u : 2u);
-        // With live0, class-0 elements that are not live are dropped.
-        if (cl[s] == 0 && live0 && t.load_cur(live0 + vv[s]) != kk[s]) cl[s] = 3;
-        c0 += cl[s] == 0;
-        c1 += cl[s] == 1;
-        c2 += cl[s] == 2;
+      if (base + (u32)s * (u32)T::kNT < n && x < n) {
+        kk[s] = A.k[x];
+        vv[s] = A.v[x];
       }
     }
-    u32 tot;
-    u32 pre = t.scan_excl(c0 | (c1 << 16), &tot);
-    u32 tot2;
-    u32 pre2 = live0 ? t.scan_excl(c2, &tot2) : 0u;
-    u32 before = x0 < n ? x0 - base : n - base;
-    u32 o0 = c0t + (pre & 0xFFFFu), o1 = c1t + (pre >> 16);
-    u32 o2 = c2t + (live0 ? pre2 : (before - (pre & 0xFFFFu) - (pre >> 16)));
+    u64 cur[E];
+    if (live0) {
+#pragma unroll
+      for (int s = 0; s < E; ++s) {
+        const u32 x = base + (u32)s * (u32)T::kNT + (u32)t.tid();
+        cur[s] = kk[s];
+        if (x < n && kv_le(KV{kk[s], vv[s]}, p1)) cur[s] = t.load_cur(live0 + vv[s]);
+      }
+    }
 #pragma unroll
     for (int s = 0; s < E; ++s) {
-      if (cl[s] == 0) {
-        O0.k[o0] = kk[s];
-        O0.v[o0] = vv[s];
-        ++o0;
-      } else if (cl[s] == 1) {
-        O1.k[o1] = kk[s];
-        O1.v[o1] = vv[s];
-        ++o1;
-      } else if (cl[s] == 2) {
-        O2.k[o2] = kk[s];
-        O2.v[o2] = vv[s];
-        ++o2;
+      const u32 x = base + (u32)s * (u32)T::kNT + (u32)t.tid();
+      const KV e{kk[s], vv[s]};
+      cl[s] = 3u;
+      at[s] = 0;
+      if (base + (u32)s * (u32)T::kNT >= n) continue;
+      cl[s] = kv_le(e, p1) ? 0u : (kv_le(e, p2) ? 1u : 2u);
+      if (live0 && cur[s] != kk[s]) cl[s] = 3u;
+      if (x >= n) cl[s] = 3u;
+      const u64 b0 = t.ballot(cl[s] == 0u), b1 = t.ballot(cl[s] == 1u), b2 = t.ballot(cl[s] == 2u);
+      const u32 r0 = t.count_below(b0), r1 = t.count_below(b1), r2 = t.count_below(b2);
+      const u32 q0 = (u32)__builtin_popcountll(b0), q1 = (u32)__builtin_popcountll(b1),
+                q2 = (u32)__builtin_popcountll(b2);
+      if constexpr (T::kNW == 1) {
+        at[s] = cl[s] == 0u ? c0 + r0 : (cl[s] == 1u ? c1 + r1 : c2 + r2);
+        c0 += q0;
+        c1 += q1;
+        c2 += q2;
+      } else {
+        at[s] = cl[s] == 0u ? r0 : (cl[s] == 1u ? r1 : r2);
+        if (t.lane() == 0) t.sh->base[par + (u32)s * T::kNW + (u32)t.wave()] = q0 | q1 << 8 | q2 << 16;
       }
     }
-    u32 tile = n - base < (u32)T::kNT * E ? n - base : (u32)T::kNT * E;
-    u32 t0 = tot & 0xFFFFu, t1 = tot >> 16;
-    c0t += t0;
-    c1t += t1;
-    c2t += live0 ? tot2 : tile - t0 - t1;
+    if constexpr (T::kNW > 1) {
+      t.sync();
+      const u32 wv = t.uni((u32)t.wave());
+      const u32 rows = (n - base + (u32)T::kNT - 1) / (u32)T::kNT;  // rows of this tile that hold counts
+      const u32 w = (u32)t.lane() < (u32)(E * T::kNW) && (u32)t.lane() < rows * (u32)T::kNW
+                        ? t.sh->base[par + (u32)t.lane()]
+                        : 0u;
+      const u32 x01 = (w & 0xFFu) | (w & 0xFF00u) << 8, x2 = w >> 16;
+      const u32 i01 = t.wave_scan(x01), i2 = t.wave_scan(x2);
+      const u32 e01 = i01 - x01, e2 = i2 - x2;
+#pragma unroll
+      for (int s = 0; s < E; ++s) {
+        if (base + (u32)s * (u32)T::kNT >= n) continue;
+        const int l = s * T::kNW + (int)wv;
+        const u32 o01 = t.lane_val(e01, l), o2 = t.lane_val(e2, l);
+        at[s] += cl[s] == 0u ? c0 + (o01 & 0xFFFFu) : (cl[s] == 1u ? c1 + (o01 >> 16) : c2 + o2);
+      }
+      const u32 t01 = t.lane_val(i01, 63);
+      c0 += t01 & 0xFFFFu;
+      c1 += t01 >> 16;
+      c2 += t.lane_val(i2, 63);
+    }
+#pragma unroll
+    for (int s = 0; s < E; ++s) {
+      if (base + (u32)s * (u32)T::kNT >= n) continue;
+      if (cl[s] == 0u) {
+        O0.k[at[s]] = kk[s];
+        O0.v[at[s]] = vv[s];
+      } else if (cl[s] == 1u) {
+        O1.k[at[s]] = kk[s];
+        O1.v[at[s]] = vv[s];
+      } else if (cl[s] == 2u) {
+        O2.k[at[s]] = kk[s];
+        O2.v[at[s]] = vv[s];
+      }
+    }
   }
   t.sync();
-  *n0 = c0t;
-  *n1 = c1t;
-  *n2 = c2t;
+  *n0 = c0;
+  *n1 = c1;
+  *n2 = c2;
 }
 
 struct DigitId {
@@ -1000,6 +1337,28 @@ PBH_INL void fix_ell(SP st, int q) {
   }
 }
 
+// fix_ell by the team: one lane per level (the loop over the levels is a chain
+// of LDS reads, 0.4 us a Resolve).  Every thread calls it; the first wavefront
+// does the work, after its own thread 0 may have changed the state.
+template <class T, class SP>
+PBH_INL void fix_ell_team(const T& t, SP st, int q) {
+  if constexpr (T::kW == 1) {
+    fix_ell(st, q);
+  } else if (t.wave() == 0) {
+    t.wsync();
+    const int l = t.lane();
+    const u32 has = l < q ? (st->L[l].nB | st->L[l].nS) : 0u;
+    const u64 m = t.ballot(has != 0);
+    int e = m ? 63 - __builtin_clzll(m) : -1;
+    if (st->deep_floor > e) e = st->deep_floor;
+    if (l == 0) st->ell = e;
+    if (l >= e && l < MAXL) {
+      st->L[l].pk = KINF;
+      st->L[l].pv = VINF;
+    }
+  }
+}
+
 // Algorithm 1, Resolve(i): empty S_i and fill B_i, with level i's arrays of
 // type AI and level i+1's of type AN.
 //   EMPTY: B_i <- DeleteDuplicates(Merge(S_i, B_i)); if more than 2d*4^i
@@ -1014,125 +1373,348 @@ PBH_INL void fix_ell(SP st, int q) {
 // FILL of level i-1); the new p_i in FILL never exceeds p_{i+1}, so nothing
 // deeper than level i+1 can be smaller than an element moved up; the two
 // splits at the end of FILL are one three-way split.
+//
+// Written as one loop over the four merges (EMPTY, the push down, FILL, the
+// move up) around one merge, one Select and one split: the round loop runs
+// through its code once per round, and every instance of these primitives
+// that it passes has to come through the 64 KiB instruction cache (four merges
+// and two of each other inlined: 286 KB for the smallest kernel, and a round
+// was bound by instruction fetches).
 template <class T, class P, class AI, class AN>
 PBH_INL void resolve_t(T t, Geom g, typename P::SP st, const u64* cur, int i) {
-  Lvl a = lvl_load(st, i);
+  constexpr bool kSame = same_arr<AI, AN>::v;
+  enum { EMPTY, PUSH, FILL, UP, END };
+  Lvl a = lvl_uni(t, st, i);
   const bool nx = i + 1 < g.q;
-  Lvl b = nx ? lvl_load(st, i + 1) : Lvl{0, 0, 0, 0, KINF, VINF, 0};
-  int ell = st->ell;
+  Lvl b = nx ? lvl_uni(t, st, i + 1) : Lvl{0, 0, 0, 0, KINF, VINF, 0};
+  int ell = (int)t.uni((u32)st->ell);
   KV pi{a.pk, a.pv}, pn{b.pk, b.pv};
   const u32 cB = (u32)nomB(g.d, i);
   u64 touched = 0;
   int err = 0;
-  if (a.nS > 0 || a.nB > cB) {
-    AI S = as_arr<AI>(lbuf(g, i, 3 + a.ssel)), B = as_arr<AI>(lbuf(g, i, a.bsel)),
-       M = as_arr<AI>(lbuf(g, i, a.bsel ^ 1));
-    if ((u64)a.nS + a.nB > capB(g.d, i)) {
-      err = E_INTERNAL;
-      goto done;
+  u32 n1 = 0;          // elements pushed down / moved up, in X
+  // arrays are named by level (i or i + 1) and buffer, and resolved where they
+  // are used (pointers would be seven pairs of scalars to keep)
+  constexpr u32 NXT = 8u, X = 2u;
+  auto at = [&](u32 c) { return lbuf(g, i + (int)(c >> 3), (int)(c & 7u)); };
+  // FILL is due once EMPTY (if due) is through
+  auto fill_due = [&] { return a.nB < cB && i < ell && nx ? (int)FILL : (int)END; };
+  int step = a.nS > 0 || a.nB > cB ? (int)EMPTY : fill_due();
+  while (step != END) {
+    // the merge of this step: B into A's order, output M
+    u32 A, B, M;
+    u32 na, nb, m;
+    int prefer = PREFER_LIVE;
+    bool merge = true;  // false: one side is empty, M is the other
+    CountLe le{pi, 0};
+    if (step == EMPTY) {
+      A = 3 + a.ssel;
+      B = a.bsel;
+      M = a.bsel ^ 1;
+      na = a.nS;
+      nb = a.nB;
+      // S_0 holds the latest updates, so at level 0 its copy of an id is the live one.
+      if (i == 0) prefer = PREFER_A;
+      if ((u64)na + nb > capB(g.d, i)) err = E_INTERNAL;
+    } else if (step == PUSH) {
+      A = NXT + (3 + b.ssel);
+      B = X;
+      M = NXT + (3 + (b.ssel ^ 1));
+      na = b.nS;
+      nb = n1;
+      // (with S_{i+1} empty the split wrote to M, where both levels are of one kind)
+      merge = !kSame || na > 0;
+    } else if (step == FILL) {
+      A = NXT + (b.bsel);
+      B = NXT + (3 + b.ssel);
+      M = NXT + (b.bsel ^ 1);
+      na = b.nB;
+      nb = b.nS;
+      merge = nb > 0;
+      if (!merge) M = A;
+      if ((u64)na + nb > capB(g.d, i + 1)) err = E_INTERNAL;
+    } else {
+      A = a.bsel;
+      B = X;
+      M = a.bsel ^ 1;
+      na = a.nB;
+      nb = n1;
+      if (i == 0 && cur != nullptr) prefer = PREFER_B;
     }
-    // S_0 holds the latest updates, so at level 0 its copy of an id is the live one.
-    u32 m = merge_dedup(t, S, a.nS, B, a.nB, M, cur, false, i == 0 ? PREFER_A : PREFER_LIVE);
-    touched += 2ull * (a.nS + a.nB) + m;
-    a.bsel ^= 1;
-    a.nS = 0;
-    a.ssel = 0;
-    u32 num = count_le(t, M, m, pi);
-    if (num > cB) {
-      pi = select_kth(t, M, m, cB);
-      num = cB;
-      touched += m;
+    if (err) break;
+    m = na + nb;
+    if (merge) {
+      if constexpr (kSame)
+        m = merge_dedup(t, as_arr<AI>(at(A)), na, as_arr<AI>(at(B)), nb, as_arr<AI>(at(M)), cur, false, prefer, &le);
+      else if (step == PUSH)
+        m = merge_dedup(t, as_arr<AN>(at(A)), na, as_arr<AI>(at(B)), nb, as_arr<AN>(at(M)), cur, false, prefer, &le);
+      else if (step == FILL)
+        m = merge_dedup(t, as_arr<AN>(at(A)), na, as_arr<AN>(at(B)), nb, as_arr<AN>(at(M)), cur, false, prefer, &le);
+      else
+        m = merge_dedup(t, as_arr<AI>(at(A)), na, as_arr<AI>(at(B)), nb, as_arr<AI>(at(M)), cur, false, prefer, &le);
     }
-    if (num < m) {
+    touched += 2ull * ((u64)na + nb) + m;
+    if (step == PUSH) {
+      b.ssel ^= 1;
+      b.nS = m;
+      if (ell < i + 1) ell = i + 1;
+      step = fill_due();
+      continue;
+    }
+    if (step == UP) {
+      a.bsel ^= 1;
+      a.nB = m;
+      step = END;
+      continue;
+    }
+    // EMPTY and FILL: choose the pivot, split M at it
+    u32 r = 0;  // rank of the pivot in M (0: no Select)
+    KV p1 = pi, p2 = kv_inf();
+    u32 O0, O1, O2;
+    const u64* live = nullptr;
+    if (step == EMPTY) {
+      a.bsel ^= 1;
+      a.nS = 0;
+      a.ssel = 0;
+      u32 num = le.n;
+      if (num > cB) r = num = cB;
+      if (num == m) {
+        a.nB = m;
+        step = fill_due();
+        continue;
+      }
       if (!nx) {
         err = E_CAPACITY;
-        goto done;
+        break;
       }
-      AI Lo = as_arr<AI>(lbuf(g, i, a.bsel ^ 1)), Hi = as_arr<AI>(lbuf(g, i, 2));
-      u32 n0, n1, n2;
-      partition3(t, M, m, pi, kv_inf(), Lo, Hi, Hi, &n0, &n1, &n2);
-      touched += 3ull * m;
+      if ((u64)b.nS + (m - num) > capS(g.d, i + 1)) {
+        err = E_INTERNAL;
+        break;
+      }
+      O0 = a.bsel ^ 1;
+      O1 = kSame && b.nS == 0 ? NXT + 3 + (b.ssel ^ 1) : X;
+      O2 = O1;
+    } else {
+      if (merge) b.bsel ^= 1;
+      b.nS = 0;
+      b.ssel = 0;
+      b.nB = m;
+      if (m == 0) {
+        step = END;
+        continue;
+      }
+      const u32 want = cB - a.nB;
+      r = want < m ? want : 0u;
+      p1 = kv_inf();
+      p2 = pn;
+      O0 = X;
+      O1 = NXT + (b.bsel ^ 1);
+      O2 = NXT + (3);
+      // Elements moving up into B_0 are checked for liveness here, all at once.
+      if (i == 0) live = cur;
+    }
+    if (r) {
+      touched += m;
+      if constexpr (kSame)
+        p1 = select_kth(t, as_arr<AI>(at(M)), m, r);
+      else if (step == EMPTY)
+        p1 = select_kth(t, as_arr<AI>(at(M)), m, r);
+      else
+        p1 = select_kth(t, as_arr<AN>(at(M)), m, r);
+    }
+    if (step == FILL && kv_less(pn, p1)) p1 = pn;
+    pi = p1;
+    touched += 3ull * m;
+    u32 n0, n2;
+    if constexpr (kSame)
+      partition3(t, as_arr<AI>(at(M)), m, p1, p2, as_arr<AI>(at(O0)), as_arr<AI>(at(O1)), as_arr<AI>(at(O2)), &n0, &n1, &n2, live);
+    else if (step == EMPTY)
+      partition3(t, as_arr<AI>(at(M)), m, p1, p2, as_arr<AI>(at(O0)), as_arr<AI>(at(O1)), as_arr<AI>(at(O2)), &n0, &n1, &n2);
+    else
+      partition3(t, as_arr<AN>(at(M)), m, p1, p2, as_arr<AI>(at(O0)), as_arr<AN>(at(O1)), as_arr<AN>(at(O2)), &n0, &n1, &n2, live);
+    if (step == EMPTY) {
       a.bsel ^= 1;
       a.nB = n0;
-      if ((u64)b.nS + n1 > capS(g.d, i + 1)) {
-        err = E_INTERNAL;
-        goto done;
-      }
-      AN Sn = as_arr<AN>(lbuf(g, i + 1, 3 + b.ssel)), Sn2 = as_arr<AN>(lbuf(g, i + 1, 3 + (b.ssel ^ 1)));
-      u32 ms = merge_dedup(t, Sn, b.nS, Hi, n1, Sn2, cur, false);
-      touched += 2ull * (b.nS + n1) + ms;
-      b.ssel ^= 1;
-      b.nS = ms;
-      if (ell < i + 1) ell = i + 1;
+      step = PUSH;
     } else {
-      a.nB = m;
-    }
-  }
-  if (a.nB < cB && i < ell && nx) {
-    AN Bn = as_arr<AN>(lbuf(g, i + 1, b.bsel)), Sn = as_arr<AN>(lbuf(g, i + 1, 3 + b.ssel)),
-       M2 = as_arr<AN>(lbuf(g, i + 1, b.bsel ^ 1));
-    if ((u64)b.nB + b.nS > capB(g.d, i + 1)) {
-      err = E_INTERNAL;
-      goto done;
-    }
-    u32 m2 = merge_dedup(t, Bn, b.nB, Sn, b.nS, M2, cur, false);
-    touched += 2ull * (b.nB + b.nS) + m2;
-    b.nS = 0;
-    b.ssel = 0;
-    b.bsel ^= 1;
-    b.nB = m2;
-    if (m2 > 0) {
-      u32 r = cB - a.nB;
-      KV pnew = (r >= m2) ? kv_inf() : select_kth(t, M2, m2, r);
-      if (r < m2) touched += m2;
-      if (kv_less(pn, pnew)) pnew = pn;
-      AI Up = as_arr<AI>(lbuf(g, i, 2));
-      AN Bk = as_arr<AN>(lbuf(g, i + 1, b.bsel ^ 1)), Sk = as_arr<AN>(lbuf(g, i + 1, 3));
-      u32 nu, nb1, ns1;
-      // Elements moving up into B_0 are checked for liveness here, all at once.
-      partition3(t, M2, m2, pnew, pn, Up, Bk, Sk, &nu, &nb1, &ns1, i == 0 ? cur : nullptr);
-      touched += 3ull * m2;
       b.bsel ^= 1;
-      b.nB = nb1;
-      b.nS = ns1;
-      b.ssel = 0;
-      AI Bi = as_arr<AI>(lbuf(g, i, a.bsel)), Bi2 = as_arr<AI>(lbuf(g, i, a.bsel ^ 1));
-      u32 mb = merge_dedup(t, Bi, a.nB, Up, nu, Bi2, cur, false, i == 0 && cur != nullptr ? PREFER_B : PREFER_LIVE);
-      touched += 2ull * (a.nB + nu) + mb;
-      a.bsel ^= 1;
-      a.nB = mb;
-      pi = pnew;
+      b.nB = n1;
+      b.nS = n2;
+      n1 = n0;
+      step = UP;
     }
   }
-  a.cnt++;
-  a.pk = pi.k;
-  a.pv = pi.v;
-done:
   t.sync();
   if (t.tid() == 0) {
     if (err) {
       st->err = err;
     } else {
-      lvl_store(st, i, a);
-      if (nx) lvl_store(st, i + 1, b);
-      st->elems += touched;
-      fix_ell(st, g.q);
+      a.cnt++;
+      a.pk = pi.k;
+      a.pv = pi.v;
+      if (touched) {
+        lvl_store(st, i, a);
+        if (nx) lvl_store(st, i + 1, b);
+        st->elems += touched;
+      } else {
+        st->L[i].cnt = a.cnt;
+      }
     }
   }
+  if (!err) fix_ell_team(t, st, g.q);
   t.sync();
+}
+
+// Resolve(0) by one wavefront with levels 0 and 1 in LDS, while the arrays
+// are small (small_rows): each of EMPTY and FILL is one pass in registers --
+// merge, Select and split without the merged array in between -- and so are
+// the push down and the move up.  The result is resolve_t's.  A round of the
+// plain rule is bound by the instructions of its one wavefront (5 to 8 cycles
+// each, whatever they do), and most of them were the general form's: places of
+// buffers for any level and placement, loops over elements per thread, the
+// merged array's way through LDS.  Returns false if resolve_t has to do (the
+// rest of) the work; the state is then as if that part were still due.
+template <class T, class P>
+PBH_INL bool resolve0_wave(const T& t, const Geom& g, typename P::SP st, const u64* cur) {
+  using AI = typename P::L;
+  Lvl a = lvl_uni(t, st, 0), b = lvl_uni(t, st, 1);
+  const u32 d = g.d, cB = 2u * d;
+  int ell = (int)t.uni((u32)st->ell);
+  auto arr = [&](u32 o) {  // by element offset: level 0 starts at 0, level 1 at 16 d
+    AI x = as_arr<AI>(Arr{g.lk, g.lv});
+    x.k += o;
+    x.v += o;
+    return x;
+  };
+  auto l1B = [&](u32 s) { return 16u * d + s * 16u * d; };
+  auto l1S = [&](u32 s) { return 64u * d + s * 8u * d; };
+  const u32 X = 8u * d;  // the level's temporary buffer
+  u32 touched = 0, n0, n1, n2;
+  KV pi{a.pk, a.pv};
+  if (a.nS > 0 || a.nB > cB) {
+    const u32 rows = small_rows<T>(a.nS, a.nB);
+    if (rows == 0 || a.nS + a.nB > 4u * d) return false;
+    u32 m = 0;
+    KV p1 = pi;
+    bool fit = true;
+    auto empty = [&](auto& s) {
+      const bool sa = a.nS <= a.nB;
+      const u32 oS = 12u * d, oB = a.bsel * 4u * d;
+      s.run(t, arr(sa ? oS : oB), sa ? a.nS : a.nB, arr(sa ? oB : oS), sa ? a.nB : a.nS, sa, cur, PREFER_A);
+      m = s.m;
+      u32 num = pi.k == KINF ? m : s.count_le(t, pi);
+      const bool sel = num > cB;
+      if (sel) num = cB;
+      if (b.nS + (m - num) > 8u * d) {
+        fit = false;
+        return;
+      }
+      if (sel) {
+        p1 = s.select(t, cB);
+        touched += m;
+      }
+      s.split(t, p1, kv_inf(), arr((a.bsel ^ 1u) * 4u * d), arr(b.nS ? X : l1S(b.ssel ^ 1u)),
+              arr(b.nS ? X : l1S(b.ssel ^ 1u)), nullptr, &n0, &n1, &n2);
+    };
+    if (rows == 1) {
+      SmallMerge<1> s;
+      empty(s);
+    } else {
+      SmallMerge<4> s;
+      empty(s);
+    }
+    if (!fit) return false;
+    touched += 2u * (a.nS + a.nB) + m;
+    a.bsel ^= 1u;
+    a.nB = n0;
+    a.nS = 0;
+    if (n1) {
+      touched += 3u * m;
+      pi = p1;
+      t.sync();
+      const u32 ns = b.nS;
+      b.nS = ns ? merge_dedup(t, arr(l1S(b.ssel)), ns, arr(X), n1, arr(l1S(b.ssel ^ 1u)), cur, false) : n1;
+      b.ssel ^= 1u;
+      touched += 2u * (ns + n1) + b.nS;
+      if (ell < 1) ell = 1;
+    }
+    t.sync();
+  }
+  bool whole = true;
+  if (a.nB < cB && 0 < ell) {
+    const u32 rows = small_rows<T>(b.nB, b.nS);
+    whole = rows != 0;
+    if (whole) {
+      u32 m = 0;
+      KV p1 = kv_inf();
+      const KV pn{b.pk, b.pv};
+      auto fill = [&](auto& s) {
+        const bool sb = b.nB <= b.nS;
+        const u32 oB = l1B(b.bsel), oS = l1S(b.ssel);
+        s.run(t, arr(sb ? oB : oS), sb ? b.nB : b.nS, arr(sb ? oS : oB), sb ? b.nS : b.nB, sb, cur, PREFER_LIVE);
+        m = s.m;
+        const u32 want = cB - a.nB;
+        if (want < m) {
+          p1 = s.select(t, want);
+          touched += m;
+        }
+        if (kv_less(pn, p1)) p1 = pn;
+        s.split(t, p1, pn, arr(X), arr(l1B(b.bsel ^ 1u)), arr(l1S(0)), cur, &n0, &n1, &n2);
+      };
+      if (rows == 1) {
+        SmallMerge<1> s;
+        fill(s);
+      } else {
+        SmallMerge<4> s;
+        fill(s);
+      }
+      t.sync();
+      touched += 2u * (b.nB + b.nS) + m;
+      b.bsel ^= 1u;
+      b.nB = n1;
+      b.nS = n2;
+      b.ssel = 0;
+      if (m) {
+        const u32 nb = a.nB;
+        a.nB = merge_dedup(t, arr(a.bsel * 4u * d), nb, arr(X), n0, arr((a.bsel ^ 1u) * 4u * d), cur, false,
+                           cur != nullptr ? PREFER_B : PREFER_LIVE);
+        a.bsel ^= 1u;
+        touched += 3u * m + 2u * (nb + n0) + a.nB;
+        pi = p1;
+      }
+    }
+  }
+  if (t.tid() == 0) {
+    a.cnt += whole ? 1u : 0u;
+    a.pk = pi.k;
+    a.pv = pi.v;
+    lvl_store(st, 0, a);
+    if (touched) lvl_store(st, 1, b);
+    st->elems += touched;
+    if (!whole) st->ell = ell;
+  }
+  if (whole) fix_ell_team(t, st, g.q);
+  t.sync();
+  return whole;
 }
 
 template <class T, class P>
 PBH_INL void resolve(const T& t, const Geom& g, typename P::SP st, const u64* cur, int i) {
   P::on_resolve(g, st, i, false);
-  if (t.tid() == 0 && st->prof_on) st->prof_res = pbh_clock();
-  if (i + 1 < g.qlds)
+  if (t.prof && t.tid() == 0) st->prof_res = pbh_clock();
+  bool done = false;
+  if constexpr (T::kNW == 1) {
+    if (i == 0 && g.qlds > 1) done = resolve0_wave<T, P>(t, g, st, cur);
+  }
+  if (done) {
+    // nothing left
+  } else if (i + 1 < g.qlds)
     resolve_t<T, P, typename P::L, typename P::L>(t, g, st, cur, i);
   else if (i < g.qlds)
     resolve_t<T, P, typename P::L, typename P::G>(t, g, st, cur, i);
   else
     resolve_t<T, P, typename P::G, typename P::G>(t, g, st, cur, i);
-  if (t.tid() == 0 && st->prof_on) st->prof[i] += pbh_clock() - st->prof_res;
+  if (t.prof && t.tid() == 0) st->prof[i] += pbh_clock() - st->prof_res;
   P::on_resolve(g, st, i, true);
 }
 
@@ -1190,9 +1772,25 @@ PBH_INL void drive_with(const T& t, const Geom& g, SP st, int sched, int what, R
   int ek = -1;               // refill position
   u64 cascades = 0, climit = 0;
   for (;;) {
-    if (st->err) break;
-    int lvl;
-    if (chain >= 0) {
+    // the words the common path looks at, read together
+    const u32 err = (u32)st->err, ell0 = (u32)st->ell, nB0 = st->L[0].nB, nS0 = st->L[0].nS, cnt0 = st->L[0].cnt,
+              nB1 = st->L[1].nB, nS1 = st->L[1].nS;
+    if (t.uni(err)) break;
+    int lvl = -1;
+    if (stage == 0) {
+      const u64 push = (u64)t.uni(nS0) + t.uni(nB0), bS = t.uni(nS1), bB = t.uni(nB1);
+      if (g.q < 2 || (bS + push <= capS(g.d, 1) && bB + bS + push <= capB(g.d, 1)) || lim <= 1) {
+        stage = 1;  // Resolve(0), with room below it
+        tgt = lvl = 0;
+      }
+    } else if (stage == 1 && chain < 0 && si == 0 && sched == 0 &&
+               ((int)t.uni(ell0) < 1 || (t.uni(cnt0) & 3u) != 0)) {
+      stage = 2;  // no Resolve(1) due
+      if (!(what & DRIVE_ENSURE) || t.uni(nB0) != 0 || (int)t.uni(ell0) < 1) break;
+    }
+    if (lvl == 0) {
+      // decided above
+    } else if (chain >= 0) {
       lvl = chain;
       chain = chain > tgt ? chain - 1 : -1;
     } else {
@@ -1353,9 +1951,9 @@ PBH_INL void deep_step(const T& t, const Geom& g, typename P::SP st, const u64* 
   const u64 c1 = nx ? lvl_count(st, i + 1) : 0ull;
   const u64 e0 = st->elems;
   // worker levels are never in LDS: only the global placement is needed
-  if (t.tid() == 0 && st->prof_on) st->prof_res = pbh_clock();
+  if (t.prof && t.tid() == 0) st->prof_res = pbh_clock();
   resolve_t<T, P, typename P::G, typename P::G>(t, g, st, cur, i);
-  if (t.tid() == 0 && st->prof_on) st->prof[i] += pbh_clock() - st->prof_res;
+  if (t.prof && t.tid() == 0) st->prof[i] += pbh_clock() - st->prof_res;
   if (st->err) {
     sy.fail(t, st->err);
     return;
@@ -1365,7 +1963,7 @@ PBH_INL void deep_step(const T& t, const Geom& g, typename P::SP st, const u64* 
   sy.put(t, st, i);
   if (nx) sy.put(t, st, i + 1);
   sy.account(t, i, (long long)n01 - (long long)c01, (long long)n1 - (long long)c1, st->elems - e0,
-             st->prof_on ? st->prof[i] : 0ull);
+             t.prof ? st->prof[i] : 0ull);
   if (nx && (st->L[i].cnt & 3u) == 0 && i + 1 <= st->ell) sy.post(t, i + 1);
   sy.done(t, i);
 }
@@ -1547,10 +2145,10 @@ PBH_HD inline int bits_for(u32 n) {
 // sorted by id.
 template <class T, class A>
 PBH_INL u32 intake(const T& t, A S, u32 n, A tmp, A tmp2, const u64* dist, int idbits) {
-  u32 bad = 0;
-  for (u32 x = (u32)t.tid() + 1; x < n; x += (u32)T::kNT) bad += S.v[x - 1] >= S.v[x];
-  bad = t.sum(bad);
-  if (bad == 0) return n;
+  if (n < 2) return n;
+  bool bad = false;
+  for (u32 x = (u32)t.tid() + 1; x < n; x += (u32)T::kNT) bad = bad || S.v[x - 1] >= S.v[x];
+  if (!t.any(bad)) return n;
   u32 out = 0;
   for (u32 base = 0; base < n; base += (u32)T::kNT) {
     u32 x = base + (u32)t.tid();
@@ -1587,46 +2185,64 @@ template <class T, class P, class A0, bool LONG = false>
 PBH_INL bool round_body(const T& t, const Geom& g, typename P::SP st, const u64* off, const u32* tg,
                         const u32* wt, u64* dist, int idbits, u64* relax, u64* upd, u32* order, u64 order_cap,
                         u64 nth) {
-  const Lvl a0 = lvl_load(st, 0);
+  const Lvl a0 = lvl_uni(t, st, 0);
   if (a0.nB == 0) return false;
   A0 B = as_arr<A0>(lbuf(g, 0, a0.bsel));
-  u64 mk = KINF;
-  u32 mv = VINF;
-  if constexpr (!LONG || in_lds<A0>::v) {
-    for (u32 x = (u32)t.tid(); x < a0.nB; x += (u32)T::kNT) {
-      u64 k = B.k[x];
-      u32 v = B.v[x];
-      if (k < mk || (k == mk && v < mv)) {
-        mk = k;
-        mv = v;
-      }
-    }
-  } else {
-    // B_0 in HBM (large d): eight loads per thread in flight per pass
-    constexpr int U = 8;
-    for (u32 base = 0; base < a0.nB; base += (u32)T::kNT * U) {
-      u64 k[U];
-      u32 v[U];
+  // The minimum, U elements per thread in flight; then it is taken out in
+  // place: B_0 is sorted by id, so the elements after it, and only those,
+  // move down by one (every wavefront has read its elements by then: the
+  // team's minimum is a barrier).  B_0 of more than U elements per thread is
+  // read again for the move, tile by tile.
+  constexpr int U = in_lds<A0>::v ? 4 : 8;
+  u64 mk = KINF, k[U];
+  u32 mv = VINF, v[U];
+  for (u32 base = 0; base < a0.nB; base += (u32)T::kNT * U) {
 #pragma unroll
-      for (int r = 0; r < U; ++r) {
-        const u32 x = base + (u32)r * (u32)T::kNT + (u32)t.tid();
-        k[r] = x < a0.nB ? B.k[x] : KINF;
-        v[r] = x < a0.nB ? B.v[x] : VINF;
-      }
-#pragma unroll
-      for (int r = 0; r < U; ++r)
-        if (k[r] < mk || (k[r] == mk && v[r] < mv)) {
-          mk = k[r];
-          mv = v[r];
-        }
+    for (int r = 0; r < U; ++r) {
+      const u32 x = base + (u32)r * (u32)T::kNT + (u32)t.tid();
+      k[r] = x < a0.nB ? B.k[x] : KINF;
+      v[r] = x < a0.nB ? B.v[x] : VINF;
     }
+#pragma unroll
+    for (int r = 0; r < U; ++r)
+      if (k[r] < mk || (k[r] == mk && v[r] < mv)) {
+        mk = k[r];
+        mv = v[r];
+      }
   }
   t.minkv(mk, mv);
   const u64 e0 = off[mv], e1 = off[mv + 1];
   if (order && nth < order_cap && t.tid() == 0) order[nth] = mv;  // the settle order, when asked for
-  u32 n0, n1, n2;
+  if (a0.nB <= (u32)T::kNT * U) {
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      const u32 x = (u32)r * (u32)T::kNT + (u32)t.tid();
+      if (x < a0.nB && v[r] > mv) {
+        B.k[x - 1] = k[r];
+        B.v[x - 1] = v[r];
+      }
+    }
+  } else {
+    for (u32 base = 0; base < a0.nB; base += (u32)T::kNT * U) {
+#pragma unroll
+      for (int r = 0; r < U; ++r) {
+        const u32 x = base + (u32)r * (u32)T::kNT + (u32)t.tid();
+        k[r] = x < a0.nB ? B.k[x] : KINF;
+        v[r] = x < a0.nB ? B.v[x] : 0u;
+      }
+      t.sync();
+#pragma unroll
+      for (int r = 0; r < U; ++r) {
+        const u32 x = base + (u32)r * (u32)T::kNT + (u32)t.tid();
+        if (x < a0.nB && v[r] > mv) {
+          B.k[x - 1] = k[r];
+          B.v[x - 1] = v[r];
+        }
+      }
+    }
+  }
+  const u32 n1 = a0.nB - 1;
   A0 T0 = as_arr<A0>(lbuf(g, 0, 2));
-  partition3(t, B, a0.nB, KV{mk, mv}, kv_inf(), T0, as_arr<A0>(lbuf(g, 0, a0.bsel ^ 1)), T0, &n0, &n1, &n2);
   prof_lap(t, st, PROF_EXTRACT);
   A0 S = as_arr<A0>(lbuf(g, 0, 3));
   u32 nu = 0;
@@ -1680,7 +2296,6 @@ PBH_INL bool round_body(const T& t, const Geom& g, typename P::SP st, const u64*
   prof_lap(t, st, PROF_RELAX);
   nu = intake(t, S, nu, T0, as_arr<A0>(lbuf(g, 0, 4)), dist, idbits);
   if (t.tid() == 0) {
-    st->L[0].bsel = a0.bsel ^ 1;
     st->L[0].nB = n1;
     st->L[0].nS = nu;
     st->L[0].ssel = 0;
@@ -1772,7 +2387,8 @@ PBH_INL u64 b0_min_key(const T& t, const Geom& g, typename P::SP st) {
 
 struct RoundMemo {  // team-uniform facts about the previous round
   float avgdeg;
-  u32 k;  // the last k the learned rule proposed
+  u32 k;          // the last k the learned rule proposed
+  bool resident;  // the round's update list is in S_0's array already
 };
 
 PBH_INL float flog2p1(float x) { return __builtin_log2f(1.0f + x); }
@@ -1791,7 +2407,8 @@ PBH_INL void round_features(const T& t, const Geom& g, SP st, A0 B, u32 nB, cons
   }
   t.minmax64(lo, hi);
   u64 tot = st->deep_n;
-  for (int i = 0; i < g.q; ++i) tot += (u64)st->L[i].nB + st->L[i].nS;
+#pragma unroll
+  for (int i = 0; i < MAXL; ++i) tot += i < g.q ? (u64)st->L[i].nB + st->L[i].nS : 0ull;
   const float spread = (float)(hi - lo);
   f[0] = flog2p1((float)tot);
   f[1] = flog2p1((float)nB);
@@ -1814,48 +2431,88 @@ PBH_INL float bf16r(float x) {
 
 PBH_INL float gelu(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
+// A thread's share of the model's parameters, read before the features are
+// known so that the reads (global memory) run beside that work: the first
+// layer's column of this thread's hidden unit, and for teams of >= 256 threads
+// its quarter of the second layer's column.
+template <class T>
+struct MlpRegs {
+  static constexpr int kQ = T::kNT >= 256 ? MLP_H / 4 : 1;
+  float w1[NFEAT], w2[kQ], b1, b2, w3, mu[NFEAT], sd[NFEAT];
+  PBH_INL void load(const T& t, const float* m) {
+    const int j = t.tid() & (MLP_H - 1);
+    const float* W2 = m + NFEAT * MLP_H + MLP_H;
+    const float* B2 = W2 + MLP_H * MLP_H;
+    const float* mm = B2 + 2 * MLP_H + 1;
+#pragma unroll
+    for (int i = 0; i < NFEAT; ++i) {
+      w1[i] = m[i * MLP_H + j];
+      mu[i] = mm[i];
+      sd[i] = mm[NFEAT + i];
+    }
+    b1 = m[NFEAT * MLP_H + j];
+    b2 = B2[j];
+    w3 = B2[MLP_H + j];
+    if constexpr (T::kNT >= 256) {
+      const int qtr = (t.tid() >> 6) & 3;
+#pragma unroll
+      for (int i = 0; i < kQ; ++i) w2[i] = W2[(qtr * kQ + i) * MLP_H + j];
+    }
+  }
+};
+
 // MLP 8 -> 64 -> 64 -> 1 with GELU (exact, x * Phi(x)); every parameter is
 // used rounded to bfloat16, as in training; thread j computes hidden unit j of
 // each layer (weights stored input-major, so the loads of
 // one input row are contiguous), the output is reduced through LDS.  BF16
 // weights, FP32 accumulation.  Returns y (k = 2^(s * y)).
 template <class T>
-PBH_INL float mlp_forward(const T& t, const float* m, const float* f) {
+PBH_INL float mlp_forward(const T& t, const float* m, const float* f, const MlpRegs<T>& r) {
   const float* W1 = m;
   const float* b1 = W1 + NFEAT * MLP_H;
   const float* W2 = b1 + MLP_H;
   const float* b2 = W2 + MLP_H * MLP_H;
   const float* w3 = b2 + MLP_H;
   const float* b3 = w3 + MLP_H;
-  const float* mu = b3 + 1;
-  const float* sd = mu + NFEAT;
+  const float* sd = b3 + 1 + NFEAT;
   float x[NFEAT];
 #pragma unroll
-  for (int i = 0; i < NFEAT; ++i) x[i] = (f[i] - mu[i]) / sd[i];
-  for (int j = t.tid(); j < MLP_H; j += T::kNT) {
-    float a = bf16r(b1[j]);
+  for (int i = 0; i < NFEAT; ++i) x[i] = (f[i] - r.mu[i]) / r.sd[i];
+  if constexpr (T::kNT >= MLP_H) {
+    if (t.tid() < MLP_H) {
+      float a = bf16r(r.b1);
 #pragma unroll
-    for (int i = 0; i < NFEAT; ++i) a += bf16r(W1[i * MLP_H + j]) * x[i];
-    t.sh->mlp_h[j] = gelu(a);
+      for (int i = 0; i < NFEAT; ++i) a += bf16r(r.w1[i]) * x[i];
+      t.sh->mlp_h[t.tid()] = gelu(a);
+    }
+  } else {
+    for (int j = t.tid(); j < MLP_H; j += T::kNT) {
+      float a = bf16r(b1[j]);
+#pragma unroll
+      for (int i = 0; i < NFEAT; ++i) a += bf16r(W1[i * MLP_H + j]) * x[i];
+      t.sh->mlp_h[j] = gelu(a);
+    }
   }
   t.sync();
   if constexpr (T::kNT >= 256) {
     // four threads per hidden unit, each summing a quarter of the inputs
-    const int j = t.tid() & (MLP_H - 1), qtr = t.tid() >> 6;
     if (t.tid() < 4 * MLP_H) {
+      const int qtr = t.tid() >> 6;
       float a = 0.0f;
-      for (int i = qtr * (MLP_H / 4); i < (qtr + 1) * (MLP_H / 4); ++i) a += bf16r(W2[i * MLP_H + j]) * t.sh->mlp_h[i];
+#pragma unroll
+      for (int i = 0; i < MLP_H / 4; ++i) a += bf16r(r.w2[i]) * t.sh->mlp_h[qtr * (MLP_H / 4) + i];
       t.sh->mlp_p[t.tid()] = a;
     }
     t.sync();
     if (t.tid() < MLP_H) {
-      float a = bf16r(b2[j]);
-      for (int q = 0; q < 4; ++q) a += t.sh->mlp_p[q * MLP_H + j];
-      t.sh->mlp_z[j] = bf16r(w3[j]) * gelu(a);
+      float a = bf16r(r.b2);
+      for (int q = 0; q < 4; ++q) a += t.sh->mlp_p[q * MLP_H + t.tid()];
+      t.sh->mlp_z[t.tid()] = bf16r(r.w3) * gelu(a);
     }
   } else {
     for (int j = t.tid(); j < MLP_H; j += T::kNT) {
       float a = bf16r(b2[j]);
+#pragma unroll 16
       for (int i = 0; i < MLP_H; ++i) a += bf16r(W2[i * MLP_H + j]) * t.sh->mlp_h[i];
       t.sh->mlp_z[j] = bf16r(w3[j]) * gelu(a);
     }
@@ -1890,8 +2547,10 @@ PBH_INL u32 propose_k(const T& t, const Geom& g, SP st, const SpecCfg& sc, A0 B,
     k = memo.k;  // between model runs the last proposal stands
   } else if (sc.rule == 2) {
     float f[NFEAT];
+    MlpRegs<T> r;
+    r.load(t, sc.model);
     round_features(t, g, st, B, nB, memo, f);
-    float y = mlp_forward(t, sc.model, f) * sc.kscale;
+    float y = mlp_forward(t, sc.model, f, r) * sc.kscale;
     // fall back to the plain rule on anything that is not a finite number
     if (y == y && y > -64.0f && y < 64.0f) {
       float kk = __builtin_exp2f(y);
@@ -1947,11 +2606,12 @@ PBH_INL void record_trace(const T& t, const Geom& g, SP st, const SpecCfg& sc, A
   t.sync();
 }
 
-// Round update list U (n pairs, global) -> one pair per id, sorted by id: keep
-// the pairs whose key equals dist[id] (the minimum, by atomicMin), sort by id,
-// drop equal neighbours (equal candidates from two sources).
-template <class T, class GA>
-PBH_INL u32 intake_list(const T& t, GA U, u32 n, GA W, const u64* dist, int idbits) {
+// The pairs of U (n of them, global) whose key equals dist[id], to W.  Each
+// pair of a round's list lowered its distance (atomicMin returned a larger
+// one), and later pairs of that id are smaller still, so exactly one pair per
+// id is left: the sorted list needs no further pass for duplicates.
+template <class T, class GA, class AW>
+PBH_INL u32 filter_live(const T& t, GA U, u32 n, AW W, const u64* dist) {
   u32 out = 0;
   constexpr int RE = 4;  // elements per thread per pass, loads issued together
   for (u32 base = 0; base < n; base += (u32)T::kNT * RE) {
@@ -1983,81 +2643,89 @@ PBH_INL u32 intake_list(const T& t, GA U, u32 n, GA W, const u64* dist, int idbi
     out += tot;
   }
   t.sync();
-  bool inU = sort_by_id(t, W, U, out, idbits);
-  GA S = inU ? U : W, D = inU ? W : U;
-  u32 m = 0;
-  for (u32 base = 0; base < out; base += (u32)T::kNT) {
-    u32 x = base + (u32)t.tid();
-    bool keep = x < out && (x == 0 || S.v[x - 1] != S.v[x]);
-    u64 k = x < out ? S.k[x] : 0;
-    u32 v = x < out ? S.v[x] : 0;
-    u32 tot;
-    u32 o = m + t.scan_excl(keep ? 1u : 0u, &tot);
-    if (keep) {
-      D.k[o] = k;
-      D.v[o] = v;
-    }
-    m += tot;
-  }
-  t.sync();
-  if (!inU) copy_arr(t, D, U, m);  // result always in U
-  return m;
+  return out;
 }
 
-// intake_list with the filtered pairs sorted in LDS (two buffers L1, L2 of at
-// least n pairs): the filter reads U and dist, the radix sort by id runs
-// between L1 and L2, and the deduplicated list is written back to U.
-template <class T, class GA, class LA>
-PBH_INL u32 intake_list_lds(const T& t, GA U, u32 n, LA L1, LA L2, const u64* dist, int idbits) {
-  u32 out = 0;
-  constexpr int RE = 4;
-  for (u32 base = 0; base < n; base += (u32)T::kNT * RE) {
-    u64 k[RE], c[RE];
-    u32 v[RE];
+// Round update list U (n pairs, global) -> one pair per id, sorted by id, in U
+// (W: scratch of the same size).
+template <class T, class GA>
+PBH_INL u32 intake_list(const T& t, GA U, u32 n, GA W, const u64* dist, int idbits) {
+  const u32 out = filter_live(t, U, n, W, dist);
+  if (!sort_by_id(t, W, U, out, idbits)) copy_arr(t, W, U, out);
+  return out;
+}
+
+// Sorts n <= RUNS * kW pairs of L1 by id into D (L2: scratch).  Each
+// wavefront sorts runs of one element per lane in registers; an element's
+// place is its place in its run plus, from a search in every other run, the
+// elements there that come before it.  Two barriers in all, where the radix
+// sort takes about six per 8-bit digit and 256 elements (256 pairs of 20-bit
+// ids, 256 threads: about 1 us against 3).  Beyond RUNS runs the searches cost
+// more than the radix passes.
+constexpr u32 RUNS = 8;
+template <class T, class LA, class AD>
+PBH_INL void sort_runs(const T& t, LA L1, LA L2, u32 n, AD D) {
+  constexpr u32 W = (u32)T::kW;
+  constexpr int Q = (int)((RUNS + T::kNW - 1) / T::kNW);  // runs per wavefront
+  u64 k[Q];
+  u32 v[Q], rank[Q];
+  const u32 nr = (n + W - 1) / W;
 #pragma unroll
-    for (int r = 0; r < RE; ++r) {
-      const u32 x = base + (u32)r * (u32)T::kNT + (u32)t.tid();
-      k[r] = x < n ? U.k[x] : 0;
-      v[r] = x < n ? U.v[x] : 0;
-    }
+  for (int q = 0; q < Q; ++q) {
+    const u32 run = (u32)q * T::kNW + (u32)t.wave();
+    if (run >= nr) continue;
+    const u32 x = run * W + (u32)t.lane();
+    const u64 kk = x < n ? L1.k[x] : 0ull;
+    u32 from;
+    v[q] = x < n ? L1.v[x] : VINF;
+    t.wave_sort(v[q], from);
+    k[q] = t.lane_get64(kk, from);
+    L2.v[x] = v[q];
+  }
+  t.sync();
 #pragma unroll
-    for (int r = 0; r < RE; ++r) {
-      const u32 x = base + (u32)r * (u32)T::kNT + (u32)t.tid();
-      c[r] = x < n ? t.load_cur(dist + v[r]) : ~k[r];
-    }
-    u32 cnt = 0;
+  for (int q = 0; q < Q; ++q) {
+    const u32 run = (u32)q * T::kNW + (u32)t.wave();
+    if (run >= nr) continue;
+    rank[q] = 0;
+#pragma unroll 4
+    for (u32 c = 0; c < nr; ++c) {
+      // the elements of run c below v (or equal, in an earlier run); all runs
+      // hold W entries, the last one padded with VINF
+      const u32 lim = c < run ? v[q] : v[q] - 1u;
+      u32 lo = 0;
+      if constexpr (W == 64) {
 #pragma unroll
-    for (int r = 0; r < RE; ++r) cnt += c[r] == k[r] ? 1u : 0u;
-    u32 tot;
-    u32 o = out + t.scan_excl(cnt, &tot);
-#pragma unroll
-    for (int r = 0; r < RE; ++r)
-      if (c[r] == k[r]) {
-        L1.k[o] = k[r];
-        L1.v[o] = v[r];
-        ++o;
+        for (u32 h = 16; h; h /= 4)
+          lo += h * ((L2.v[c * W + lo + h - 1] <= lim ? 1u : 0u) + (L2.v[c * W + lo + 2 * h - 1] <= lim ? 1u : 0u) +
+                     (L2.v[c * W + lo + 3 * h - 1] <= lim ? 1u : 0u));
       }
-    out += tot;
-  }
-  t.sync();
-  const bool in2 = sort_by_id(t, L1, L2, out, idbits);
-  LA S = in2 ? L2 : L1;
-  u32 m = 0;
-  for (u32 base = 0; base < out; base += (u32)T::kNT) {
-    u32 x = base + (u32)t.tid();
-    bool keep = x < out && (x == 0 || S.v[x - 1] != S.v[x]);
-    u64 k = x < out ? S.k[x] : 0;
-    u32 v = x < out ? S.v[x] : 0;
-    u32 tot;
-    u32 o = m + t.scan_excl(keep ? 1u : 0u, &tot);
-    if (keep) {
-      U.k[o] = k;
-      U.v[o] = v;
+      lo += L2.v[c * W + lo] <= lim ? 1u : 0u;
+      lo = c > run && v[q] == 0u ? 0u : lo;
+      rank[q] += c == run ? (u32)t.lane() : lo;
     }
-    m += tot;
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const u32 run = (u32)q * T::kNW + (u32)t.wave();
+    if (run >= nr || v[q] == VINF) continue;
+    D.k[rank[q]] = k[q];
+    D.v[rank[q]] = v[q];
   }
   t.sync();
-  return m;
+}
+
+// The round's final pairs (n of them in L1, one per id; L1 and L2 hold lcap),
+// sorted by id, to D.
+template <class T, class LA, class AD>
+PBH_INL void intake_sorted(const T& t, LA L1, LA L2, u32 lcap, u32 n, AD D, int idbits) {
+  constexpr u32 W = (u32)T::kW;
+  if (n <= RUNS * W && (n + W - 1) / W * W <= lcap)
+    sort_runs(t, L1, L2, n, D);
+  else if (sort_by_id(t, L1, L2, n, idbits))
+    copy_arr(t, L2, D, n);
+  else
+    copy_arr(t, L1, D, n);
 }
 
 // One speculative round: extract the `k` smallest of B_0, relax every out-edge
@@ -2067,7 +2735,7 @@ PBH_INL bool round_spec(const T& t, const Geom& g, typename P::SP st, const u64*
                         const u32* wt, u64* dist, int idbits, u32 k, const SpecCfg& sc, SsspCounters* c,
                         RoundMemo* memo, u32* ulen) {
   using G = typename P::G;
-  const Lvl a0 = lvl_load(st, 0);
+  const Lvl a0 = lvl_uni(t, st, 0);
   if (a0.nB == 0) return false;
   A0 B = as_arr<A0>(lbuf(g, 0, a0.bsel));
   const u32 take = k < a0.nB ? k : a0.nB;
@@ -2098,7 +2766,15 @@ PBH_INL bool round_spec(const T& t, const Geom& g, typename P::SP st, const u64*
   if (t.tid() == 0) t.sh->exd[take] = E;
   t.sync();
   G U{(decltype(G::k))sc.uk, (decltype(G::v))sc.uv};
-  u32 nu = 0;
+  // the LDS after the levels, two lists of lcap pairs
+  using L = typename P::L;
+  unsigned char* lb = reinterpret_cast<unsigned char*>(g.lk) + lvl_off(g.d, g.qlds) * 12ull;
+  L L1, L2;
+  L1.k = (decltype(L1.k))reinterpret_cast<u64*>(lb);
+  L2.k = (decltype(L2.k))reinterpret_cast<u64*>(lb + (u64)sc.lcap * 8u);
+  L1.v = (decltype(L1.v))reinterpret_cast<u32*>(lb + (u64)sc.lcap * 16u);
+  L2.v = (decltype(L2.v))reinterpret_cast<u32*>(lb + (u64)sc.lcap * 20u);
+  u32 nu = 0, nl = 0;  // improved pairs in U / final pairs in L1
   // RE edges per thread per pass: their CSR loads and atomics are all in
   // flight before any result is waited for; one scan places the improvements.
   constexpr int RE = 8;
@@ -2138,6 +2814,38 @@ PBH_INL bool round_spec(const T& t, const Geom& g, typename P::SP st, const u64*
       cnt += imp[r] ? 1u : 0u;
     }
     u32 tot;
+    if (sc.lcap != 0 && E <= (u32)T::kNT * RE) {
+      // The round's only pass: once every edge is relaxed (the barrier), a
+      // pair whose key is the distance is final, so the filter works on the
+      // registers and the list goes straight to LDS; U, its way through global
+      // memory and its reads are left out.
+      t.sync();
+      prof_lap(t, st, PROF_RELAX);
+      u64 c[RE];
+#pragma unroll
+      for (int r = 0; r < RE; ++r) c[r] = imp[r] ? t.load_cur(dist + v[r]) : 0ull;
+      cnt = 0;
+#pragma unroll
+      for (int r = 0; r < RE; ++r) {
+        imp[r] = imp[r] && c[r] == cand[r];
+        cnt += imp[r] ? 1u : 0u;
+      }
+      u32 p = t.scan_excl(cnt, &tot);
+      if (tot <= sc.lcap) {
+#pragma unroll
+        for (int r = 0; r < RE; ++r)
+          if (imp[r]) {
+            L1.k[p] = cand[r];
+            L1.v[p] = v[r];
+            ++p;
+          }
+        nl = tot;
+        break;
+      }
+      cnt = 0;
+#pragma unroll
+      for (int r = 0; r < RE; ++r) cnt += imp[r] ? 1u : 0u;
+    }
     u32 p = nu + t.scan_excl(cnt, &tot);
 #pragma unroll
     for (int r = 0; r < RE; ++r)
@@ -2150,16 +2858,17 @@ PBH_INL bool round_spec(const T& t, const Geom& g, typename P::SP st, const u64*
   }
   t.sync();
   prof_lap(t, st, PROF_RELAX);
-  if (sc.lcap != 0 && nu <= sc.lcap) {
-    // the list fits in the LDS after the levels: sort it there
-    using L = typename P::L;
-    unsigned char* lb = reinterpret_cast<unsigned char*>(g.lk) + lvl_off(g.d, g.qlds) * 12ull;
-    L L1, L2;
-    L1.k = (decltype(L1.k))reinterpret_cast<u64*>(lb);
-    L2.k = (decltype(L2.k))reinterpret_cast<u64*>(lb + (u64)sc.lcap * 8u);
-    L1.v = (decltype(L1.v))reinterpret_cast<u32*>(lb + (u64)sc.lcap * 16u);
-    L2.v = (decltype(L2.v))reinterpret_cast<u32*>(lb + (u64)sc.lcap * 20u);
-    nu = intake_list_lds(t, U, nu, L1, L2, dist, idbits);
+  memo->resident = false;
+  if (nu != 0 && sc.lcap != 0 && nu <= sc.lcap) nl = filter_live(t, U, nu, L1, dist);
+  if (nl != 0 || nu == 0) {
+    // the list is in the LDS after the levels: sort it there; if it is one
+    // piece it goes to S_0's (empty) array at once
+    nu = nl;
+    memo->resident = nu <= g.d;
+    if (memo->resident)
+      intake_sorted(t, L1, L2, sc.lcap, nu, as_arr<A0>(lbuf(g, 0, 3)), idbits);
+    else
+      intake_sorted(t, L1, L2, sc.lcap, nu, U, idbits);
   } else {
     G Wt{(decltype(G::k))sc.tk, (decltype(G::v))sc.tv};
     nu = intake_list(t, U, nu, Wt, dist, idbits);
@@ -2222,7 +2931,7 @@ PBH_INL void sssp_rounds(const T& t, const Geom& g, typename P::SP st, const u64
   }
   t.sync();
   SsspCounters c{0, 0, 1, 0, KINF, 0};
-  RoundMemo memo{0.0f, 1u};
+  RoundMemo memo{0.0f, 1u, false};
   u32 upos = 0, ulen = 0;
   for (;;) {
     // Resolve(0) and the schedule after the previous operation (the source's
@@ -2235,7 +2944,9 @@ PBH_INL void sssp_rounds(const T& t, const Geom& g, typename P::SP st, const u64
     if (SPEC && upos < ulen) {  // next piece of the round's bulk update
       u32 len = ulen - upos < g.d ? ulen - upos : g.d;
       G U{(decltype(G::k))sc.uk, (decltype(G::v))sc.uv};
-      if (g.qlds > 0) {
+      if (memo.resident) {
+        // nothing to move
+      } else if (g.qlds > 0) {
         typename P::L S = as_arr<typename P::L>(lbuf(g, 0, 3));
         for (u32 x = (u32)t.tid(); x < len; x += (u32)T::kNT) {
           S.k[x] = U.k[upos + x];

@@ -154,7 +154,7 @@ struct DevDeepSync {
   __device__ void merge_stats(const T& t, SP st, int lo, int q) const {
     if (t.tid() == 0) {
       st->elems += ld64(&c->elems);
-      if (st->prof_on)
+      if (t.prof)
         for (int j = lo; j < q; ++j) st->prof[j] += c->busy[j];
     }
     t.sync();
@@ -179,9 +179,9 @@ __device__ __attribute__((always_inline)) void deep_worker(DevTeam<NT, true>& t,
   g.lk = nullptr;  // worker levels are never in LDS
   g.lv = nullptr;
   if (p.stage) stage_setup(t, (unsigned char PBH_LDS*)dyn);
+  t.prof = p.prof;
   if (threadIdx.x == 0) {
     state_init(st, g.d, g.q);
-    st->prof_on = p.prof;
   }
   t.sync();
   DevDeepSync<DevTeam<NT, true>> sy{p.deep, p.deep_lim};
@@ -200,8 +200,8 @@ __device__ __attribute__((always_inline)) void deep_worker(DevTeam<NT, true>& t,
 // loop, and the call's register conventions left 248-256 VGPRs and a 350-byte
 // stack frame per lane (inlined: 126-193 VGPRs, no stack; learned ring 1.58
 // -> 1.37 s, the paper's DAG 2.08 -> 1.68 s, plain ring 11.56 -> 10.56 s).
-template <int NT, bool FULL, bool SPEC = true>
-__device__ __attribute__((always_inline)) void sssp_query(DevTeam<NT, FULL>& t, HeapState PBH_LDS* st,
+template <int NT, bool FULL, bool SPEC = true, bool SHARED = false>
+__device__ __attribute__((always_inline)) void sssp_query(DevTeam<NT, FULL, SHARED>& t, HeapState PBH_LDS* st,
                                                          unsigned char* dyn, const SsspParams& p) {
   Geom g = p.g;
   const u64 nl = lvl_off(g.d, g.qlds);
@@ -211,14 +211,14 @@ __device__ __attribute__((always_inline)) void sssp_query(DevTeam<NT, FULL>& t, 
   // Resolves it also holds a speculative round's list for its sort)
   if constexpr (FULL)
     if (p.stage) stage_setup(t, (unsigned char PBH_LDS*)(dyn + nl * 12u));
+  t.prof = p.prof;
   if (threadIdx.x == 0) {
     state_init(st, g.d, g.q);
-    st->prof_on = p.prof;
   }
   t.sync();
   SsspCounters c;
-  using TT = DevTeam<NT, FULL>;
-  if constexpr (FULL) {
+  using TT = DevTeam<NT, FULL, SHARED>;
+  if constexpr (FULL && SHARED) {
     // the deep-level service is off when it gets no sync object
     DevDeepSync<TT> sy{p.deep, p.deep_lim};
     if (p.deep) {
