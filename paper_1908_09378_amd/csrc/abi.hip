@@ -930,13 +930,36 @@ int sssp_batch(const sssp_query* queries, uint32_t nq, const sssp_opts* opts, ss
   }
   if (o.trace_features && (!o.trace_keys || !o.trace_ids || !o.trace_count || o.trace_every == 0))
     return fail(PBH_EINVAL, "sssp_batch: trace needs keys, ids, count and trace_every");
+  // The LDS after the levels holds the rounds' lists for the intake sort (as
+  // for a single query; the staging area shares it), as far as that costs no
+  // team its place: the teams that the queries can fill stay resident together
+  // (a batch of 1,024 queries of 64 threads loses more by waiting its turn).
+  const size_t lds_heap = lds;  // (the statistics' figure: the levels and the staging)
+  size_t lds_list = 0;
+  int need = 1;
+  if (spec_needs_list(o)) {
+    int per_cu = 0;
+    HIPCHK(hipDeviceGetAttribute(&per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev));
+    need = std::max(1, std::min(multi_occupancy(team, lds_heap), (int)(((u64)nq + cus - 1) / cus)));
+    const size_t taken = sssp_static_lds(team) + 2048;  // (with room for the allocation's grain)
+    const size_t share = (size_t)per_cu / (size_t)need;
+    lds_list = std::min(budget, share > taken ? share - taken : 0);
+  }
   std::vector<u64> lel(nq, 0);
   u64 total_lel = 0;
   for (u32 j = 0; j < nq; ++j) {
     u32 kmax = 1;
     int rc = spec_from_opts(o, desc[j].g.d, &desc[j].spec, &kmax);
     if (rc) return rc;
-    if (spec_needs_list(o)) lel[j] = 2ull * kmax * desc[j].g.d;
+    if (spec_needs_list(o)) {
+      lel[j] = 2ull * kmax * desc[j].g.d;
+      const size_t lvb = (size_t)lvl_off(desc[j].g.d, desc[j].g.qlds) * 12ull;
+      const u64 lcap = lds_list > lvb ? std::min<u64>((lds_list - lvb) / 24u, (u64)kmax * desc[j].g.d) : 0;
+      if (lcap >= 256) {
+        desc[j].spec.lcap = (u32)lcap;
+        lds = std::max(lds, lvb + (size_t)lcap * 24u);
+      }
+    }
     total_lel += lel[j];
     if (o.trace_features) {
       desc[j].spec.trace_f = o.trace_features;
@@ -1029,7 +1052,7 @@ int sssp_batch(const sssp_query* queries, uint32_t nq, const sssp_opts* opts, ss
     stats->levels = 0;
     stats->d = dmax;
     stats->team = (u32)team;
-    stats->lds_levels = (u32)(lds / 12);
+    stats->lds_levels = (u32)(lds_heap / 12);
     stats->kernel_ms = ms;
   }
   // Queries whose heap outgrew its slice run again alone, starting from the

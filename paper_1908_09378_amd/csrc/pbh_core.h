@@ -1782,6 +1782,25 @@ PBH_INL void drive_with(const T& t, const Geom& g, SP st, int sched, int what, R
       if (g.q < 2 || (bS + push <= capS(g.d, 1) && bB + bS + push <= capB(g.d, 1)) || lim <= 1) {
         stage = 1;  // Resolve(0), with room below it
         tgt = lvl = 0;
+        if constexpr (T::kW > 1) {
+          // Nothing to empty and nothing to fill (half of the speculative
+          // rounds' Resolves): only the count and an emptied level 0 show.
+          const u32 nb = t.uni(nB0), ell = t.uni(ell0), cnt = t.uni(cnt0) + 1u;
+          if (push == nb && nb <= (u32)nomB(g.d, 0) && ((int)ell < 1 || nb == (u32)nomB(g.d, 0))) {
+            t.sync();
+            if (t.tid() == 0) {
+              st->L[0].cnt = cnt;
+              if ((int)ell < 1) st->ell = nb ? 0 : -1;
+            }
+            t.sync();
+            if (sched == 0 && ((int)ell < 1 || (cnt & 3u) != 0)) {
+              stage = 2;
+              if (!(what & DRIVE_ENSURE) || nb != 0 || (int)ell < 1) break;
+            }
+            lvl = -1;
+            continue;
+          }
+        }
       }
     } else if (stage == 1 && chain < 0 && si == 0 && sched == 0 &&
                ((int)t.uni(ell0) < 1 || (t.uni(cnt0) & 3u) != 0)) {
@@ -2747,8 +2766,8 @@ PBH_INL bool round_spec(const T& t, const Geom& g, typename P::SP st, const u64*
     for (u32 j = (u32)t.tid(); j < take; j += (u32)T::kNT)
       if (c->extracted + j < sc.order_cap) sc.order[c->extracted + j] = X.v[j];
   prof_lap(t, st, PROF_EXTRACT);
-  // out-degree prefix sums of the extracted vertices
-  u32 E = 0;
+  // the extracted vertices' rows: first edge and prefix sums of the out-degrees
+  u32 E = 0, maxdeg = 0;
   for (u32 base = 0; base < take; base += (u32)T::kNT) {
     u32 j = base + (u32)t.tid();
     u64 e0 = 0, e1 = 0;
@@ -2762,9 +2781,51 @@ PBH_INL bool round_spec(const T& t, const Geom& g, typename P::SP st, const u64*
     u32 p = E + t.scan_excl((u32)(e1 - e0), &tot);
     if (j < take) t.sh->exd[j] = p;
     E += tot;
+    maxdeg = (u32)(e1 - e0) > maxdeg ? (u32)(e1 - e0) : maxdeg;
   }
+  maxdeg = t.wave_max32(maxdeg);
   if (t.tid() == 0) t.sh->exd[take] = E;
+  if constexpr (T::kNW > 1) {
+    if (t.lane() == 0) t.sh->wv[t.wave()] = maxdeg;
+  }
   t.sync();
+  if constexpr (T::kNW > 1) {
+#pragma unroll
+    for (int w = 0; w < T::kNW; ++w) maxdeg = t.sh->wv[w] > maxdeg ? t.sh->wv[w] : maxdeg;
+    maxdeg = t.uni(maxdeg);
+  }
+  // Which edge is whose.  With even degrees, by groups: 2^gl lanes (the mean
+  // degree, rounded up) scan a vertex's edges in `per` steps; a row is a block
+  // of vertices at one step, and two LDS reads give a thread its edge.  Where
+  // that would leave more than a third of the threads without one (measured on
+  // degrees around 24: slower than searching), an edge's vertex is the largest
+  // j with exd[j] <= e.  The edges are then taken kW at a time by a wavefront:
+  // the vertex of every kW-th edge is found first (one search per thread), and
+  // an edge's own search runs over the few vertices of its wavefront's edges.
+  u32 gl = 2;
+  while (gl < 6 && ((u64)take << gl) < E) ++gl;
+  if ((u32)T::kNT < 64u) gl = 0;
+  const u32 per = (maxdeg + (1u << gl) - 1) >> gl, vpr = (u32)T::kNT >> gl;
+  const u64 grows = (u64)((take + vpr - 1) / vpr) * per;
+  const bool groups = 2ull * grows * T::kNT <= 3ull * E + 2ull * T::kNT;
+  auto owner = [&](u32 e, u32 lo, u32 hi) -> u32 {
+    while (hi - lo > 1) {
+      const u32 mid = (lo + hi) >> 1;
+      if (t.sh->exd[mid] <= e)
+        lo = mid;
+      else
+        hi = mid;
+    }
+    return lo;
+  };
+  const u32 nch = (E + (u32)T::kW - 1) / (u32)T::kW;
+  const u32 rows = groups ? (u32)grows : (E + (u32)T::kNT - 1) / (u32)T::kNT;
+  const bool marked = !groups && T::kW > 1 && nch < 256u;
+  if (marked) {
+    for (u32 c = (u32)t.tid(); c <= nch; c += (u32)T::kNT)
+      t.sh->hist[c] = owner(c * (u32)T::kW < E ? c * (u32)T::kW : E - 1, 0, take);
+    t.sync();
+  }
   G U{(decltype(G::k))sc.uk, (decltype(G::v))sc.uv};
   // the LDS after the levels, two lists of lcap pairs
   using L = typename P::L;
@@ -2775,46 +2836,78 @@ PBH_INL bool round_spec(const T& t, const Geom& g, typename P::SP st, const u64*
   L1.v = (decltype(L1.v))reinterpret_cast<u32*>(lb + (u64)sc.lcap * 16u);
   L2.v = (decltype(L2.v))reinterpret_cast<u32*>(lb + (u64)sc.lcap * 20u);
   u32 nu = 0, nl = 0;  // improved pairs in U / final pairs in L1
-  // RE edges per thread per pass: their CSR loads and atomics are all in
-  // flight before any result is waited for; one scan places the improvements.
+  // RE rows per pass: their CSR loads and atomics are all in flight before any
+  // result is waited for; one scan places the improvements.
   constexpr int RE = 8;
-  for (u32 eb = 0; eb < E; eb += (u32)T::kNT * RE) {
-    u64 ei[RE], cand[RE];
-    u32 v[RE];
+  u32 blk = 0, stp = 0;  // block of vertices and step of the next row (groups)
+  for (u32 rb = 0; rb < rows; rb += RE) {
+    u64 cand[RE];
+    u32 v[RE], w[RE];
     bool imp[RE];
 #pragma unroll
     for (int r = 0; r < RE; ++r) {
-      const u32 e = eb + (u32)r * (u32)T::kNT + (u32)t.tid();
-      ei[r] = 0;
+      imp[r] = false;
       cand[r] = 0;
-      if (e < E) {
-        u32 lo = 0, hi = take;  // largest j with exd[j] <= e
-        while (hi - lo > 1) {
-          u32 mid = (lo + hi) >> 1;
-          if (t.sh->exd[mid] <= e)
-            lo = mid;
-          else
-            hi = mid;
+      v[r] = w[r] = 0;
+      if (rb + (u32)r >= rows) continue;
+      u32 lo = 0, at;
+      bool in;
+      if (groups) {
+        const u32 j = blk * vpr + ((u32)t.tid() >> gl);
+        lo = j < take ? j : take - 1;
+        at = (stp << gl) + ((u32)t.tid() & ((1u << gl) - 1u));
+        in = j < take && at < t.sh->exd[lo + 1] - t.sh->exd[lo];
+        if (++stp == per) {
+          stp = 0;
+          ++blk;
         }
-        ei[r] = t.sh->ex0[lo] + (e - t.sh->exd[lo]);
-        cand[r] = X.k[lo];
+      } else {
+        const u32 e = (rb + (u32)r) * (u32)T::kNT + (u32)t.tid();
+        u32 hi = take;
+        in = e < E;
+        if (marked) {
+          const u32 c = (rb + (u32)r) * T::kNW + t.uni((u32)t.wave());
+          if (c < nch) {
+            lo = t.uni(t.sh->hist[c]);
+            hi = t.uni(t.sh->hist[c + 1]) + 1u;
+          }
+        }
+        lo = owner(in ? e : E - 1, lo, hi);
+        at = e - t.sh->exd[lo];
       }
+      const u64 ei = in ? t.sh->ex0[lo] + at : 0ull;
+      imp[r] = in;  // (a thread without an edge reads the graph's first one)
+      v[r] = tg[ei];
+      w[r] = wt[ei];
+      cand[r] = X.k[lo];
     }
+    // Most edges improve nothing.  In a round of one pass the distances are
+    // looked at first, and atomics go out only for what may improve them
+    // (distances only fall: an old value lets a needless atomic through, no
+    // more): ring of 100,003, 900 edges a round, 5.8 -> 4.9 us.  In larger
+    // rounds a compute unit's time is the number of lines it asks for, which
+    // the look would add to: 6,000 scattered edges, 31 us without, 34 with it.
+    u64 now[RE];
 #pragma unroll
     for (int r = 0; r < RE; ++r) {
-      const bool in = eb + (u32)r * (u32)T::kNT + (u32)t.tid() < E;
-      v[r] = in ? tg[ei[r]] : 0u;
-      cand[r] += in ? (u64)wt[ei[r]] : 0ull;
+      now[r] = KINF;
+      if (rows <= (u32)RE && (u32)r < rows) now[r] = t.load_cur(dist + v[r]);
     }
     u32 cnt = 0;
 #pragma unroll
     for (int r = 0; r < RE; ++r) {
-      const bool in = eb + (u32)r * (u32)T::kNT + (u32)t.tid() < E;
-      imp[r] = in && cand[r] < t.atomic_min(dist + v[r], cand[r]);
+      if (rb + (u32)r >= rows) continue;
+      cand[r] += (u64)w[r];
+      imp[r] = imp[r] && cand[r] < now[r];
+    }
+#pragma unroll
+    for (int r = 0; r < RE; ++r) {
+      if (rb + (u32)r >= rows) continue;
+      if (imp[r]) imp[r] = cand[r] < t.atomic_min(dist + v[r], cand[r]);
       cnt += imp[r] ? 1u : 0u;
     }
     u32 tot;
-    if (sc.lcap != 0 && E <= (u32)T::kNT * RE) {
+    if (sc.lcap != 0 && rows <= (u32)RE) {
       // The round's only pass: once every edge is relaxed (the barrier), a
       // pair whose key is the distance is final, so the filter works on the
       // registers and the list goes straight to LDS; U, its way through global

@@ -201,6 +201,7 @@ struct DevTeam {
   __device__ __forceinline__ u32 lane_val(u32 x, int l) const { return __builtin_amdgcn_readlane(x, l); }
   __device__ __forceinline__ u64 lane_val64(u64 x, int l) const { return readlane64(x, l); }
   __device__ __forceinline__ bool any_lane(bool p) const { return __ballot(p) != 0; }
+  __device__ __forceinline__ u32 wave_max32(u32 x) const { return ~wave_min32(~x); }
   __device__ __forceinline__ u32 wave_or32(u32 x) const { return wave_or(x); }
   // Inclusive prefix sum within the wavefront.
   __device__ __forceinline__ u32 wave_scan(u32 x) const { return wave_incl(x); }
@@ -371,6 +372,7 @@ struct HostTeamT {
   u32 lane_val(u32 x, int) const { return x; }
   u64 lane_val64(u64 x, int) const { return x; }
   bool any_lane(bool p) const { return p; }
+  u32 wave_max32(u32 x) const { return x; }
   u32 wave_or32(u32 x) const { return x; }
   u32 wave_scan(u32 x) const { return x; }
   void wsync() const {}

@@ -4,6 +4,7 @@ level in HBM (the general forms), and Select at the edges of its forms."""
 import numpy as np
 import pytest
 
+import oracle
 import paper_1908_09378_amd as pkg
 import workloads as W
 from gpu_util import dev32, run_sssp
@@ -64,3 +65,52 @@ def run_select(nt, keys, ids, r):
     assert rc == 0
     h = host64(out)
     return int(h[0]), int(h[1])
+
+
+def skewed(n, hub, deg, seed):
+    """`deg` edges from each vertex, one after another on a ring, some without
+    any, and two hubs of `hub` edges."""
+    rng = np.random.default_rng(seed)
+    cnt = np.full(n, deg, np.int64)
+    cnt[rng.integers(1, n, n // 8)] = 0
+    cnt[[0, n // 2]] = hub
+    off = np.concatenate([[0], np.cumsum(cnt)]).astype(np.uint64)
+    m = int(off[-1])
+    src = np.repeat(np.arange(n), cnt)
+    tg = ((src + rng.integers(1, 3 * deg + 2, m)) % n).astype(np.uint32)
+    far = rng.random(m) < 0.2
+    tg[far] = rng.integers(0, n, int(far.sum()))
+    return W.csr_from_edges(n, src, tg, rng.integers(0, 50, m).astype(np.uint32), "skewed")
+
+
+@pytest.mark.parametrize("team", [64, 256, 1024])
+@pytest.mark.parametrize("hub,deg", [(0, 1), (5, 4), (64, 16), (700, 3), (2100, 24), (9000, 2)])
+def test_whose_edge_is_whose(team, hub, deg):
+    """The two ways of dealing out the edges of a round (groups of lanes for
+    even degrees, a search for others), with one and with several passes."""
+    g = skewed(997, hub or 1, deg, hub + deg)
+    ref = oracle.dijkstra(g, 0)
+    for k in (1, 2, 63, 64, 256):
+        d, _ = run_sssp(pkg, g, 0, d=max(64, g.max_degree()), team=team, k_rule=pkg.K_FIXED, k_fixed=k, k_max=256)
+        assert np.array_equal(d, ref), k
+
+
+@pytest.mark.parametrize("nq", [3, 600])
+def test_batch_lists(nq):
+    """Round lists in LDS (few queries) and as far as residency leaves room."""
+    import torch
+    from gpu_util import DEV, graph_to_dev, host64
+    gs = [W.grid4(31, 17, 1, 100, 3), skewed(600, 200, 5, 1), W.path_graph(80)]
+    dg = [graph_to_dev(g) for g in gs]
+    qs, refs = [], []
+    for i in range(nq):
+        g = gs[i % 3]
+        s = i % 7
+        qs.append((*dg[i % 3], g.n, g.m, s, torch.empty(g.n, dtype=torch.int64, device=DEV)))
+        refs.append(oracle.dijkstra(g, s))
+    for team in (64, 256):
+        for q in qs:
+            q[6].fill_(7)
+        pkg.sssp_batch(qs, k_rule=pkg.K_FIXED, k_fixed=40, k_max=256, team=team)
+        for q, ref in zip(qs, refs):
+            assert np.array_equal(host64(q[6]), ref)
