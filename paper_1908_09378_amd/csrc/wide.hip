@@ -1,18 +1,18 @@
 // Device-wide engine of the parallel bucket heap (see wide.h).
 //
 // Kernels (256 threads per workgroup, tiles of 2048 elements):
-//   k_merge<false> / k_scan / k_merge<true>
+//   k_merge<false> / k_merge<true>
 //       Merge of two id-sorted arrays with DeleteDuplicates (Section 2.1):
 //       a counting pass (which also finds each tile's merge-path split
-//       points), a scan of the tile counts, and a writing pass; in both passes
-//       each thread walks 8 consecutive merge positions from one merge-path
-//       search in LDS, and the writing pass stores its outputs through an
-//       LDS transpose.  The counting pass can also count outputs <= a pivot
-//       (the count in Resolve's EMPTY step) and the key range (the start of
-//       Select), as per-workgroup partials folded by the scan, which then
-//       publishes the step before the writing pass runs.
-//   k_part<false> / k_scan (three arrays) / k_part<true>
+//       points and, where Resolve asks for it, counts the outputs <= a pivot)
+//       and a writing pass; in both each thread walks 8 consecutive merge
+//       positions from one merge-path search in LDS, and the writing pass
+//       stores its outputs through an LDS transpose and notes their key range
+//       (the start of Select).
+//   k_part<false> / k_part<true>
 //       Stable three-way split by two (key, id) pivots.
+//   A counting pass adds its counts up as its workgroups end, 64 of them at a
+//   time; a writing pass's workgroup sums what is before its tile itself.
 //   k_sel_pass / k_sel_collect
 //       Select: radix selection on the 96-bit (key, id) value, 8 bits per
 //       pass from the first bit where the keys differ, until at most 256
@@ -28,8 +28,9 @@
 //       and LDS (per-thread sort, then merge-path rounds), then merge passes.
 //   k_absent, k_delete
 //       Mark extracted or deleted ids absent.
-// The few results the host needs after a step (sizes, the selected element)
-// are written by the step's last kernel into host-mapped memory.
+// The few results the host needs after a step are written into host-mapped
+// memory as soon as they are known; the host goes on while the step's writing
+// pass runs.
 #include "wide.h"
 
 #include <algorithm>
@@ -56,10 +57,8 @@ constexpr int GRID_HIST = 512;           // workgroups of a Select pass or gathe
                                          // atomics, and one on the shared pass counter: about 10 ns
                                          // each on one address, 2048 workgroups measured 20 us)
 
-// Device-side state of a selection (read and written by the Select kernels)
-// and the key range of the array it runs on.
+// Device-side state of a selection (read and written by the Select kernels).
 struct Ctl {
-  u64 kmin, kmax;
   u64 spk;
   u32 spv;
   int snb;      // leading bits of (key, id) fixed so far
@@ -71,35 +70,45 @@ struct Ctl {
   u32 sncand;
   u32 passdone;  // workgroups finished with the current pass (the last one picks)
   u32 npass;     // passes that did work since the last gather (profiling)
-  u32 scandone;  // workgroups of a publishing k_scan finished (the last one publishes)
   u32 shist[SEL_BINS];
 };
 
-// What the host reads after a step.  The step's kernels write it in device
-// memory; k_post then copies it into host-mapped coherent memory and writes
+// What the host reads of a selection.  The Select kernels write it in device
+// memory (the split reads it there) and then into host-mapped coherent memory,
 // the step's sequence number last, which the host polls.
 struct Mail {
-  u32 total;    // output size of a merge or of the mark compaction
-  u32 num_le;   // merge outputs <= the counting pivot
-  u32 part[4];  // three-way split sizes
-  u64 newly;    // ids inserted by the intake
   u64 rk;       // selected element
   u32 rv;
   int sfail;    // the selection needs more passes
   int sbad;     // the selection found no element of the rank (never expected)
   u32 npass;    // Select passes of the step that did work (the others returned at once)
-  u32 pad_;     // keeps seq the struct's last word
   u32 seq;      // number of the last step published (host copy only)
 };
-static_assert(offsetof(Mail, seq) + sizeof(u32) == sizeof(Mail) && sizeof(Mail) % 4 == 0,
-              "k_post copies whole words and writes seq last");
-constexpr u32 MAIL_WORDS = sizeof(Mail) / 4;
 
 __device__ __forceinline__ u64 atomic_min64(u64* p, u64 v) {
   return __hip_atomic_fetch_min((u64 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ u64 atomic_max64(u64* p, u64 v) {
+  return __hip_atomic_fetch_max((u64 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ u32 atomic_add32(u32* p, u32 v) {
   return __hip_atomic_fetch_add((u32 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Agent-scope atomic loads and stores: coherent across the XCDs' L2 caches
+// within a launch, for words that workgroups of one launch hand to each
+// other (a plain store can stay in one XCD's L2 until the kernel ends).
+__device__ __forceinline__ u32 ld_a32(const u32* p) {
+  return __hip_atomic_load((const u32 PBH_GLB*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ u64 ld_a64(const u64* p) {
+  return __hip_atomic_load((const u64 PBH_GLB*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_a32(u32* p, u32 v) {
+  __hip_atomic_store((u32 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_a64(u64* p, u64 v) {
+  __hip_atomic_store((u64 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Exclusive scan over the workgroup (NTH threads); *total = the sum.
@@ -146,6 +155,70 @@ __device__ __forceinline__ void block_minmax(u64& lo, u64& hi, u64* swl, u64* sw
   __syncthreads();
 }
 
+// ------------------------------------------------------------------ counts
+//
+// A counting pass's workgroups leave their tiles' counts in memory and add
+// them up in passing, per 64 tiles; the last of each 64 has their sums and
+// posts them to the host.  A workgroup of the writing pass sums the counts
+// before its tile itself, by one or two loads per lane of one wavefront.  (A
+// scan kernel between the passes took 3 to 9 us and two gaps between
+// launches.  One pass that counts and writes, each tile waiting for the counts
+// of the tiles before it, was slower: 91-110 us for a merge of 8.4 million
+// elements and 131 us for a split, 66-84 and 66 us in two passes, because
+// every tile then waits with its LDS and registers held; and the host learns
+// the sizes only at its end.)
+
+__device__ __forceinline__ u64 atomic_add64(u64* p, u64 v) {
+  return __hip_atomic_fetch_add((u64 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Up to three counts of 64 workgroups in one word: F fields of 57 / F bits,
+// and above them how many of the workgroups have added theirs.
+template <int F>
+struct Field {
+  static constexpr u32 bits = 57u / F;
+  static constexpr u64 mask = (1ull << bits) - 1;
+};
+constexpr u64 ARRIVED = 1ull << 57;
+constexpr u32 LINE = 16;  // words of 8 bytes in a cache line
+
+// The end of workgroup t of nt, by one thread: the last of its 64 leaves their
+// packed sums in gs[t / 64] (when set), where the writing pass reads them, and
+// posts the full word to the host, which adds the groups up (one more stage on
+// the device, over the groups' sums, took 3.7 us).  Atomics on one cache line
+// take about 10 ns each, so each word has a line of its own.
+__device__ __forceinline__ void arrive(u64* acc, u64* gs, u64* post, u32 t, u32 nt, u64 counts) {
+  const u32 g = t >> 6;
+  u64* w = acc + (u64)LINE * g;
+  const u64 a = atomic_add64(w, ARRIVED + counts) + ARRIVED + counts;
+  if ((u32)(a >> 57) != min(64u, nt - (g << 6))) return;
+  st_a64(w, 0ull);
+  if (gs) gs[g] = a & (ARRIVED - 1);
+  __hip_atomic_store(post + g, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Key range of a merge's outputs, per 64 tiles: the writing pass's workgroups
+// widen their group's by atomics.  (One range for all: 4096 workgroups took
+// twice as long for it.)  A line each.
+struct alignas(128) Range {
+  u64 lo, hi;
+};
+
+// What a counting pass leaves and a writing pass reads.
+struct Pass {
+  u32* tc;     // tile counts, one array of `stride` per output stream
+  u32 stride;
+  u64* gs;     // sums of 64 tiles, packed
+  u64* acc;    // arrival words, a line each
+  u64* post;   // host-mapped: a word per 64 tiles
+};
+// The outputs before tile t in stream f of F, by one wavefront.
+template <int F>
+__device__ __forceinline__ u32 before_tile(const Pass& ps, u32 f, u32 t) {
+  const u32 lane = threadIdx.x & 63u, g = t >> 6;
+  u32 x = lane < (t & 63u) ? ps.tc[(u64)f * ps.stride + (g << 6) + lane] : 0u;
+  for (u32 y = lane; y < g; y += 64u) x += (u32)((ps.gs[y] >> (f * Field<F>::bits)) & Field<F>::mask);
+  return __builtin_amdgcn_readlane(wave_incl(x), 63);
+}
 // How many of the first `diag` elements of merge(A, B) come from A; ties go
 // to A first.  ById compares ids, otherwise (key, id).
 template <bool BYKV, class KP, class VP>
@@ -215,9 +288,9 @@ struct MArgs {
   u32 nb;
   u64* ck;
   u32* cv;
-  const u64* cur;  // liveness for PREFER_LIVE and filterB (may be null)
+  const u64* cur;  // liveness for PREFER_LIVE (may be null)
   int prefer;
-  int filterB;
+  Range* range;    // where the outputs' key range goes (may be null)
   u64 pk;          // outputs <= (pk, pv) are counted
   u32 pv;
 };
@@ -241,10 +314,6 @@ __device__ __forceinline__ bool pair_keep(const MArgs& a, u64 ka, u64 kb, u32 v,
   return true;
 }
 
-// Split searches per workgroup of the sort's partition kernel (one
-// wavefront each).
-constexpr u32 SPW = NT / 64;
-
 // One tile of merge(A, B) by id with DeleteDuplicates: the outputs at merge
 // positions [t*TILE, (t+1)*TILE), whose inputs are A[i0, i1) and B[j0, j1)
 // (staged in LDS: ids, and keys in the writing pass).  Each thread takes WE
@@ -252,32 +321,25 @@ constexpr u32 SPW = NT / 64;
 // start, then a sequential walk merges them (ties: A first), so a copy of an
 // id present in both inputs sits right after A's copy.  The pair is decided
 // at A's slot (pair_keep) and B's slot is dropped; a partner just outside the
-// tile is A[i0-1] or B[j1].  Counting pass: tcnt[t] = kept outputs; with
-// KEYS it also stages the keys and counts the outputs <= (pk, pv) and their
-// key range, as per-workgroup partials (thousands of workgroups updating the
-// same word with atomics would serialise in the L2) that the scan folds.
-// So the scan, which runs before the writing pass, has every result the host
-// reads.  Writing pass: a scan of the threads' kept counts gives each output
-// its place in the tile's output range; the outputs are transposed through
-// LDS (reusing the input staging, at index o + o/8 so that the threads' runs
-// of WE spread over the banks) and stored coalesced at toff[t] + o.  Stored
-// straight from the walk, each store instruction would touch 64 cache lines
-// (a thread's outputs are consecutive), which measured 1.6x slower.
-struct Partials {
-  u32* cnt;
-  u64* lo;
-  u64* hi;
-};
-
+// tile is A[i0-1] or B[j1].  Counting pass: the tile's kept outputs; with KEYS
+// it also stages the keys and counts the outputs <= (pk, pv), which Resolve's
+// EMPTY step needs before the writing pass.  Writing pass: a scan of the
+// threads' kept counts gives each output its place in the tile's output
+// range; the outputs are transposed through LDS (reusing the input staging,
+// at index o + o/8 so that the threads' runs of WE spread over the banks) and
+// stored coalesced.  Stored straight from the walk, each store instruction
+// would touch 64 cache lines (a thread's outputs are consecutive), which
+// measured 1.6x slower.  The key range goes into ctl by atomics, of which
+// nearly all are spared by a look at the range so far.
 template <bool WRITE, bool KEYS = WRITE>
-__global__ __launch_bounds__(NT) void k_merge(MArgs a, const u32* part, u32* part_out, u32* tcnt, const u32* toff,
-                                              Partials pt) {
+__global__ __launch_bounds__(NT) void k_merge(MArgs a, u32* part, Pass ps) {
   static_assert(KEYS || !WRITE, "the writing pass stages keys");
   constexpr u32 NONE = 0xFFFFFFFFu;  // exhausted input (ids are < 2^32 - 1)
   constexpr u32 PAD = WRITE ? TILE / 8 : 0;  // room for the transposed index o + o/8
   __shared__ u32 sv[TILE + PAD];
   __shared__ u64 sk[KEYS ? TILE + PAD : 1];
   __shared__ u32 sw[NT / 64];
+  __shared__ u32 s_base;
   __shared__ u64 swl[NT / 64], swh[NT / 64];
   const u32 t = blockIdx.x, total = a.na + a.nb;
   const u32 d0 = t * TILE, d1 = min(d0 + TILE, total);
@@ -297,12 +359,16 @@ __global__ __launch_bounds__(NT) void k_merge(MArgs a, const u32* part, u32* par
     i0 = ssplit[0];
     i1 = ssplit[1];
     if (threadIdx.x == 0) {
-      part_out[t] = i0;
-      if (t + 1 == gridDim.x) part_out[t + 1] = i1;
+      part[t] = i0;
+      if (t + 1 == gridDim.x) part[t + 1] = i1;
     }
   } else {
     i0 = part[t];
     i1 = part[t + 1];
+    if (threadIdx.x < 64) {
+      const u32 b = before_tile<2>(ps, 0, t);
+      if (threadIdx.x == 0) s_base = b;
+    }
   }
   const u32 j0 = d0 - i0, j1 = d1 - i1;
   const u32 nA = i1 - i0, nT = d1 - d0, nB = nT - nA;
@@ -369,7 +435,6 @@ __global__ __launch_bounds__(NT) void k_merge(MArgs a, const u32* part, u32* par
       const u32 v = vb;
       const u64 k = KEYS ? sk[nA + j] : 0ull;
       kp = !(havePrevA && prevA == v);
-      if (kp && a.filterB) kp = a.cur[v] == (KEYS ? k : a.bk[j0 + j]);
       vo[q] = v;
       ko[q] = k;
       ++j;
@@ -379,31 +444,22 @@ __global__ __launch_bounds__(NT) void k_merge(MArgs a, const u32* part, u32* par
   }
   const u32 nk = (u32)__builtin_popcount(keep);
   if constexpr (!WRITE) {
-    const u32 tot = block_sum<NT>(nk, sw);
-    if (threadIdx.x == 0) tcnt[t] = tot;
+    u32 nle = 0;
     if constexpr (KEYS) {
-      // statistics of the kept outputs: how many are <= (pk, pv), and the
-      // key range
-      u32 nle = 0;
-      u64 lo = KINF, hi = 0;
 #pragma unroll
-      for (int q = 0; q < WE; ++q)
-        if ((keep >> q) & 1u) {
-          nle += kv_le(KV{ko[q], vo[q]}, KV{a.pk, a.pv});
-          lo = ko[q] < lo ? ko[q] : lo;
-          hi = ko[q] > hi ? ko[q] : hi;
-        }
-      nle = block_sum<NT>(nle, sw);
-      block_minmax<NT>(lo, hi, swl, swh);
-      if (threadIdx.x == 0) {
-        pt.cnt[t] = nle;
-        pt.lo[t] = lo;
-        pt.hi[t] = hi;
-      }
+      for (int q = 0; q < WE; ++q) nle += ((keep >> q) & 1u) && kv_le(KV{ko[q], vo[q]}, KV{a.pk, a.pv});
+    }
+    const u32 tot = block_sum<NT>(nk | (nle << 16), sw);  // (a tile's counts fit 16 bits)
+    if (threadIdx.x == 0) {
+      const u32 kept = tot & 0xFFFFu;
+      ps.tc[t] = kept;
+      if (a.range && (t & 63u) == 0) a.range[t >> 6] = Range{KINF, 0};  // (for the writing pass)
+      arrive(ps.acc, ps.gs, ps.post, t, gridDim.x, kept | ((u64)(tot >> 16) << Field<2>::bits));
     }
   } else {
     u32 tot;
     u32 o = block_scan<NT>(nk, &tot, sw);  // its barriers also end every walk's reads of sv / sk
+    u64 lo = KINF, hi = 0;
 #pragma unroll
     for (int q = 0; q < WE; ++q)
       if ((keep >> q) & 1u) {
@@ -411,9 +467,17 @@ __global__ __launch_bounds__(NT) void k_merge(MArgs a, const u32* part, u32* par
         sk[z] = ko[q];
         sv[z] = vo[q];
         ++o;
+        lo = ko[q] < lo ? ko[q] : lo;
+        hi = ko[q] > hi ? ko[q] : hi;
       }
-    __syncthreads();
-    const u32 base = toff[t];
+    block_minmax<NT>(lo, hi, swl, swh);  // (its barriers also order the transpose)
+    if (a.range && threadIdx.x == 0 && tot != 0) {
+      Range* r = a.range + (t >> 6);
+      const u64 clo = ld_a64(&r->lo), chi = ld_a64(&r->hi);
+      if (lo < clo) atomic_min64(&r->lo, lo);
+      if (hi > chi) atomic_max64(&r->hi, hi);
+    }
+    const u32 base = s_base;
 #pragma unroll
     for (int q = 0; q < WE; ++q) {
       const u32 x = threadIdx.x + (u32)q * NT;
@@ -425,118 +489,6 @@ __global__ __launch_bounds__(NT) void k_merge(MArgs a, const u32* part, u32* par
     }
   }
 }
-
-// A step published by the kernel that computes the last result the host
-// reads (the scan of a merge, split or compaction, which also folds the
-// merge's statistics), instead of by k_post after the step's last kernel:
-// the host then reads the sizes and goes on while the step's writing pass,
-// whose output it never reads, still runs (its next launches queue behind
-// that pass on the stream).  mail == nullptr: the kernel does not publish.
-struct Pub {
-  const Mail* box;
-  Mail* mail;
-  u32 seq;
-};
-
-// Copies the box into the host-mapped mailbox and then writes the sequence
-// number (as k_post).  Called by every thread of the publishing workgroup
-// once its results are in the box: the wait and the barrier make this
-// workgroup's stores reach the L2, which the agent-scope loads read.
-__device__ __forceinline__ void publish(const Pub& p) {
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  const u32 l = threadIdx.x;
-  if (l + 1 < MAIL_WORDS) {
-    ((u32*)p.mail)[l] =
-        __hip_atomic_load((const u32 PBH_GLB*)p.box + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __threadfence_system();
-  }
-  __syncthreads();
-  if (l == 0) __hip_atomic_store(&p.mail->seq, p.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-// Sums n partial counts into *sum (when sum != null) and folds the partial
-// key ranges into ctl->kmin / kmax.  One workgroup.
-__global__ __launch_bounds__(1024) void k_reduce(Partials pt, u32 n, u32* sum32, u64* sum64, Ctl* c) {
-  __shared__ u32 sw[16];
-  __shared__ u64 swl[16], swh[16];
-  u64 tot = 0, lo = KINF, hi = 0;
-  for (u32 x = threadIdx.x; x < n; x += 1024) {
-    tot += pt.cnt[x];
-    if (pt.lo) {
-      lo = pt.lo[x] < lo ? pt.lo[x] : lo;
-      hi = pt.hi[x] > hi ? pt.hi[x] : hi;
-    }
-  }
-  const u32 s = block_sum<1024>((u32)tot, sw);
-  block_minmax<1024>(lo, hi, swl, swh);
-  if (threadIdx.x == 0) {
-    if (sum32) *sum32 = s;
-    if (sum64) *sum64 = s;
-    if (pt.lo) {
-      c->kmin = lo;
-      c->kmax = hi;
-    }
-  }
-}
-
-// Exclusive scan of n tile counts (one workgroup of 1024); *total = the sum.
-// blockIdx.x selects one of several count arrays spaced `stride` apart.
-// With fold.cnt set (one workgroup only) it also folds n per-tile partials:
-// *fold_sum = their count, ctl->kmin / kmax = their key range.  With
-// pub.mail set, the last of the workgroups to finish publishes the step
-// (ctl->scandone counts them; the totals are stored with agent-scope stores
-// so that it reads every one).
-__global__ __launch_bounds__(1024) void k_scan(const u32* cnt, u32 n, u32 stride, u32* off, u32* total, Ctl* ctl,
-                                               Pub pub, Partials fold, u32* fold_sum) {
-  __shared__ u32 sw[16];
-  __shared__ u64 swl[16], swh[16];
-  __shared__ int s_last;
-  if (fold.cnt) {
-    u32 c = 0;
-    u64 lo = KINF, hi = 0;
-    for (u32 x = threadIdx.x; x < n; x += 1024) {
-      c += fold.cnt[x];
-      lo = fold.lo[x] < lo ? fold.lo[x] : lo;
-      hi = fold.hi[x] > hi ? fold.hi[x] : hi;
-    }
-    c = block_sum<1024>(c, sw);
-    block_minmax<1024>(lo, hi, swl, swh);
-    if (threadIdx.x == 0) {
-      *fold_sum = c;
-      ctl->kmin = lo;
-      ctl->kmax = hi;
-    }
-  }
-  cnt += (u64)blockIdx.x * stride;
-  off += (u64)blockIdx.x * stride;
-  u32 carry = 0;
-  for (u32 b = 0; b < n; b += 1024) {
-    u32 x = b + threadIdx.x;
-    u32 v = x < n ? cnt[x] : 0u;
-    u32 tot;
-    u32 e = block_scan<1024>(v, &tot, sw);
-    if (x < n) off[x] = carry + e;
-    carry += tot;
-  }
-  if (threadIdx.x == 0)
-    __hip_atomic_store((u32 PBH_GLB*)(total + blockIdx.x), carry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (!pub.mail) return;
-  if (gridDim.x > 1) {
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      const u32 prev =
-          __hip_atomic_fetch_add((u32 PBH_GLB*)&ctl->scandone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      s_last = prev == gridDim.x - 1;
-      if (s_last) __hip_atomic_store((u32 PBH_GLB*)&ctl->scandone, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    if (!s_last) return;
-  }
-  publish(pub);
-}
-
 
 // ------------------------------------------------------------------ three-way split
 
@@ -575,59 +527,90 @@ __device__ __forceinline__ u32 pclass(const PArgs& a, KV p1, u64 k, u32 v) {
   return c;
 }
 
-// Tile t = elements [t*TILE, (t+1)*TILE), visited in WE rounds of NT
-// consecutive elements so that each round's outputs are written coalesced.
+// Tile t = elements [t*TILE, (t+1)*TILE) in WE rounds of NT consecutive
+// elements, so that each round's outputs are written in runs.  A ballot per
+// class counts a wavefront's elements of a round; the tile's 32 counts (8
+// rounds x 4 wavefronts, in order) are scanned by each wavefront, lane for
+// lane, and three wavefronts sum what is before the tile, one per class.
+// The counting pass reads the ids only where they decide.
 template <bool WRITE>
-__global__ __launch_bounds__(NT) void k_part(PArgs a, u32* tc, const u32* toff, u32 stride) {
-  __shared__ u32 sw[NT / 64];
+__global__ __launch_bounds__(NT) void k_part(PArgs a, Pass ps) {
+  constexpr int NW = NT / 64;
+  static_assert(NW * WE <= 64, "one lane per round and wavefront");
   const u32 t = blockIdx.x;
+  const u32 wv = threadIdx.x >> 6, lane = threadIdx.x & 63u;
   KV p1;
   const u32 n = part_pivot(a, &p1) ? a.n : 0u;  // a failed Select: every element counts as dropped
   const u64 base = (u64)t * TILE;
-  u32 c01 = 0, c2 = 0;
-  u32 run[3] = {0, 0, 0};
-  if constexpr (WRITE) {
-    run[0] = toff[t];
-    run[1] = toff[stride + t];
-    run[2] = toff[2 * stride + t];
-  }
   u64 kk[WE];
-  u32 vv[WE];
 #pragma unroll
   for (int r = 0; r < WE; ++r) {
     const u64 x = base + (u64)r * NT + threadIdx.x;
     kk[r] = x < n ? a.k[x] : 0;
-    vv[r] = x < n ? a.v[x] : 0;
-  }
-#pragma unroll
-  for (int r = 0; r < WE; ++r) {
-    const u64 x = base + (u64)r * NT + threadIdx.x;
-    const u64 k = kk[r];
-    const u32 v = vv[r];
-    const u32 c = x < n ? pclass(a, p1, k, v) : 3u;
-    if constexpr (!WRITE) {
-      c01 += c == 0 ? 1u : (c == 1 ? 1u << 16 : 0u);
-      c2 += c == 2;
-    } else {
-      u32 tot;
-      u32 e = block_scan<NT>(c < 3 ? 1u << (10 * c) : 0u, &tot, sw);
-      if (c < 3) {
-        u32 pos = run[c] + ((e >> (10 * c)) & 1023u);
-        a.ok[c][pos] = k;
-        a.ov[c][pos] = v;
-      }
-      run[0] += tot & 1023u;
-      run[1] += (tot >> 10) & 1023u;
-      run[2] += (tot >> 20) & 1023u;
-    }
   }
   if constexpr (!WRITE) {
+    __shared__ u32 sw[NT / 64];
+    u32 c01 = 0, c2 = 0;
+#pragma unroll
+    for (int r = 0; r < WE; ++r) {
+      const u64 x = base + (u64)r * NT + threadIdx.x;
+      if (x >= n) continue;
+      const u64 k = kk[r];
+      const bool ids = k == p1.k || k == a.p2k || (a.live && k < p1.k);
+      const u32 c = pclass(a, p1, k, ids ? a.v[x] : 0u);
+      c01 += c == 0 ? 1u : (c == 1 ? 1u << 16 : 0u);
+      c2 += c == 2;
+    }
     c01 = block_sum<NT>(c01, sw);
     c2 = block_sum<NT>(c2, sw);
     if (threadIdx.x == 0) {
-      tc[t] = c01 & 0xFFFFu;
-      tc[stride + t] = c01 >> 16;
-      tc[2 * stride + t] = c2;
+      const u32 c0 = c01 & 0xFFFFu, c1 = c01 >> 16;
+      ps.tc[t] = c0;
+      ps.tc[ps.stride + t] = c1;
+      ps.tc[2 * ps.stride + t] = c2;
+      arrive(ps.acc, ps.gs, ps.post, t, gridDim.x,
+             c0 | ((u64)c1 << Field<3>::bits) | ((u64)c2 << (2 * Field<3>::bits)));
+    }
+  } else {
+    __shared__ u32 s01[64], s2[64], s_base[3];
+    u32 vv[WE], cls = 0, rank[WE];  // class, and place within the wavefront's round
+#pragma unroll
+    for (int r = 0; r < WE; ++r) {
+      const u64 x = base + (u64)r * NT + threadIdx.x;
+      vv[r] = x < n ? a.v[x] : 0;
+    }
+    if (wv < 3) {
+      const u32 b = before_tile<3>(ps, wv, t);
+      if (lane == 0) s_base[wv] = b;
+    }
+#pragma unroll
+    for (int r = 0; r < WE; ++r) {
+      const u64 x = base + (u64)r * NT + threadIdx.x;
+      const u32 c = x < n ? pclass(a, p1, kk[r], vv[r]) : 3u;
+      const u64 b0 = __ballot(c == 0), b1 = __ballot(c == 1), b2 = __ballot(c == 2);
+      const u64 b = c == 0 ? b0 : (c == 1 ? b1 : b2);
+      cls |= c << (2 * r);
+      rank[r] = __builtin_amdgcn_mbcnt_hi((u32)(b >> 32), __builtin_amdgcn_mbcnt_lo((u32)b, 0u));
+      if (lane == 0) {
+        s01[r * NW + (int)wv] = (u32)__popcll(b0) | ((u32)__popcll(b1) << 16);
+        s2[r * NW + (int)wv] = (u32)__popcll(b2);
+      }
+    }
+    __syncthreads();
+    const u32 m01 = lane < NW * WE ? s01[lane] : 0u, m2 = lane < NW * WE ? s2[lane] : 0u;
+    const u32 e01 = wave_incl(m01) - m01, e2 = wave_incl(m2) - m2;
+#pragma unroll
+    for (int r = 0; r < WE; ++r) {
+      const int l = r * NW + (int)__builtin_amdgcn_readfirstlane(wv);
+      const u32 f01 = __builtin_amdgcn_readlane(e01, l), f2 = __builtin_amdgcn_readlane(e2, l);
+      const u32 c = (cls >> (2 * r)) & 3u;
+      if (c < 3) {
+        const u32 pos = s_base[c] + rank[r] + (c == 0 ? f01 & 0xFFFFu : (c == 1 ? f01 >> 16 : f2));
+        u64* ok = c == 0 ? a.ok[0] : (c == 1 ? a.ok[1] : a.ok[2]);
+        u32* ov = c == 0 ? a.ov[0] : (c == 1 ? a.ov[1] : a.ov[2]);
+        ok[pos] = kk[r];
+        ov[pos] = vv[r];
+      }
     }
   }
 }
@@ -648,22 +631,6 @@ __device__ __forceinline__ u32 sel_digit(u64 k, u32 v, int p, int w) {
   return (u32)(((k << 32) | v) >> p) & mask;
 }
 
-// Agent-scope atomic loads and stores: coherent across the XCDs' L2 caches
-// within a launch, for words that workgroups of one launch hand to each
-// other (a plain store can stay in one XCD's L2 until the kernel ends).
-__device__ __forceinline__ u32 ld_a32(const u32* p) {
-  return __hip_atomic_load((const u32 PBH_GLB*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ u64 ld_a64(const u64* p) {
-  return __hip_atomic_load((const u64 PBH_GLB*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_a32(u32* p, u32 v) {
-  __hip_atomic_store((u32 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_a64(u64* p, u64 v) {
-  __hip_atomic_store((u64 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Is this workgroup the last of the launch to get here?  Each thread first
 // waits for its own memory operations (its atomics have then been performed),
 // then one counter increment per workgroup; the last one sees gridDim.x - 1
@@ -681,7 +648,7 @@ __device__ __forceinline__ bool last_workgroup(u32* ctr, int* s_last) {
 }
 
 // The starting prefix of a selection of rank r among n elements whose keys
-// lie in [ctl->kmin, ctl->kmax]: the bits the keys share.
+// lie in [mn, mx]: the bits the keys share.
 struct SelState {
   u64 pk;
   u32 pv;
@@ -689,8 +656,7 @@ struct SelState {
   u32 rank, cnt;
   int done;
 };
-__device__ __forceinline__ SelState sel_start(const Ctl* c, u32 r, u32 n) {
-  const u64 mn = c->kmin, mx = c->kmax;
+__device__ __forceinline__ SelState sel_start(u64 mn, u64 mx, u32 r, u32 n) {
   SelState q;
   if (mn == mx) {
     q.nb = 64;
@@ -711,16 +677,24 @@ __device__ __forceinline__ SelState sel_start(const Ctl* c, u32 r, u32 n) {
 // atomic per non-empty bin); the last workgroup to finish reads the total,
 // moves the bin holding the rank into the prefix, writes the new state to ctl
 // and clears the histogram.  The first pass (`first`) derives the starting
-// prefix from the key range in ctl (every workgroup the same); later passes
+// prefix from the key range (every workgroup the same); later passes
 // read the state, and return at once when the selection is done.
-__global__ __launch_bounds__(NT) void k_sel_pass(const u64* K, const u32* V, u32 n, Ctl* c, u32 r, int first) {
+__global__ __launch_bounds__(NT) void k_sel_pass(const u64* K, const u32* V, u32 n, Ctl* c, u32 r, int first,
+                                                 const Range* range, u32 nrange) {
   static_assert(SEL_BINS == NT, "one bin per thread");
   __shared__ u32 h[SEL_BINS];
   __shared__ u32 sw[NT / 64];
   __shared__ int s_last;
   SelState q;
   if (first) {
-    q = sel_start(c, r, n);
+    __shared__ u64 swl[NT / 64], swh[NT / 64];
+    u64 lo = KINF, hi = 0;
+    for (u32 x = threadIdx.x; x < nrange; x += NT) {
+      lo = range[x].lo < lo ? range[x].lo : lo;
+      hi = range[x].hi > hi ? range[x].hi : hi;
+    }
+    block_minmax<NT>(lo, hi, swl, swh);
+    q = sel_start(lo, hi, r, n);
     if (q.done) {  // few enough elements: no pass needed
       if (blockIdx.x == 0 && threadIdx.x == 0) {
         c->spk = q.pk;
@@ -798,22 +772,30 @@ __global__ __launch_bounds__(NT) void k_sel_pass(const u64* K, const u32* V, u32
   st_a32(&c->shist[b], 0u);
 }
 
+// The end of a publication: this thread's stores to the mailbox become
+// visible to the host before the number does.
+__device__ __forceinline__ void publish(Mail* mail, u32 seq) {
+  __threadfence_system();
+  __hip_atomic_store(&mail->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Gathers the elements that match the selected prefix (at most CANDMAX) and,
 // in the last workgroup to finish, ranks them by counting: the one with
 // exactly rank-1 smaller candidates is the answer.  Publishes the outcome to
 // the box (sfail: the passes were not done; sbad: a consistency check failed).
 __global__ __launch_bounds__(NT) void k_sel_collect(const u64* K, const u32* V, u32 n, Ctl* c, u64* ck, u32* cv,
-                                                    Mail* box) {
+                                                    Mail* box, Mail* mail, u32 seq) {
   __shared__ u64 sk[CANDMAX];
   __shared__ u32 sv[CANDMAX];
   __shared__ int s_last;
   const int done = c->sdone;
   if (!done) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-      box->sfail = 1;
-      box->sbad = 0;
-      box->npass = c->npass;
+      box->sfail = mail->sfail = 1;
+      box->sbad = mail->sbad = 0;
+      mail->npass = c->npass;
       c->npass = 0;
+      publish(mail, seq);
     }
     return;
   }
@@ -851,9 +833,9 @@ __global__ __launch_bounds__(NT) void k_sel_collect(const u64* K, const u32* V, 
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    box->sfail = 0;
-    box->sbad = (c->sbad || r == 0 || r > m || nc0 != c->scnt) ? 1 : 0;
-    box->npass = c->npass;
+    box->sfail = mail->sfail = 0;
+    box->sbad = mail->sbad = (c->sbad || r == 0 || r > m || nc0 != c->scnt) ? 1 : 0;
+    mail->npass = c->npass;
     c->npass = 0;
     st_a32(&c->sncand, 0u);
   }
@@ -863,49 +845,13 @@ __global__ __launch_bounds__(NT) void k_sel_collect(const u64* K, const u32* V, 
     u32 below = 0;
     for (u32 y = 0; y < m; ++y) below += sk[y] < k || (sk[y] == k && sv[y] < v);
     if (below + 1 == r) {
-      box->rk = k;
-      box->rv = v;
+      box->rk = mail->rk = k;
+      box->rv = mail->rv = v;
+      __threadfence_system();
     }
   }
-}
-
-__global__ __launch_bounds__(NT) void k_minmax(const u64* K, u32 n, Partials pt) {
-  __shared__ u64 swl[NT / 64], swh[NT / 64];
-  u64 lo = KINF, hi = 0;
-  const u64 step = (u64)gridDim.x * NT;
-  for (u64 x0 = (u64)blockIdx.x * NT + threadIdx.x; x0 < n; x0 += 4 * step) {
-    u64 k[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) k[q] = x0 + q * step < n ? K[x0 + q * step] : KINF;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (x0 + q * step < n) {
-        lo = k[q] < lo ? k[q] : lo;
-        hi = k[q] > hi ? k[q] : hi;
-      }
-  }
-  block_minmax<NT>(lo, hi, swl, swh);
-  if (threadIdx.x == 0) {
-    pt.cnt[blockIdx.x] = 0;
-    pt.lo[blockIdx.x] = lo;
-    pt.hi[blockIdx.x] = hi;
-  }
-}
-
-// ------------------------------------------------------------------ publishing
-
-// Copies a step's results (box, device memory) into the host-mapped mailbox,
-// then writes the sequence number with a system-scope release.  Each lane
-// fences its own word before the barrier, so every word is visible to the
-// host before seq is.
-__global__ __launch_bounds__(64) void k_post(const Mail* box, Mail* mail, u32 seq) {
-  const u32 l = threadIdx.x;
-  if (l + 1 < MAIL_WORDS) {
-    ((u32*)mail)[l] = ((const u32*)box)[l];
-    __threadfence_system();
-  }
   __syncthreads();
-  if (l == 0) __hip_atomic_store(&mail->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (threadIdx.x == 0) publish(mail, seq);
 }
 
 // ------------------------------------------------------------------ intake
@@ -915,7 +861,7 @@ __global__ __launch_bounds__(64) void k_post(const Mail* box, Mail* mail, u32 se
 // same 1, so no atomic is needed: a random atomic costs a round trip to the
 // memory side, a byte store is merged in the L2).
 __global__ __launch_bounds__(NT) void k_intake(const u64* keys, const u32* ids, u64 count, u64* cur, u8* marks,
-                                               Partials pt) {
+                                               u64* acc, u64* post) {
   __shared__ u32 sw[NT / 64];
   u32 newly = 0;
   const u64 step = (u64)gridDim.x * NT;
@@ -938,15 +884,18 @@ __global__ __launch_bounds__(NT) void k_intake(const u64* keys, const u32* ids, 
       }
   }
   newly = block_sum<NT>(newly, sw);
-  if (threadIdx.x == 0) pt.cnt[blockIdx.x] = newly;
+  if (threadIdx.x == 0) arrive(acc, nullptr, post, blockIdx.x, gridDim.x, newly);
 }
 
 // Mark compaction: marked ids in increasing order -> (cur[id], id); the
 // marks are cleared.  Each thread takes 32 consecutive ids (two 16-byte loads)
-// per round, turned into a 32-bit mask; tile t = ids [t*TILE*32, (t+1)*TILE*32)
-// in WE rounds.  In the writing pass each round's marked ids are gathered in
-// LDS in order (a scan of the masks' popcounts places them) and then written
-// out coalesced, one output per thread, with cur[id] read alongside.
+// per round, turned into a 32-bit mask; a tile is BR rounds of NT * 32 ids (8
+// rounds left 16 workgroups for a million ids: counting 6, writing 12 us).
+// In the writing pass each round's marked ids are gathered in LDS in order (a
+// scan of the masks' popcounts places them) and then written out coalesced,
+// one output per thread, with cur[id] read alongside.
+constexpr int BR = 2;
+constexpr u32 BTILE = NT * BR;  // words of 32 ids
 __device__ __forceinline__ u32 mark_mask(uint4 m) {
   const u32 w[4] = {m.x, m.y, m.z, m.w};
   u32 bits = 0;
@@ -957,57 +906,64 @@ __device__ __forceinline__ u32 mark_mask(uint4 m) {
   return bits;
 }
 template <bool WRITE>
-__global__ __launch_bounds__(NT) void k_bits(u8* marks, u32 nwords, u32* tc, const u32* toff, const u64* cur,
-                                             u64* uk, u32* uv) {
+__global__ __launch_bounds__(NT) void k_bits(u8* marks, u32 nwords, const u64* cur, u64* uk, u32* uv, Pass ps) {
+  static_assert(BR == 2, "two counts of 16 bits");
   __shared__ u32 sw[NT / 64];
   __shared__ u32 sid[WRITE ? NT * 32 : 1];
+  __shared__ u32 s_base;
   const u32 t = blockIdx.x;
-  u32 run = WRITE ? toff[t] : 0u, cnt = 0;
   uint4* m4 = (uint4*)marks;
-  u32 bitsr[WE];
+  u32 bitsr[BR], pc = 0;
 #pragma unroll
-  for (int r = 0; r < WE; ++r) {
-    const u64 w = (u64)t * TILE + (u64)r * NT + threadIdx.x;
+  for (int r = 0; r < BR; ++r) {
+    const u64 w = (u64)t * BTILE + (u64)r * NT + threadIdx.x;
     bitsr[r] = w < nwords ? mark_mask(m4[2 * w]) | (mark_mask(m4[2 * w + 1]) << 16) : 0u;
+    pc |= (u32)__builtin_popcount(bitsr[r]) << (16 * r);
   }
+  if constexpr (WRITE) {
+    if (threadIdx.x < 64) {
+      const u32 b = before_tile<1>(ps, 0, t);
+      if (threadIdx.x == 0) s_base = b;
+    }
+  }
+  u32 tot;
+  const u32 ex = block_scan<NT>(pc, &tot, sw);
+  const u32 t0 = tot & 0xFFFFu, t1 = tot >> 16;
+  if constexpr (!WRITE) {
+    if (threadIdx.x == 0) {
+      ps.tc[t] = t0 + t1;
+      arrive(ps.acc, ps.gs, ps.post, t, gridDim.x, t0 + t1);
+    }
+  } else {
 #pragma unroll
-  for (int r = 0; r < WE; ++r) {
-    const u64 w = (u64)t * TILE + (u64)r * NT + threadIdx.x;
-    u32 bits = bitsr[r];
-    const u32 pc = (u32)__builtin_popcount(bits);
-    if constexpr (!WRITE) {
-      cnt += pc;
-    } else {
-      u32 tot;
-      u32 o = block_scan<NT>(pc, &tot, sw);  // its barriers also end the previous round's reads of sid
+    for (int r = 0; r < BR; ++r) {
+      const u64 w = (u64)t * BTILE + (u64)r * NT + threadIdx.x;
+      u32 bits = bitsr[r], o = r ? ex >> 16 : ex & 0xFFFFu;
       if (bits) {
         m4[2 * w] = make_uint4(0u, 0u, 0u, 0u);
         m4[2 * w + 1] = make_uint4(0u, 0u, 0u, 0u);
       }
+      if (r) __syncthreads();  // (the round before read sid)
       while (bits) {
         const u32 b = (u32)__builtin_ctz(bits);
         bits &= bits - 1;
         sid[o++] = (u32)w * 32u + b;
       }
       __syncthreads();
-      for (u32 x = threadIdx.x; x < tot; x += NT) {
+      const u32 run = s_base + (r ? t0 : 0u), len = r ? t1 : t0;
+      for (u32 x = threadIdx.x; x < len; x += NT) {
         const u32 id = sid[x];
         uv[run + x] = id;
         uk[run + x] = cur[id];
       }
-      run += tot;
     }
-  }
-  if constexpr (!WRITE) {
-    cnt = block_sum<NT>(cnt, sw);
-    if (threadIdx.x == 0) tc[t] = cnt;
   }
 }
 
 // Delete of a batch of ids: cur[id] = KINF; each workgroup counts the ids
 // that were present (the exchange returns the old key, so repeats in the
 // batch count once).
-__global__ __launch_bounds__(NT) void k_delete(const u32* ids, u64 count, u64* cur, Partials pt) {
+__global__ __launch_bounds__(NT) void k_delete(const u32* ids, u64 count, u64* cur, u64* acc, u64* post) {
   __shared__ u32 sw[NT / 64];
   u32 gone = 0;
   for (u64 x = (u64)blockIdx.x * NT + threadIdx.x; x < count; x += (u64)gridDim.x * NT)
@@ -1016,7 +972,7 @@ __global__ __launch_bounds__(NT) void k_delete(const u32* ids, u64 count, u64* c
                 ? 1u
                 : 0u;
   gone = block_sum<NT>(gone, sw);
-  if (threadIdx.x == 0) pt.cnt[blockIdx.x] = gone;
+  if (threadIdx.x == 0) arrive(acc, nullptr, post, blockIdx.x, gridDim.x, gone);
 }
 
 __global__ void k_absent(const u32* ids, u64 n, u64* cur) {
@@ -1140,6 +1096,10 @@ __device__ __forceinline__ void run_pair(u32 n, u32 L, u64 s, u32* base, u32* na
   *nb = (u32)(end - mid);
 }
 
+// Split searches per workgroup of the sort's partition kernel (one
+// wavefront each).
+constexpr u32 SPW = NT / 64;
+
 __global__ __launch_bounds__(NT) void k_spart(const u64* K, const u32* V, u32 n, u32 L, u32 ntiles, u32* part) {
   const u32 t = blockIdx.x * SPW + (threadIdx.x >> 6);
   if (t >= ntiles) return;
@@ -1241,12 +1201,21 @@ struct WideScratch {
   u64 marks_n = 0;
   u32* part = nullptr;  // tile split points (maxtiles + 1)
   u32* tc = nullptr;    // tile counts, 3 arrays of maxtiles
-  u32* toff = nullptr;  // tile offsets, 3 arrays of maxtiles
+  u64* gs = nullptr;    // their sums over 64 tiles, packed
+  u64* acc = nullptr;   // arrival words (one per 64 workgroups; a line each)
+  // Posts (host-mapped, a word per 64 workgroups) of a step and of the kernel
+  // before it that counts ids (intake, delete).
+  u64* post_h[2] = {nullptr, nullptr};
+  u64* post_d[2] = {nullptr, nullptr};
+  u32 npost[2] = {0, 0};  // workgroups of the launches that post
+  // Key range of each level's B_i, per 64 tiles of the merge that last wrote
+  // it (what was split off since only narrows it), and how many there are.
+  Range* range[MAXL] = {};
+  u32 nrange[MAXL] = {};
   u64* cand_k = nullptr;
   u32* cand_v = nullptr;
   u64* tmp_k = nullptr;  // sort scratch (4d elements)
   u32* tmp_v = nullptr;
-  Partials pt{nullptr, nullptr, nullptr};  // one slot per tile / workgroup (maxtiles, >= GRID_STRIDE)
   u32 maxtiles = 0;
   hipStream_t s = 0;
   // Profiling (off by default): HIP events around every kernel launch of
@@ -1322,35 +1291,52 @@ int prof_collect(WideScratch* w) {
   return 0;
 }
 
-// Waits until the host sees step `want` published, by polling the mailbox's
-// sequence number (a stream synchronisation would add the runtime's
+// Waits until the host sees results in host-mapped memory, by polling it (a stream synchronisation would add the runtime's
 // completion path and a system-scope cache write-back to every step).
-// Should the number not arrive within a second, the stream is synchronised,
-// which also reports a failed kernel (E_DEVICE); a step whose kernels all
-// ended without the number arriving gives E_TIMEOUT.
-int wait_mail(WideScratch* w, u32 want) {
+// Should they not arrive within a second, the stream is synchronised, which
+// also reports a failed kernel (E_DEVICE); a step whose kernels all ended
+// without them gives E_TIMEOUT.
+template <class Ready>
+int wait_for(WideScratch* w, Ready&& ready) {
   const auto t0 = std::chrono::steady_clock::now();
   for (u32 spin = 1;; ++spin) {
-    if (__atomic_load_n(&w->mail_h->seq, __ATOMIC_ACQUIRE) == want) return 0;
+    if (ready()) return 0;
     if ((spin & 4095u) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::seconds(1)) break;
   }
   WCHK(hipStreamSynchronize(w->s));
-  return __atomic_load_n(&w->mail_h->seq, __ATOMIC_ACQUIRE) == want ? 0 : E_TIMEOUT;
+  return ready() ? 0 : E_TIMEOUT;
+}
+int wait_mail(WideScratch* w, u32 want) {
+  return wait_for(w, [&] { return __atomic_load_n(&w->mail_h->seq, __ATOMIC_ACQUIRE) == want; });
 }
 
-// Ends a step whose kernels do not publish it: k_post publishes the box,
-// then the host waits for it.
-int fetch(WideScratch* w) {
-  const u32 want = ++w->seq;
-  plaunch(w, WK_OTHER, 2ull * sizeof(Mail),
-          [&] { hipLaunchKernelGGL(k_post, dim3(1), dim3(64), 0, w->s, w->box, w->mail_d, want); });
-  if (int rc = launch_ok()) return rc;
-  return wait_mail(w, want);
+// Clears the words in which the nt workgroups of the next launch post their
+// counts, and returns their device address; read_posts waits for them and adds
+// them up, F counts.
+u64* open_posts(WideScratch* w, int which, u32 nt) {
+  w->npost[which] = nt;
+  for (u32 g = 0; g < cdiv(nt, 64); ++g) __atomic_store_n(w->post_h[which] + g, 0ull, __ATOMIC_RELAXED);
+  return w->post_d[which];
+}
+template <int F>
+int read_posts(WideScratch* w, int which, u64* sums) {
+  for (int f = 0; f < F; ++f) sums[f] = 0;
+  for (u32 g = 0; g < cdiv(w->npost[which], 64); ++g) {
+    u64 x = 0;
+    if (int rc = wait_for(w, [&] { return (x = __atomic_load_n(w->post_h[which] + g, __ATOMIC_ACQUIRE)) != 0; }))
+      return rc;
+    for (int f = 0; f < F; ++f) sums[f] += (x >> (f * Field<F>::bits)) & Field<F>::mask;
+  }
+  return 0;
+}
+Pass next_pass(WideScratch* w, u32 nt) {
+  return Pass{w->tc, w->maxtiles, w->gs, w->acc, open_posts(w, 0, nt)};
 }
 
-// C = DeleteDuplicates(Merge(A, B)) by id; *num_le = outputs <= piv.
-int wmerge(WideScratch* w, Arr A, u32 na, Arr B, u32 nb, Arr C, const u64* cur, int prefer, bool filterB, KV piv,
-           u32* m, u32* num_le, bool stats = true) {
+// C = DeleteDuplicates(Merge(A, B)) by id; *num_le = outputs <= piv.  // With count_le the
+// counting pass reads the keys too; level >= 0: the outputs become its B.
+int wmerge(WideScratch* w, Arr A, u32 na, Arr B, u32 nb, Arr C, const u64* cur, int prefer, int level, bool count_le,
+           KV piv, u32* m, u32* num_le) {
   const u64 total = (u64)na + nb;
   if (total == 0) {
     *m = 0;
@@ -1359,34 +1345,23 @@ int wmerge(WideScratch* w, Arr A, u32 na, Arr B, u32 nb, Arr C, const u64* cur, 
   }
   const u32 nt = cdiv(total, TILE);
   if (nt > w->maxtiles) return E_INTERNAL;
-  MArgs a{A.k, A.v, na, B.k, B.v, nb, C.k, C.v, cur, prefer, filterB ? 1 : 0, piv.k, piv.v};
-  // With stats the counting pass also stages the keys and counts the outputs
-  // <= piv and their key range; the scan folds those and publishes the step,
-  // so the host goes on while the writing pass runs.
-  if (stats)
-    plaunch(w, WK_MERGE_COUNT, 12ull * total, [&] {
-      hipLaunchKernelGGL((k_merge<false, true>), dim3(nt), dim3(NT), 0, w->s, a, (const u32*)nullptr, w->part, w->tc,
-                         (const u32*)nullptr, w->pt);
-    });
-  else
-    plaunch(w, WK_MERGE_COUNT, 4ull * total, [&] {
-      hipLaunchKernelGGL((k_merge<false, false>), dim3(nt), dim3(NT), 0, w->s, a, (const u32*)nullptr, w->part,
-                         w->tc, (const u32*)nullptr, w->pt);
-    });
-  const u32 want = ++w->seq;
-  plaunch(w, WK_OTHER, (stats ? 28ull : 8ull) * nt, [&] {
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, w->s, w->tc, nt, 0u, w->toff, &w->box->total, w->ctl,
-                       Pub{w->box, w->mail_d, want}, stats ? w->pt : Partials{nullptr, nullptr, nullptr},
-                       &w->box->num_le);
+  const MArgs a{A.k, A.v, na, B.k, B.v, nb, C.k, C.v, cur, prefer, level >= 0 ? w->range[level] : nullptr, piv.k, piv.v};
+  if (level >= 0) w->nrange[level] = cdiv(nt, 64);
+  const Pass ps = next_pass(w, nt);
+  plaunch(w, WK_MERGE_COUNT, (count_le ? 12ull : 4ull) * total, [&] {
+    if (count_le)
+      hipLaunchKernelGGL((k_merge<false, true>), dim3(nt), dim3(NT), 0, w->s, a, w->part, ps);
+    else
+      hipLaunchKernelGGL((k_merge<false, false>), dim3(nt), dim3(NT), 0, w->s, a, w->part, ps);
   });
   const int iw = plaunch(w, WK_MERGE_WRITE, 12ull * total, [&] {
-    hipLaunchKernelGGL((k_merge<true, true>), dim3(nt), dim3(NT), 0, w->s, a, (const u32*)w->part, (u32*)nullptr,
-                       (u32*)nullptr, (const u32*)w->toff, w->pt);
+    hipLaunchKernelGGL((k_merge<true, true>), dim3(nt), dim3(NT), 0, w->s, a, w->part, ps);
   });
   if (int rc = launch_ok()) return rc;
-  if (int rc = wait_mail(w, want)) return rc;
-  *m = w->mail_h->total;
-  *num_le = stats ? w->mail_h->num_le : 0u;
+  u64 sums[2];
+  if (int rc = read_posts<2>(w, 0, sums)) return rc;
+  *m = (u32)sums[0];
+  *num_le = (u32)sums[1];
   patch_bytes(w, iw, 12ull * (total + *m));  // 12 B per input read + 12 B per output written
   return 0;
 }
@@ -1394,20 +1369,12 @@ int wmerge(WideScratch* w, Arr A, u32 na, Arr B, u32 nb, Arr C, const u64* cur, 
 // Select(A, r) (rank r, 1-based) followed by the three-way split of A at
 // (min(Select(A, r), cap), p2) into O0 / O1 / O2, as one host step: the
 // split reads the selected element on the device.  *p1 = the split's first
-// pivot.  The key range of A must be in ctl (from the merge that wrote A)
-// unless have_range is false.
+// pivot.  A's keys lie in the range of level `level`.
 int wpartition3_sel(WideScratch* w, Arr A, u32 n, KV p1, KV p2, Arr O0, Arr O1, Arr O2, const u64* live, u32* n0,
                     u32* n1, u32* n2, const Mail* sel);
-int wselpart(WideScratch* w, Arr A, u32 n, u32 r, bool have_range, KV cap, KV p2, Arr O0, Arr O1, Arr O2,
+int wselpart(WideScratch* w, Arr A, u32 n, u32 r, int level, KV cap, KV p2, Arr O0, Arr O1, Arr O2,
              const u64* live, KV* p1, u32* n0, u32* n1, u32* n2) {
   if (n == 0 || r == 0 || r > n) return E_INTERNAL;
-  if (!have_range) {
-    const u32 gm = grid_for(n);
-    plaunch(w, WK_OTHER, 8ull * n, [&] { hipLaunchKernelGGL(k_minmax, dim3(gm), dim3(NT), 0, w->s, A.k, n, w->pt); });
-    plaunch(w, WK_OTHER, 20ull * gm, [&] {
-      hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, w->s, w->pt, gm, (u32*)nullptr, (u64*)nullptr, w->ctl);
-    });
-  }
   const u32 g = grid_for(n), gh = std::min<u32>(g, GRID_HIST);
   // Each pass fixes 8 more of the 96 bits, so 12 passes (4 rounds of 3)
   // always finish; two or three typically do (three when the keys crowd at
@@ -1418,13 +1385,15 @@ int wselpart(WideScratch* w, Arr A, u32 n, u32 r, bool have_range, KV cap, KV p2
     for (int p = 0; p < 3; ++p)
       ip[p] = plaunch(w, WK_SEL_PASS, 8ull * n, [&] {
         hipLaunchKernelGGL(k_sel_pass, dim3(gh), dim3(NT), 0, w->s, A.k, A.v, n, w->ctl, r,
-                           round == 0 && p == 0 ? 1 : 0);
+                           round == 0 && p == 0 ? 1 : 0, w->range[level], w->nrange[level]);
       });
+    const u32 want = ++w->seq;
     const int ic = plaunch(w, WK_SEL_GATHER, 8ull * n, [&] {
       hipLaunchKernelGGL(k_sel_collect, dim3(gh), dim3(NT), 0, w->s, A.k, A.v, n, w->ctl, w->cand_k, w->cand_v,
-                         w->box);
+                         w->box, w->mail_d, want);
     });
     if (int rc = wpartition3_sel(w, A, n, cap, p2, O0, O1, O2, live, n0, n1, n2, w->box)) return rc;
+    if (int rc = wait_mail(w, want)) return rc;
     // passes after the last needed one, and a gather before the passes were
     // done, returned at once: they read nothing
     for (int p = (int)w->mail_h->npass; p < 3; ++p) patch_kind(w, ip[p], WK_IDLE), patch_bytes(w, ip[p], 0);
@@ -1448,24 +1417,16 @@ int wpartition3_sel(WideScratch* w, Arr A, u32 n, KV p1, KV p2, Arr O0, Arr O1, 
   }
   const u32 nt = cdiv(n, TILE);
   if (nt > w->maxtiles) return E_INTERNAL;
-  PArgs a{A.k, A.v, n, p1.k, p1.v, p2.k, p2.v, live, {O0.k, O1.k, O2.k}, {O0.v, O1.v, O2.v}, sel};
-  plaunch(w, WK_SPLIT_COUNT, 12ull * n, [&] {
-    hipLaunchKernelGGL(k_part<false>, dim3(nt), dim3(NT), 0, w->s, a, w->tc, (const u32*)nullptr, w->maxtiles);
-  });
-  // published by the scan: the sizes are known before the writing pass
-  const u32 want = ++w->seq;
-  plaunch(w, WK_OTHER, 24ull * nt, [&] {
-    hipLaunchKernelGGL(k_scan, dim3(3), dim3(1024), 0, w->s, w->tc, nt, w->maxtiles, w->toff, w->box->part, w->ctl,
-                       Pub{w->box, w->mail_d, want}, Partials{nullptr, nullptr, nullptr}, (u32*)nullptr);
-  });
-  plaunch(w, WK_SPLIT_WRITE, 24ull * n, [&] {
-    hipLaunchKernelGGL(k_part<true>, dim3(nt), dim3(NT), 0, w->s, a, (u32*)nullptr, w->toff, w->maxtiles);
-  });
+  const PArgs a{A.k, A.v, n, p1.k, p1.v, p2.k, p2.v, live, {O0.k, O1.k, O2.k}, {O0.v, O1.v, O2.v}, sel};
+  const Pass ps = next_pass(w, nt);
+  plaunch(w, WK_SPLIT_COUNT, 8ull * n, [&] { hipLaunchKernelGGL(k_part<false>, dim3(nt), dim3(NT), 0, w->s, a, ps); });
+  plaunch(w, WK_SPLIT_WRITE, 24ull * n, [&] { hipLaunchKernelGGL(k_part<true>, dim3(nt), dim3(NT), 0, w->s, a, ps); });
   if (int rc = launch_ok()) return rc;
-  if (int rc = wait_mail(w, want)) return rc;
-  *n0 = w->mail_h->part[0];
-  *n1 = w->mail_h->part[1];
-  *n2 = w->mail_h->part[2];
+  u64 sums[3];
+  if (int rc = read_posts<3>(w, 0, sums)) return rc;
+  *n0 = (u32)sums[0];
+  *n1 = (u32)sums[1];
+  *n2 = (u32)sums[2];
   return 0;
 }
 
@@ -1517,7 +1478,8 @@ int wresolve(WideScratch* w, const Geom& g, HeapState* st, const u64* cur, int i
     if ((u64)a.nS + a.nB > capB(g.d, i)) return E_INTERNAL;
     u32 m, num;
     // S_0 holds the latest updates, so at level 0 its copy of an id is the live one.
-    if ((rc = wmerge(w, S, a.nS, B, a.nB, M, cur, i == 0 ? PREFER_A : PREFER_LIVE, false, pi, &m, &num))) return rc;
+    if ((rc = wmerge(w, S, a.nS, B, a.nB, M, cur, i == 0 ? PREFER_A : PREFER_LIVE, i, true, pi, &m, &num)))
+      return rc;
     touched += 2ull * (a.nS + a.nB) + m;
     a.bsel ^= 1;
     a.nS = 0;
@@ -1526,10 +1488,13 @@ int wresolve(WideScratch* w, const Geom& g, HeapState* st, const u64* cur, int i
     if (sel) num = cB;
     if (num < m) {
       if (!nx) return E_CAPACITY;
-      Arr Lo = lbuf(g, i, a.bsel ^ 1), Hi = lbuf(g, i, 2);
+      // (an empty S_{i+1} takes the upper part as it is)
+      Arr Sn = lbuf(g, i + 1, 3 + b.ssel), Sn2 = lbuf(g, i + 1, 3 + (b.ssel ^ 1));
+      Arr Lo = lbuf(g, i, a.bsel ^ 1), Hi = b.nS ? lbuf(g, i, 2) : Sn2;
+      if (b.nS == 0 && m - std::min(num, m) > capS(g.d, i + 1)) return E_INTERNAL;
       u32 n0, n1, n2;
       if (sel) {  // p_i <- Select(B_i, 2d*4^i), and the split at it
-        if ((rc = wselpart(w, M, m, cB, true, kv_inf(), kv_inf(), Lo, Hi, Hi, nullptr, &pi, &n0, &n1, &n2))) return rc;
+        if ((rc = wselpart(w, M, m, cB, i, kv_inf(), kv_inf(), Lo, Hi, Hi, nullptr, &pi, &n0, &n1, &n2))) return rc;
         touched += m;
       } else if ((rc = wpartition3(w, M, m, pi, kv_inf(), Lo, Hi, Hi, nullptr, &n0, &n1, &n2))) {
         return rc;
@@ -1538,9 +1503,9 @@ int wresolve(WideScratch* w, const Geom& g, HeapState* st, const u64* cur, int i
       a.bsel ^= 1;
       a.nB = n0;
       if ((u64)b.nS + n1 > capS(g.d, i + 1)) return E_INTERNAL;
-      Arr Sn = lbuf(g, i + 1, 3 + b.ssel), Sn2 = lbuf(g, i + 1, 3 + (b.ssel ^ 1));
-      u32 ms, dummy;
-      if ((rc = wmerge(w, Sn, b.nS, Hi, n1, Sn2, cur, PREFER_LIVE, false, kv_inf(), &ms, &dummy, false))) return rc;
+      u32 ms = n1, dummy;
+      if (b.nS && (rc = wmerge(w, Sn, b.nS, Hi, n1, Sn2, cur, PREFER_LIVE, -1, false, kv_inf(), &ms, &dummy)))
+        return rc;
       touched += 2ull * (b.nS + n1) + ms;
       b.ssel ^= 1;
       b.nS = ms;
@@ -1550,25 +1515,30 @@ int wresolve(WideScratch* w, const Geom& g, HeapState* st, const u64* cur, int i
     }
   }
   if (a.nB < cB && i < ell && nx) {
-    Arr Bn = lbuf(g, i + 1, b.bsel), Sn = lbuf(g, i + 1, 3 + b.ssel), M2 = lbuf(g, i + 1, b.bsel ^ 1);
     if ((u64)b.nB + b.nS > capB(g.d, i + 1)) return E_INTERNAL;
-    u32 m2, dummy;
-    if ((rc = wmerge(w, Bn, b.nB, Sn, b.nS, M2, cur, PREFER_LIVE, false, kv_inf(), &m2, &dummy))) return rc;
+    u32 m2 = b.nB, dummy;
+    if (b.nS) {  // (an empty one leaves B_{i+1} as it is)
+      Arr Bn = lbuf(g, i + 1, b.bsel), Sn = lbuf(g, i + 1, 3 + b.ssel);
+      if ((rc = wmerge(w, Bn, b.nB, Sn, b.nS, lbuf(g, i + 1, b.bsel ^ 1), cur, PREFER_LIVE, i + 1, false, kv_inf(),
+                       &m2, &dummy)))
+        return rc;
+      b.bsel ^= 1;
+    }
     touched += 2ull * (b.nB + b.nS) + m2;
     b.nS = 0;
     b.ssel = 0;
-    b.bsel ^= 1;
     b.nB = m2;
     if (m2 > 0) {
       const u32 r = cB - a.nB;
-      Arr Up = lbuf(g, i, 2), Bk = lbuf(g, i + 1, b.bsel ^ 1), Sk = lbuf(g, i + 1, 3);
+      Arr M2 = lbuf(g, i + 1, b.bsel), Bk = lbuf(g, i + 1, b.bsel ^ 1), Sk = lbuf(g, i + 1, 3);
+      Arr Up = lbuf(g, i, 2);
       u32 nu, nb1, ns1;
       // p_i <- min(Select(B_{i+1}, r), p_{i+1}), and the split at (p_i,
       // p_{i+1}); elements moving up into B_0 are checked for liveness here,
       // all at once.
       KV pnew = pn;
       if (r < m2) {
-        if ((rc = wselpart(w, M2, m2, r, true, pn, pn, Up, Bk, Sk, i == 0 ? cur : nullptr, &pnew, &nu, &nb1, &ns1)))
+        if ((rc = wselpart(w, M2, m2, r, i + 1, pn, pn, Up, Bk, Sk, i == 0 ? cur : nullptr, &pnew, &nu, &nb1, &ns1)))
           return rc;
         touched += m2;
       } else if ((rc = wpartition3(w, M2, m2, pnew, pn, Up, Bk, Sk, i == 0 ? cur : nullptr, &nu, &nb1, &ns1))) {
@@ -1581,8 +1551,8 @@ int wresolve(WideScratch* w, const Geom& g, HeapState* st, const u64* cur, int i
       b.ssel = 0;
       Arr Bi = lbuf(g, i, a.bsel), Bi2 = lbuf(g, i, a.bsel ^ 1);
       u32 mb;
-      if ((rc = wmerge(w, Bi, a.nB, Up, nu, Bi2, cur, i == 0 ? PREFER_B : PREFER_LIVE, false, kv_inf(), &mb,
-                       &dummy, false)))
+      if ((rc = wmerge(w, Bi, a.nB, Up, nu, Bi2, cur, i == 0 ? PREFER_B : PREFER_LIVE, i, false, kv_inf(), &mb,
+                       &dummy)))
         return rc;
       touched += 2ull * (a.nB + nu) + mb;
       a.bsel ^= 1;
@@ -1624,19 +1594,33 @@ int wide_reserve(WideScratch* w, u64 elems) {
   if (need <= w->maxtiles) return 0;
   if (w->part) (void)hipFree(w->part);
   if (w->tc) (void)hipFree(w->tc);
-  if (w->toff) (void)hipFree(w->toff);
-  if (w->pt.cnt) (void)hipFree(w->pt.cnt);
-  if (w->pt.lo) (void)hipFree(w->pt.lo);
-  if (w->pt.hi) (void)hipFree(w->pt.hi);
-  w->part = w->tc = w->toff = nullptr;
-  w->pt = Partials{nullptr, nullptr, nullptr};
+  if (w->gs) (void)hipFree(w->gs);
+  if (w->acc) (void)hipFree(w->acc);
+  w->part = w->tc = nullptr;
+  w->gs = w->acc = nullptr;
   w->maxtiles = 0;
+  const u64 ng = need / 64 + 1;
   WCHK(hipMalloc(&w->part, (need + 1) * sizeof(u32)));
   WCHK(hipMalloc(&w->tc, 3 * need * sizeof(u32)));
-  WCHK(hipMalloc(&w->toff, 3 * need * sizeof(u32)));
-  WCHK(hipMalloc(&w->pt.cnt, need * sizeof(u32)));
-  WCHK(hipMalloc(&w->pt.lo, need * sizeof(u64)));
-  WCHK(hipMalloc(&w->pt.hi, need * sizeof(u64)));
+  WCHK(hipMalloc(&w->gs, ng * sizeof(u64)));
+  WCHK(hipMalloc(&w->acc, LINE * ng * sizeof(u64)));
+  WCHK(hipMemset(w->acc, 0, LINE * ng * sizeof(u64)));
+  for (int r = 0; r < 2; ++r) {
+    if (w->post_h[r]) (void)hipHostFree(w->post_h[r]);
+    w->post_h[r] = nullptr;
+    WCHK(hipHostMalloc(&w->post_h[r], ng * sizeof(u64), hipHostMallocMapped | hipHostMallocCoherent));
+    WCHK(hipHostGetDevicePointer((void**)&w->post_d[r], w->post_h[r], 0));
+  }
+  // the levels' ranges in one array; they outlive the growth of the heap
+  Range* p = nullptr;
+  WCHK(hipMalloc(&p, MAXL * ng * sizeof(Range)));
+  Range* old = w->range[0];
+  for (int i = 0; i < MAXL; ++i) {
+    if (w->nrange[i])
+      WCHK(hipMemcpy(p + i * ng, w->range[i], w->nrange[i] * sizeof(Range), hipMemcpyDeviceToDevice));
+    w->range[i] = p + i * ng;
+  }
+  if (old) (void)hipFree(old);
   w->maxtiles = (u32)need;
   return 0;
 }
@@ -1691,10 +1675,11 @@ void wide_destroy(WideScratch* w) {
   if (w->mail_h) (void)hipHostFree(w->mail_h);
   if (w->part) (void)hipFree(w->part);
   if (w->tc) (void)hipFree(w->tc);
-  if (w->toff) (void)hipFree(w->toff);
-  if (w->pt.cnt) (void)hipFree(w->pt.cnt);
-  if (w->pt.lo) (void)hipFree(w->pt.lo);
-  if (w->pt.hi) (void)hipFree(w->pt.hi);
+  if (w->gs) (void)hipFree(w->gs);
+  if (w->acc) (void)hipFree(w->acc);
+  if (w->range[0]) (void)hipFree(w->range[0]);  // (all levels')
+  for (u64* p : w->post_h)
+    if (p) (void)hipHostFree(p);
   if (w->cand_k) (void)hipFree(w->cand_k);
   if (w->cand_v) (void)hipFree(w->cand_v);
   if (w->tmp_k) (void)hipFree(w->tmp_k);
@@ -1714,7 +1699,9 @@ int wide_bulk_update(WideScratch* w, WideHeap* h, const u64* keys, const u32* id
   const bool direct = count <= h->g.d;
   if (direct)
     if (int rc = grow_if_needed(w, h)) return rc;
-  if (int rc = wide_reserve(w, capB(h->g.d, h->g.q - 1))) return rc;
+  // (room for the tiles of the largest level and of the mark compaction)
+  const u64 bits = (u64)h->nwords * TILE / BTILE;
+  if (int rc = wide_reserve(w, std::max(capB(h->g.d, h->g.q - 1), bits))) return rc;
   if (w->marks_n < 32ull * h->nwords) {
     if (w->marks) (void)hipFree(w->marks);
     w->marks = nullptr;
@@ -1725,39 +1712,30 @@ int wide_bulk_update(WideScratch* w, WideHeap* h, const u64* keys, const u32* id
   }
   const u32 gi = grid_for(count);
   // per pair: the pair (12 B) and the atomicMin on its current key (8 B)
+  u64* posts = open_posts(w, 1, gi);
   plaunch(w, WK_INTAKE, 20ull * count, [&] {
-    hipLaunchKernelGGL(k_intake, dim3(gi), dim3(NT), 0, w->s, keys, ids, count, h->cur, w->marks, w->pt);
+    hipLaunchKernelGGL(k_intake, dim3(gi), dim3(NT), 0, w->s, keys, ids, count, h->cur, w->marks, w->acc, posts);
   });
-  plaunch(w, WK_OTHER, 4ull * gi, [&] {
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, w->s, Partials{w->pt.cnt, nullptr, nullptr}, gi,
-                       (u32*)nullptr, &w->box->newly, w->ctl);
-  });
-  const u32 nt = cdiv(h->nwords, TILE);
+  const u32 nt = cdiv(h->nwords, BTILE);
   if (nt > w->maxtiles) return E_INTERNAL;
   const Arr S0 = lbuf(h->g, 0, 3);
   u64* uk = direct ? S0.k : h->ukeys;
   u32* uv = direct ? S0.v : h->uids;
   const u64 nmark = 32ull * h->nwords;  // one mark byte per id
+  const Pass ps = next_pass(w, nt);
   plaunch(w, WK_BITS_COUNT, nmark, [&] {
-    hipLaunchKernelGGL(k_bits<false>, dim3(nt), dim3(NT), 0, w->s, w->marks, h->nwords, w->tc, (const u32*)nullptr,
-                       (const u64*)h->cur, uk, uv);
-  });
-  // published by the scan: the count of U is known before the compaction
-  const u32 want = ++w->seq;
-  plaunch(w, WK_OTHER, 8ull * nt, [&] {
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, w->s, w->tc, nt, 0u, w->toff, &w->box->total, w->ctl,
-                       Pub{w->box, w->mail_d, want}, Partials{nullptr, nullptr, nullptr}, (u32*)nullptr);
+    hipLaunchKernelGGL(k_bits<false>, dim3(nt), dim3(NT), 0, w->s, w->marks, h->nwords, (const u64*)h->cur, uk, uv, ps);
   });
   const int ib = plaunch(w, WK_BITS_WRITE, nmark, [&] {
-    hipLaunchKernelGGL(k_bits<true>, dim3(nt), dim3(NT), 0, w->s, w->marks, h->nwords, (u32*)nullptr, w->toff,
-                       (const u64*)h->cur, uk, uv);
+    hipLaunchKernelGGL(k_bits<true>, dim3(nt), dim3(NT), 0, w->s, w->marks, h->nwords, (const u64*)h->cur, uk, uv, ps);
   });
   if (int rc = launch_ok()) return rc;
-  if (int rc = wait_mail(w, want)) return rc;
-  const u64 nu = w->mail_h->total;
+  u64 newly, nu;
+  if (int rc = read_posts<1>(w, 1, &newly)) return rc;
+  if (int rc = read_posts<1>(w, 0, &nu)) return rc;
   // marks read, plus per output its current key read (8 B) and the pair written (12 B)
   patch_bytes(w, ib, nmark + 20ull * nu);
-  st->live += w->mail_h->newly;
+  st->live += newly;
   for (u64 c0 = 0; c0 < nu;) {
     if (!direct)
       if (int rc = grow_if_needed(w, h)) return rc;
@@ -1787,12 +1765,9 @@ int wide_delete(WideScratch* w, WideHeap* h, const u32* ids, u64 count) {
   if (count == 0) return 0;
   if (int rc = wide_reserve(w, capB(h->g.d, h->g.q - 1))) return rc;
   const u32 gi = grid_for(count);
+  u64* posts = open_posts(w, 1, gi);
   plaunch(w, WK_ABSENT, 12ull * count,
-          [&] { hipLaunchKernelGGL(k_delete, dim3(gi), dim3(NT), 0, w->s, ids, count, h->cur, w->pt); });
-  plaunch(w, WK_OTHER, 4ull * gi, [&] {
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, w->s, Partials{w->pt.cnt, nullptr, nullptr}, gi,
-                       (u32*)nullptr, &w->box->newly, w->ctl);
-  });
+          [&] { hipLaunchKernelGGL(k_delete, dim3(gi), dim3(NT), 0, w->s, ids, count, h->cur, w->acc, posts); });
   if (int rc = launch_ok()) return rc;
   const Lvl a0 = st->L[0];
   if (a0.nB) {
@@ -1802,10 +1777,10 @@ int wide_delete(WideScratch* w, WideHeap* h, const u32* ids, u64 count) {
     st->L[0].bsel ^= 1;
     st->L[0].nB = n0;
     st->elems += (u64)a0.nB + n0;
-  } else if (int rc = fetch(w)) {
-    return rc;
   }
-  st->live -= w->mail_h->newly;
+  u64 gone;
+  if (int rc = read_posts<1>(w, 1, &gone)) return rc;
+  st->live -= gone;
   fix_ell(st, h->g.q);
   if (int rc = grow_if_needed(w, h)) return rc;
   wdrive(w, h, DRIVE_AFTER);
@@ -1840,7 +1815,7 @@ int wide_extract_min(WideScratch* w, WideHeap* h, u64 k, u64* okeys, u32* oids, 
     KV thr = kv_inf();
     u32 n0, n1, n2;
     if (take < a0.nB) {
-      if (int rc = wselpart(w, B, a0.nB, take, false, kv_inf(), kv_inf(), X, lbuf(h->g, 0, a0.bsel ^ 1), X, nullptr,
+      if (int rc = wselpart(w, B, a0.nB, take, 0, kv_inf(), kv_inf(), X, lbuf(h->g, 0, a0.bsel ^ 1), X, nullptr,
                             &thr, &n0, &n1, &n2))
         return rc;
     } else if (int rc = wpartition3(w, B, a0.nB, thr, kv_inf(), X, lbuf(h->g, 0, a0.bsel ^ 1), X, nullptr, &n0, &n1,
