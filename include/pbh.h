@@ -145,11 +145,11 @@ int pbh_merge_profile(pbh_t *h, uint64_t *launches, uint64_t *bytes, double *ms)
  * engine).  kind < the number of kinds; pbh_kernel_name(kind) names it
  * (NULL past the last kind).  Algorithmic bytes per launch: merge writing
  * pass 12 per input + 12 per output element; merge counting pass 4 per input
- * (ids); Select pass and gather 12 per element (passes that return at once
- * are a kind of their own with 0 bytes); split counting 12 and writing 24 per
- * element; intake 20 per pair; mark compaction 1 per id (+ 20 per output in
- * the writing pass); extract sort 24 per element per pass; absent marking 12
- * per id.  Errors: PBH_EINVAL (NULL argument, kind out of range).
+ * (ids; 12 where it counts against a pivot); Select pass and gather 8 per
+ * element (passes that return at once are a kind of their own with 0 bytes);
+ * split counting 8 and writing 24 per element; intake 20 per pair; mark
+ * compaction 1 per id (+ 20 per output in the writing pass); extract sort 24
+ * per element per pass; deletion 12 per id.  Errors: PBH_EINVAL (NULL argument, kind out of range).
  */
 int pbh_kernel_profile(pbh_t *h, uint32_t kind, uint64_t *launches, uint64_t *bytes, double *ms);
 const char *pbh_kernel_name(uint32_t kind);

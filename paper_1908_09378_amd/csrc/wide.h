@@ -48,7 +48,8 @@ int wide_delete(WideScratch* w, WideHeap* h, const u32* ids, u64 count);
 // ascending by (key, id); *count_out = number written.
 int wide_extract_min(WideScratch* w, WideHeap* h, u64 k, u64* okeys, u32* oids, u64* count_out);
 
-// Kernel kinds of the engine, for profiling.
+// Kernel kinds of the engine, for profiling.  (No launch is of kind WK_OTHER
+// any more; the kinds keep their numbers.)
 enum {
   WK_MERGE_WRITE, WK_MERGE_COUNT, WK_SEL_PASS, WK_SEL_GATHER, WK_SPLIT_COUNT, WK_SPLIT_WRITE, WK_INTAKE,
   WK_BITS_COUNT, WK_BITS_WRITE, WK_SORT_TILE, WK_SORT_MERGE, WK_ABSENT, WK_OTHER, WK_IDLE, WK_COUNT

@@ -15,19 +15,20 @@
 //   time; a writing pass's workgroup sums what is before its tile itself.
 //   k_sel_pass / k_sel_collect
 //       Select: radix selection on the 96-bit (key, id) value, 8 bits per
-//       pass from the first bit where the keys differ, until at most 256
-//       candidates remain; those are gathered and ranked.  The last
-//       workgroup of a pass makes its pick, the last one of the gather ranks
-//       the candidates; the split that follows reads the result on the
-//       device, so Select and split are one host step.
+//       pass from the first bit where the keys differ, until a few thousand
+//       candidates remain; those are gathered, and the last workgroup of the
+//       gather finishes among them.  The split that follows reads the result
+//       on the device, so Select and split are one host step.
 //   k_intake / k_bits<false> / k_bits<true>
 //       BulkUpdate intake: atomicMin on the current keys, a mark byte per id
 //       whose key dropped, and their compaction into U sorted by id.
-//   k_tsort / k_spart / k_smerge
-//       Sorting the extracted minima by (key, id): tiles sorted in registers
-//       and LDS (per-thread sort, then merge-path rounds), then merge passes.
-//   k_absent, k_delete
-//       Mark extracted or deleted ids absent.
+//   k_rank, k_tsort / k_smerge
+//       Sorting the extracted minima by (key, id): a few thousand by each
+//       one's rank among all; more by tiles sorted in registers and LDS
+//       (per-thread sort, then merge-path rounds), then merge passes.  The
+//       kernel that writes them out also marks their ids absent.
+//   k_delete
+//       Marks deleted ids absent.
 // The few results the host needs after a step are written into host-mapped
 // memory as soon as they are known; the host goes on while the step's writing
 // pass runs.
@@ -50,27 +51,30 @@ constexpr int NT = 256;
 constexpr int WE = 8;
 constexpr u32 TILE = NT * WE;  // 2048
 constexpr int SEL_BITS = 8;
-constexpr int SEL_BINS = 1 << SEL_BITS;  // one bin per thread of the pick kernel
-constexpr u32 CANDMAX = NT;              // candidates ranked by one workgroup
+constexpr int SEL_BINS = 1 << SEL_BITS;
 constexpr int GRID_STRIDE = 2048;        // workgroups of the grid-stride kernels
-constexpr int GRID_HIST = 512;           // workgroups of a Select pass or gather (each flushes <= 256
-                                         // atomics, and one on the shared pass counter: about 10 ns
-                                         // each on one address, 2048 workgroups measured 20 us)
+constexpr int ST = 1024;                 // threads of the Select kernels
+constexpr int GRID_SEL = 256;            // their workgroups: one per compute unit (each flushes its
+                                         // histogram by atomics, about 10 ns a cache line)
+constexpr u32 CANDMAX = 8192;            // candidates, finished in LDS (32,768 read from memory by the
+                                         // last workgroup: 50 us more; another pass is at most 18)
+constexpr u32 RANKED = 256;              // the last candidates, ranked by counting
 
 // Device-side state of a selection (read and written by the Select kernels).
+struct SelState {
+  u64 pk;   // prefix: the leading nb bits of (key, id) fixed so far
+  u32 pv;
+  int nb;
+  u32 rank; // rank still sought among the elements with that prefix
+  u32 cnt;  // elements with that prefix
+  int done; // few enough candidates: gather them
+  int bad;  // no bin held the rank (never expected)
+};
 struct Ctl {
-  u64 spk;
-  u32 spv;
-  int snb;      // leading bits of (key, id) fixed so far
-  u32 srank;    // rank still sought among the elements with that prefix
-  u32 scnt;     // elements with that prefix
-  int sdone;    // few enough candidates: gather them
-  int sfail;    // the gather ran before the passes were done
-  int sbad;     // no bin held the rank (never expected)
+  SelState q;    // before the passes now running
   u32 sncand;
-  u32 passdone;  // workgroups finished with the current pass (the last one picks)
-  u32 npass;     // passes that did work since the last gather (profiling)
-  u32 shist[SEL_BINS];
+  u32 collected; // workgroups finished with the gather (the last one goes on)
+  alignas(128) u32 shist[2][SEL_BINS];  // of the two passes
 };
 
 // What the host reads of a selection.  The Select kernels write it in device
@@ -647,129 +651,135 @@ __device__ __forceinline__ bool last_workgroup(u32* ctr, int* s_last) {
   return *s_last != 0;
 }
 
-// The starting prefix of a selection of rank r among n elements whose keys
-// lie in [mn, mx]: the bits the keys share.
-struct SelState {
-  u64 pk;
-  u32 pv;
-  int nb;
-  u32 rank, cnt;
-  int done;
-};
-__device__ __forceinline__ SelState sel_start(u64 mn, u64 mx, u32 r, u32 n) {
+// The workgroup-wide scratch of the Select kernels.
+struct SelShared {
+  u32 sw[ST / 64];
+  u64 swl[ST / 64], swh[ST / 64];
   SelState q;
-  if (mn == mx) {
+};
+
+// The start of a selection of rank r among n elements whose keys lie in the
+// given ranges: the bits the keys share are the prefix.  By the whole
+// workgroup, as sel_pick.
+__device__ __forceinline__ SelState sel_start(const Range* range, u32 nrange, u32 r, u32 n, SelShared& sh) {
+  u64 lo = KINF, hi = 0;
+  for (u32 x = threadIdx.x; x < nrange; x += ST) {
+    lo = range[x].lo < lo ? range[x].lo : lo;
+    hi = range[x].hi > hi ? range[x].hi : hi;
+  }
+  block_minmax<ST>(lo, hi, sh.swl, sh.swh);
+  SelState q;
+  if (lo == hi) {
     q.nb = 64;
-    q.pk = mn;
+    q.pk = lo;
   } else {
-    q.nb = __builtin_clzll(mn ^ mx);
-    q.pk = q.nb ? (mn >> (64 - q.nb)) << (64 - q.nb) : 0ull;
+    q.nb = __builtin_clzll(lo ^ hi);
+    q.pk = q.nb ? (lo >> (64 - q.nb)) << (64 - q.nb) : 0ull;
   }
   q.pv = 0;
   q.rank = r;
   q.cnt = n;
   q.done = n <= CANDMAX;
+  q.bad = 0;
+  return q;
+}
+__device__ __forceinline__ int sel_width(const SelState& q) { return 96 - q.nb < SEL_BITS ? 96 - q.nb : SEL_BITS; }
+
+// The state after a pass over q's elements that counted hb of them in this
+// thread's bin (threads past SEL_BINS: 0): the bin that holds the rank goes
+// into the prefix.
+__device__ __forceinline__ SelState sel_pick(const SelState& q, u32 hb, u32 limit, SelShared& sh) {
+  const int w = sel_width(q), p = 96 - q.nb - w;
+  u32 tot;
+  const u32 before = block_scan<ST>(hb, &tot, sh.sw);
+  SelState z = q;
+  if (threadIdx.x == 0 && (q.rank == 0 || q.rank > tot)) {
+    z.done = z.bad = 1;
+    sh.q = z;
+  }
+  if (hb && before < q.rank && q.rank <= before + hb) {
+    const u32 b = threadIdx.x;
+    if (p >= 32) {
+      z.pk |= (u64)b << (p - 32);
+    } else {
+      u64 lo = ((z.pk & 0xFFFFFFFFull) << 32) | z.pv;
+      lo |= (u64)b << p;
+      z.pk = (z.pk & 0xFFFFFFFF00000000ull) | (lo >> 32);
+      z.pv = (u32)lo;
+    }
+    z.nb = q.nb + w;
+    z.rank = q.rank - before;
+    z.cnt = hb;
+    z.done = hb <= limit || z.nb == 96;
+    sh.q = z;
+  }
+  __syncthreads();
+  z = sh.q;
+  __syncthreads();
+  return z;
+}
+
+// The state after `passes` passes of this step.  Every workgroup works it out
+// from the histograms (a pass whose last workgroup did so took 4 us more).
+__device__ __forceinline__ SelState sel_after(Ctl* c, SelState q, int passes, SelShared& sh, u32* npass) {
+  *npass = 0;
+  for (int p = 0; p < passes && !q.done; ++p) {
+    q = sel_pick(q, threadIdx.x < SEL_BINS ? c->shist[p][threadIdx.x] : 0u, CANDMAX, sh);
+    *npass += 1;
+  }
   return q;
 }
 
-// One radix pass of Select (rank r among A[0, n)): every workgroup histograms
-// its share of the elements that match the prefix fixed so far (LDS, then one
-// atomic per non-empty bin); the last workgroup to finish reads the total,
-// moves the bin holding the rank into the prefix, writes the new state to ctl
-// and clears the histogram.  The first pass (`first`) derives the starting
-// prefix from the key range (every workgroup the same); later passes
-// read the state, and return at once when the selection is done.
-__global__ __launch_bounds__(NT) void k_sel_pass(const u64* K, const u32* V, u32 n, Ctl* c, u32 r, int first,
+// One radix pass of Select (rank r among A[0, n)), number `pass` of its step:
+// every workgroup histograms its share of the elements that match the prefix
+// fixed so far (in four copies in LDS, then one atomic per non-empty bin).
+// The first pass of a selection (nrange != 0) derives the starting prefix from
+// the key range; the others read the state before the step.  A pass returns at
+// once when the selection is done.  Bound by the read of the keys: 8 loads of
+// 8 bytes in flight per thread and 16 wavefronts per compute unit (8.4 million
+// keys: 17 us; with 4 loads and 8 wavefronts, 29).
+__global__ __launch_bounds__(ST) void k_sel_pass(const u64* K, const u32* V, u32 n, Ctl* c, u32 r, int pass,
                                                  const Range* range, u32 nrange) {
-  static_assert(SEL_BINS == NT, "one bin per thread");
-  __shared__ u32 h[SEL_BINS];
-  __shared__ u32 sw[NT / 64];
-  __shared__ int s_last;
+  constexpr int CP = 4;
+  __shared__ SelShared sh;
+  __shared__ u32 h[CP][SEL_BINS];
   SelState q;
-  if (first) {
-    __shared__ u64 swl[NT / 64], swh[NT / 64];
-    u64 lo = KINF, hi = 0;
-    for (u32 x = threadIdx.x; x < nrange; x += NT) {
-      lo = range[x].lo < lo ? range[x].lo : lo;
-      hi = range[x].hi > hi ? range[x].hi : hi;
-    }
-    block_minmax<NT>(lo, hi, swl, swh);
-    q = sel_start(lo, hi, r, n);
-    if (q.done) {  // few enough elements: no pass needed
-      if (blockIdx.x == 0 && threadIdx.x == 0) {
-        c->spk = q.pk;
-        c->spv = q.pv;
-        c->snb = q.nb;
-        c->srank = q.rank;
-        c->scnt = q.cnt;
-        c->sdone = 1;
-        c->sbad = 0;
-      }
-      return;
-    }
+  if (nrange) {
+    q = sel_start(range, nrange, r, n, sh);
+    if (blockIdx.x == 0 && threadIdx.x == 0) c->q = q;
   } else {
-    q.done = c->sdone;
-    if (q.done) return;
-    q.pk = c->spk;
-    q.pv = c->spv;
-    q.nb = c->snb;
-    q.rank = c->srank;
-    q.cnt = c->scnt;
+    u32 np;
+    q = sel_after(c, c->q, pass, sh, &np);
   }
-  const int w = 96 - q.nb < SEL_BITS ? 96 - q.nb : SEL_BITS;
-  const int p = 96 - q.nb - w;
+  if (q.done) return;
+  const int w = sel_width(q), p = 96 - q.nb - w;
   // the ids take part only once the prefix or this pass's digit reaches
   // them; until then the pass reads the keys alone
   const bool needv = q.nb > 64 || p < 32;
-  h[threadIdx.x] = 0;
+  for (u32 x = threadIdx.x; x < CP * SEL_BINS; x += ST) (&h[0][0])[x] = 0;
   __syncthreads();
-  const u64 step = (u64)gridDim.x * NT;
-  for (u64 x0 = (u64)blockIdx.x * NT + threadIdx.x; x0 < n; x0 += 4 * step) {
-    u64 k[4];
-    u32 v[4];
+  u32* mine = h[(threadIdx.x >> 6) % CP];
+  const u64 step = (u64)gridDim.x * ST;
+  for (u64 x0 = (u64)blockIdx.x * ST + threadIdx.x; x0 < n; x0 += WE * step) {
+    u64 k[WE];
+    u32 v[WE];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < WE; ++j) {
       const u64 x = x0 + j * step;
       k[j] = x < n ? K[x] : KINF;
       v[j] = needv && x < n ? V[x] : 0u;
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (x0 + j * step < n && sel_match(k[j], v[j], q.pk, q.pv, q.nb)) atomicAdd(&h[sel_digit(k[j], v[j], p, w)], 1u);
+    for (int j = 0; j < WE; ++j)
+      if (x0 + j * step < n && sel_match(k[j], v[j], q.pk, q.pv, q.nb)) atomicAdd(&mine[sel_digit(k[j], v[j], p, w)], 1u);
   }
   __syncthreads();
-  if (h[threadIdx.x]) atomic_add32(&c->shist[threadIdx.x], h[threadIdx.x]);
-  if (!last_workgroup(&c->passdone, &s_last)) return;
-  // the pick, by the last workgroup: bin b (one per thread) holds the rank
-  if (threadIdx.x == 0) c->npass += 1;
-  const u32 b = threadIdx.x;
-  const u32 hb = ld_a32(&c->shist[b]);
-  u32 tot;
-  const u32 before = block_scan<NT>(hb, &tot, sw);
-  if (hb && before < q.rank && q.rank <= before + hb) {
-    u64 pk = q.pk;
-    u32 pv = q.pv;
-    if (p >= 32) {
-      pk |= (u64)b << (p - 32);
-    } else {
-      u64 lo = ((pk & 0xFFFFFFFFull) << 32) | pv;
-      lo |= (u64)b << p;
-      pk = (pk & 0xFFFFFFFF00000000ull) | (lo >> 32);
-      pv = (u32)lo;
-    }
-    c->spk = pk;
-    c->spv = pv;
-    c->snb = q.nb + w;
-    c->srank = q.rank - before;
-    c->scnt = hb;
-    c->sdone = hb <= CANDMAX || q.nb + w == 96;
-    c->sbad = 0;
+  if (threadIdx.x < SEL_BINS) {
+    u32 sum = 0;
+#pragma unroll
+    for (int j = 0; j < CP; ++j) sum += h[j][threadIdx.x];
+    if (sum) atomic_add32(&c->shist[pass][threadIdx.x], sum);
   }
-  if (threadIdx.x == 0 && (q.rank == 0 || q.rank > tot)) {
-    c->sbad = 1;
-    c->sdone = 1;
-  }
-  st_a32(&c->shist[b], 0u);
 }
 
 // The end of a publication: this thread's stores to the mailbox become
@@ -779,79 +789,145 @@ __device__ __forceinline__ void publish(Mail* mail, u32 seq) {
   __hip_atomic_store(&mail->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Gathers the elements that match the selected prefix (at most CANDMAX) and,
-// in the last workgroup to finish, ranks them by counting: the one with
-// exactly rank-1 smaller candidates is the answer.  Publishes the outcome to
-// the box (sfail: the passes were not done; sbad: a consistency check failed).
-__global__ __launch_bounds__(NT) void k_sel_collect(const u64* K, const u32* V, u32 n, Ctl* c, u64* ck, u32* cv,
-                                                    Mail* box, Mail* mail, u32 seq) {
+// Gathers the elements that match the prefix after the step's passes (at most
+// CANDMAX), each workgroup through a list in LDS; the last workgroup to finish
+// goes on with radix passes among them until at most RANKED are left and ranks
+// those by counting: the one with exactly rank-1 smaller candidates is the
+// answer.  Publishes the outcome to
+// the box and to the host (sfail: the passes were not done, and the state is
+// left for the next step; sbad: a consistency check failed).  nrange != 0: the
+// selection starts here, without passes.
+__global__ __launch_bounds__(ST) void k_sel_collect(const u64* K, const u32* V, u32 n, Ctl* c, u32 r, int passes,
+                                                    const Range* range, u32 nrange, u64* ck, u32* cv, Mail* box,
+                                                    Mail* mail, u32 seq) {
+  __shared__ SelShared sh;
   __shared__ u64 sk[CANDMAX];
   __shared__ u32 sv[CANDMAX];
+  __shared__ u32 h[SEL_BINS];
+  __shared__ u32 s_n, s_base;
   __shared__ int s_last;
-  const int done = c->sdone;
-  if (!done) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-      box->sfail = mail->sfail = 1;
-      box->sbad = mail->sbad = 0;
-      mail->npass = c->npass;
-      c->npass = 0;
-      publish(mail, seq);
-    }
-    return;
-  }
-  const u64 pk = c->spk;
-  const u32 pv = c->spv;
-  const int nb = c->snb;
-  const u64 step = (u64)gridDim.x * NT;
-  const bool needv = nb > 64;  // otherwise the match reads the keys alone, and a candidate's id is read when found
-  if (!c->sbad)
-    for (u64 x0 = (u64)blockIdx.x * NT + threadIdx.x; x0 < n; x0 += 4 * step) {
-      u64 k[4];
-      u32 v[4];
+  u32 npass = 0;
+  SelState q = nrange ? sel_start(range, nrange, r, n, sh) : sel_after(c, c->q, passes, sh, &npass);
+  const bool go = q.done && !q.bad;
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  if (go) {
+    const u64 step = (u64)gridDim.x * ST;
+    const bool needv = q.nb > 64;  // otherwise the match reads the keys alone, and a candidate's id is read when found
+    for (u64 x0 = (u64)blockIdx.x * ST + threadIdx.x; x0 < n; x0 += WE * step) {
+      u64 k[WE];
+      u32 v[WE];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < WE; ++j) {
         const u64 x = x0 + j * step;
         k[j] = x < n ? K[x] : KINF;
         v[j] = needv && x < n ? V[x] : 0u;
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (x0 + j * step < n && sel_match(k[j], v[j], pk, pv, nb)) {
-          const u32 o = atomic_add32(&c->sncand, 1u);
-          if (o < CANDMAX) {
-            st_a64(ck + o, k[j]);
-            st_a32(cv + o, needv ? v[j] : V[x0 + j * step]);
-          }
+      for (int j = 0; j < WE; ++j) {
+        const u64 x = x0 + j * step;
+        if (x >= n || !sel_match(k[j], v[j], q.pk, q.pv, q.nb)) continue;
+        const u32 id = needv ? v[j] : V[x], o = atomicAdd(&s_n, 1u);
+        if (o < CANDMAX) {
+          sk[o] = k[j];
+          sv[o] = id;
+        }
+      }
+    }
+    __syncthreads();
+    const u32 m = min(s_n, CANDMAX);  // (an excess shows in the sum)
+    if (gridDim.x > 1) {
+      if (threadIdx.x == 0) s_base = s_n ? atomic_add32(&c->sncand, s_n) : 0u;
+      __syncthreads();
+      for (u32 x = threadIdx.x; x < m; x += ST)
+        if (s_base + x < CANDMAX) {
+          st_a64(ck + s_base + x, sk[x]);
+          st_a32(cv + s_base + x, sv[x]);
         }
     }
-  if (!last_workgroup(&c->passdone, &s_last)) return;
-  const u32 nc0 = ld_a32(&c->sncand), m = nc0 < CANDMAX ? nc0 : CANDMAX;
-  const u32 r = c->srank;
-  if (threadIdx.x < m) {
-    sk[threadIdx.x] = ld_a64(ck + threadIdx.x);
-    sv[threadIdx.x] = ld_a32(cv + threadIdx.x);
+  }
+  if (!last_workgroup(&c->collected, &s_last)) return;
+  // every workgroup has read the state and the histograms
+  if (threadIdx.x < SEL_BINS) c->shist[0][threadIdx.x] = c->shist[1][threadIdx.x] = 0;
+  if (!q.done) {
+    if (threadIdx.x == 0) {
+      c->q = q;
+      box->sfail = mail->sfail = 1;
+      box->sbad = mail->sbad = 0;
+      mail->npass = npass;
+      publish(mail, seq);
+    }
+    return;
+  }
+  // (one workgroup's candidates never left LDS)
+  const u32 found = gridDim.x == 1 ? s_n : ld_a32(&c->sncand), m = min(found, CANDMAX);
+  bool bad = !go || found != q.cnt || m != found;
+  __syncthreads();  // (s_n and sncand are read)
+  if (gridDim.x > 1) {
+    if (threadIdx.x == 0) st_a32(&c->sncand, 0u);
+    for (u32 x = threadIdx.x; x < m; x += ST) {
+      sk[x] = ld_a64(ck + x);
+      sv[x] = ld_a32(cv + x);
+    }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    box->sfail = mail->sfail = 0;
-    box->sbad = mail->sbad = (c->sbad || r == 0 || r > m || nc0 != c->scnt) ? 1 : 0;
-    mail->npass = c->npass;
-    c->npass = 0;
-    st_a32(&c->sncand, 0u);
+  while (!bad && q.cnt > RANKED && q.nb < 96) {
+    const int w = sel_width(q), p = 96 - q.nb - w;
+    if (threadIdx.x < SEL_BINS) h[threadIdx.x] = 0;
+    __syncthreads();
+    for (u32 x = threadIdx.x; x < m; x += ST) {
+      const u64 k = sk[x];
+      const u32 v = sv[x];
+      if (sel_match(k, v, q.pk, q.pv, q.nb)) atomicAdd(&h[sel_digit(k, v, p, w)], 1u);
+    }
+    __syncthreads();
+    q = sel_pick(q, threadIdx.x < SEL_BINS ? h[threadIdx.x] : 0u, RANKED, sh);
+    bad = q.bad;
   }
-  if (threadIdx.x < m) {
-    const u64 k = sk[threadIdx.x];
-    const u32 v = sv[threadIdx.x];
+  __shared__ u64 fk[RANKED];
+  __shared__ u32 fv[RANKED];
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  if (!bad)
+    for (u32 x = threadIdx.x; x < m; x += ST) {
+      const u64 k = sk[x];
+      const u32 v = sv[x];
+      if (!sel_match(k, v, q.pk, q.pv, q.nb)) continue;
+      const u32 o = atomicAdd(&s_n, 1u);
+      if (o < RANKED) {
+        fk[o] = k;
+        fv[o] = v;
+      }
+    }
+  __syncthreads();
+  const u32 left = s_n;
+  bad = bad || left != q.cnt || left > RANKED || q.rank == 0 || q.rank > left;
+  if (!bad) {  // four threads per candidate
+    constexpr u32 T = ST / RANKED;
+    const u32 x = threadIdx.x / T;
     u32 below = 0;
-    for (u32 y = 0; y < m; ++y) below += sk[y] < k || (sk[y] == k && sv[y] < v);
-    if (below + 1 == r) {
+    u64 k = 0;
+    u32 v = 0;
+    if (x < left) {
+      k = fk[x];
+      v = fv[x];
+      for (u32 y = threadIdx.x % T; y < left; y += T) below += fk[y] < k || (fk[y] == k && fv[y] < v);
+    }
+#pragma unroll
+    for (u32 d = 1; d < T; d *= 2) below += __shfl_xor(below, (int)d);
+    if (x < left && threadIdx.x % T == 0 && below + 1 == q.rank) {
       box->rk = mail->rk = k;
       box->rv = mail->rv = v;
       __threadfence_system();
     }
   }
   __syncthreads();
-  if (threadIdx.x == 0) publish(mail, seq);
+  if (threadIdx.x == 0) {
+    box->sfail = mail->sfail = 0;
+    box->sbad = mail->sbad = bad;
+    mail->npass = npass;
+    publish(mail, seq);
+  }
 }
 
 // ------------------------------------------------------------------ intake
@@ -975,11 +1051,6 @@ __global__ __launch_bounds__(NT) void k_delete(const u32* ids, u64 count, u64* c
   if (threadIdx.x == 0) arrive(acc, nullptr, post, blockIdx.x, gridDim.x, gone);
 }
 
-__global__ void k_absent(const u32* ids, u64 n, u64* cur) {
-  for (u64 x = (u64)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += (u64)gridDim.x * blockDim.x)
-    cur[ids[x]] = KINF;
-}
-
 // ------------------------------------------------------------------ sort by (key, id)
 
 // Compare-exchange by (key, id).
@@ -994,50 +1065,97 @@ __device__ __forceinline__ void cx(u64& ka, u32& va, u64& kb, u32& vb) {
   }
 }
 
-// Sorts each tile of TILE (key, id) pairs by (key, id): every thread sorts
-// its WE consecutive elements in registers (odd-even transposition), then
-// rounds merge the runs of WE, 2WE, ..., TILE/2 pairwise in LDS (ping-pong
-// buffers), each thread producing its WE consecutive outputs after one
-// merge-path search.  About a quarter of the LDS accesses of a bitonic sort
-// of the tile in LDS, and 8 barriers instead of 66.  Padding (KINF, VINF)
-// sorts last and is not written.
-__global__ __launch_bounds__(NT) void k_tsort(const u64* sk_, const u32* sv_, u32 n, u64* dk, u32* dv) {
-  __shared__ u64 bk[2][TILE];
-  __shared__ u32 bv[2][TILE];
-  const u64 base = (u64)blockIdx.x * TILE;
+// Sorts up to RANK_SORT pairs by counting, for each, the pairs below it, and
+// marks their ids absent: 32 pairs per workgroup, each against all by 32
+// threads, through tiles in LDS.  The work grows with the square, but it is
+// one launch over the whole device, without a serial chain: 5,000 pairs 16 us
+// (tiles of 2048 and two merge passes: 28 + 2 x 11 us, three workgroups at
+// work); 12,000 pairs 41 us, 16,384 55 us, where a tile sort and two merge
+// passes take 45.
+constexpr u32 RANK_SORT = 12288;
+constexpr u32 RW = 32, RTILE = 4096;
+__global__ __launch_bounds__(1024) void k_rank(const u64* K, const u32* V, u32 n, u64* dk, u32* dv, u64* cur) {
+  constexpr u32 SL = 1024 / RW;
+  __shared__ u64 sk[RTILE];
+  __shared__ u32 sv[RTILE];
+  __shared__ u32 rank[RW];
+  const u32 e = threadIdx.x % RW, sl = threadIdx.x / RW, x = blockIdx.x * RW + e;
+  const u64 k = x < n ? K[x] : KINF;
+  const u32 v = x < n ? V[x] : VINF;
+  if (sl == 0) rank[e] = 0;
+  u32 below = 0;
+  for (u32 b = 0; b < n; b += RTILE) {
+    const u32 m = min(n - b, RTILE);
+    __syncthreads();
+    for (u32 y = threadIdx.x; y < m; y += 1024) {
+      sk[y] = K[b + y];
+      sv[y] = V[b + y];
+    }
+    __syncthreads();
+#pragma unroll 8
+    for (u32 y = sl; y < m; y += SL) {
+      const u64 o = sk[y];
+      below += o < k || (o == k && sv[y] < v);
+    }
+  }
+  atomicAdd(&rank[e], below);
+  __syncthreads();
+  if (sl == 0 && x < n) {
+    const u32 r = rank[e];
+    dk[r] = k;
+    dv[r] = v;
+    cur[v] = KINF;
+  }
+}
+
+// Sorts each tile of STILE (key, id) pairs by (key, id): every thread sorts
+// its SE consecutive elements in registers (odd-even transposition), then
+// rounds merge the runs of SE, 2SE, ..., STILE/2 pairwise in LDS (ping-pong
+// buffers), each thread producing its SE consecutive outputs after one
+// merge-path search.  Padding (KINF, VINF) sorts last and is not written.
+// Bound by the serial chain of the searches and walks, so the tile is spread
+// over many threads (2048 pairs: 256 threads of 8 28 us, 512 of 4 20 us, 1024
+// of 2 18 us), and it is as large as the LDS lets it be, which saves a merge
+// pass of 8 to 10 us (4096 pairs by 1024 threads of 4: 27 us).
+constexpr int SORT_T = 1024, SE = 4;
+constexpr u32 STILE = SORT_T * SE;
+__global__ __launch_bounds__(SORT_T) void k_tsort(const u64* sk_, const u32* sv_, u32 n, u64* dk, u32* dv) {
+  __shared__ u64 bk[2][STILE];
+  __shared__ u32 bv[2][STILE];
+  const u64 base = (u64)blockIdx.x * STILE;
   {
-    u64 lk[WE];
-    u32 lv[WE];
+    u64 lk[SE];
+    u32 lv[SE];
 #pragma unroll
-    for (int q = 0; q < WE; ++q) {
-      const u64 g = base + threadIdx.x + (u64)q * NT;
+    for (int q = 0; q < SE; ++q) {
+      const u64 g = base + threadIdx.x + (u64)q * SORT_T;
       lk[q] = g < n ? sk_[g] : KINF;
       lv[q] = g < n ? sv_[g] : VINF;
     }
 #pragma unroll
-    for (int q = 0; q < WE; ++q) {
-      bk[0][threadIdx.x + q * NT] = lk[q];
-      bv[0][threadIdx.x + q * NT] = lv[q];
+    for (int q = 0; q < SE; ++q) {
+      bk[0][threadIdx.x + q * SORT_T] = lk[q];
+      bv[0][threadIdx.x + q * SORT_T] = lv[q];
     }
   }
   __syncthreads();
-  const u32 o0 = threadIdx.x * WE;
-  u64 k[WE];
-  u32 v[WE];
+  const u32 o0 = threadIdx.x * SE;
+  u64 k[SE];
+  u32 v[SE];
 #pragma unroll
-  for (int q = 0; q < WE; ++q) {
+  for (int q = 0; q < SE; ++q) {
     k[q] = bk[0][o0 + q];
     v[q] = bv[0][o0 + q];
   }
 #pragma unroll
-  for (int r = 0; r < WE; ++r)
+  for (int r = 0; r < SE; ++r)
 #pragma unroll
-    for (int i = r & 1; i + 1 < WE; i += 2) cx(k[i], v[i], k[i + 1], v[i + 1]);
+    for (int i = r & 1; i + 1 < SE; i += 2) cx(k[i], v[i], k[i + 1], v[i + 1]);
   int cur = 1;
-  for (u32 L = WE; L < TILE; L *= 2, cur ^= 1) {
+  for (u32 L = SE; L < STILE; L *= 2, cur ^= 1) {
     // (buffer cur was last read two rounds ago, before the previous barrier)
 #pragma unroll
-    for (int q = 0; q < WE; ++q) {
+    for (int q = 0; q < SE; ++q) {
       bk[cur][o0 + q] = k[q];
       bv[cur][o0 + q] = v[q];
     }
@@ -1051,7 +1169,7 @@ __global__ __launch_bounds__(NT) void k_tsort(const u64* sk_, const u32* sv_, u3
     u64 xa = i < L ? ak[i] : KINF, xb = j < L ? bk2[j] : KINF;
     u32 ya = i < L ? av[i] : VINF, yb = j < L ? bv2[j] : VINF;
 #pragma unroll
-    for (int q = 0; q < WE; ++q) {
+    for (int q = 0; q < SE; ++q) {
       const bool ta = i < L && (j >= L || xa < xb || (xa == xb && ya <= yb));
       if (ta) {
         k[q] = xa;
@@ -1069,14 +1187,14 @@ __global__ __launch_bounds__(NT) void k_tsort(const u64* sk_, const u32* sv_, u3
     }
   }
 #pragma unroll
-  for (int q = 0; q < WE; ++q) {
+  for (int q = 0; q < SE; ++q) {
     bk[cur][o0 + q] = k[q];
     bv[cur][o0 + q] = v[q];
   }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < WE; ++q) {
-    const u32 x = threadIdx.x + (u32)q * NT;
+  for (int q = 0; q < SE; ++q) {
+    const u32 x = threadIdx.x + (u32)q * SORT_T;
     const u64 g = base + x;
     if (g < n) {
       dk[g] = bk[cur][x];
@@ -1086,8 +1204,7 @@ __global__ __launch_bounds__(NT) void k_tsort(const u64* sk_, const u32* sv_, u3
 }
 
 // Merge pass over sorted runs of length L (a multiple of TILE): runs 2p and
-// 2p+1 are merged into [2pL, 2pL + 2L).  part[t] = A-elements before output
-// tile t within its pair.
+// 2p+1 are merged into [2pL, 2pL + 2L).  The last pass marks the ids absent (when set).
 __device__ __forceinline__ void run_pair(u32 n, u32 L, u64 s, u32* base, u32* na, u32* nb) {
   const u64 b = (s / (2ull * L)) * 2ull * L;
   const u64 mid = b + L < n ? b + L : n, end = b + 2ull * L < n ? b + 2ull * L : n;
@@ -1096,21 +1213,8 @@ __device__ __forceinline__ void run_pair(u32 n, u32 L, u64 s, u32* base, u32* na
   *nb = (u32)(end - mid);
 }
 
-// Split searches per workgroup of the sort's partition kernel (one
-// wavefront each).
-constexpr u32 SPW = NT / 64;
-
-__global__ __launch_bounds__(NT) void k_spart(const u64* K, const u32* V, u32 n, u32 L, u32 ntiles, u32* part) {
-  const u32 t = blockIdx.x * SPW + (threadIdx.x >> 6);
-  if (t >= ntiles) return;
-  u32 b, na, nb;
-  run_pair(n, L, (u64)t * TILE, &b, &na, &nb);
-  const u32 i = mpath_wave<true>(K + b, V + b, na, K + b + na, V + b + na, nb, t * TILE - b);
-  if ((threadIdx.x & 63u) == 0) part[t] = i;
-}
-
-__global__ __launch_bounds__(NT) void k_smerge(const u64* K, const u32* V, u32 n, u32 L, const u32* part, u64* DK,
-                                               u32* DV) {
+__global__ __launch_bounds__(NT) void k_smerge(const u64* K, const u32* V, u32 n, u32 L, u64* DK, u32* DV,
+                                               u64* absent) {
   __shared__ u64 sk[TILE];
   __shared__ u32 sv[TILE];
   const u32 t = blockIdx.x;
@@ -1119,8 +1223,14 @@ __global__ __launch_bounds__(NT) void k_smerge(const u64* K, const u32* V, u32 n
   run_pair(n, L, s, &b, &na, &nb);
   const u32 d0 = (u32)(s - b);
   const u32 d1 = min(d0 + TILE, na + nb);
-  const u32 i0 = part[t];
-  const u32 i1 = d1 == na + nb ? na : part[t + 1];
+  __shared__ u32 ssplit[2];
+  const u32 wv = threadIdx.x >> 6;
+  if (wv < 2) {  // the tile's ends, one 65-way search each
+    const u32 i = mpath_wave<true>(K + b, V + b, na, K + b + na, V + b + na, nb, wv ? d1 : d0);
+    if ((threadIdx.x & 63u) == 0) ssplit[wv] = i;
+  }
+  __syncthreads();
+  const u32 i0 = ssplit[0], i1 = ssplit[1];
   const u32 j0 = d0 - i0, j1 = d1 - i1;
   const u32 nA = i1 - i0, nT = d1 - d0, nB = j1 - j0;
   {
@@ -1179,6 +1289,7 @@ __global__ __launch_bounds__(NT) void k_smerge(const u64* K, const u32* V, u32 n
   for (u32 x = threadIdx.x; x < nT; x += NT) {
     DK[s + x] = sk[x];
     DV[s + x] = sv[x];
+    if (absent) absent[sv[x]] = KINF;
   }
 }
 
@@ -1199,7 +1310,7 @@ struct WideScratch {
   u32 seq = 0;             // steps published so far
   u8* marks = nullptr;     // one byte per id (32 per 32-id word), zero between calls
   u64 marks_n = 0;
-  u32* part = nullptr;  // tile split points (maxtiles + 1)
+  u32* part = nullptr;  // tile split points of a merge (maxtiles + 1)
   u32* tc = nullptr;    // tile counts, 3 arrays of maxtiles
   u64* gs = nullptr;    // their sums over 64 tiles, packed
   u64* acc = nullptr;   // arrival words (one per 64 workgroups; a line each)
@@ -1375,28 +1486,29 @@ int wpartition3_sel(WideScratch* w, Arr A, u32 n, KV p1, KV p2, Arr O0, Arr O1, 
 int wselpart(WideScratch* w, Arr A, u32 n, u32 r, int level, KV cap, KV p2, Arr O0, Arr O1, Arr O2,
              const u64* live, KV* p1, u32* n0, u32* n1, u32* n2) {
   if (n == 0 || r == 0 || r > n) return E_INTERNAL;
-  const u32 g = grid_for(n), gh = std::min<u32>(g, GRID_HIST);
-  // Each pass fixes 8 more of the 96 bits, so 12 passes (4 rounds of 3)
-  // always finish; two or three typically do (three when the keys crowd at
-  // one end of their range, as decreased keys do).  Passes after the last
-  // needed one return at once.
-  for (int round = 0; round < 4; ++round) {
-    int ip[3];
-    for (int p = 0; p < 3; ++p)
+  const u32 gs = std::min<u32>(cdiv(n, ST * 4), GRID_SEL);
+  // Each pass fixes 8 more of the 96 bits, so 12 passes (6 steps of 2) always
+  // finish; one or two typically do (two when the keys crowd at one end of
+  // their range, as decreased keys do).  A pass after the last needed one
+  // returns at once; few enough elements need none.
+  for (int step = 0; step < 6; ++step) {
+    const int passes = n <= CANDMAX ? 0 : 2;
+    const auto first = [&](int p) { return step == 0 && p == 0 ? w->nrange[level] : 0u; };
+    int ip[2];
+    for (int p = 0; p < passes; ++p)
       ip[p] = plaunch(w, WK_SEL_PASS, 8ull * n, [&] {
-        hipLaunchKernelGGL(k_sel_pass, dim3(gh), dim3(NT), 0, w->s, A.k, A.v, n, w->ctl, r,
-                           round == 0 && p == 0 ? 1 : 0, w->range[level], w->nrange[level]);
+        hipLaunchKernelGGL(k_sel_pass, dim3(gs), dim3(ST), 0, w->s, A.k, A.v, n, w->ctl, r, p, w->range[level], first(p));
       });
     const u32 want = ++w->seq;
     const int ic = plaunch(w, WK_SEL_GATHER, 8ull * n, [&] {
-      hipLaunchKernelGGL(k_sel_collect, dim3(gh), dim3(NT), 0, w->s, A.k, A.v, n, w->ctl, w->cand_k, w->cand_v,
-                         w->box, w->mail_d, want);
+      hipLaunchKernelGGL(k_sel_collect, dim3(gs), dim3(ST), 0, w->s, A.k, A.v, n, w->ctl, r, passes, w->range[level],
+                         first(passes), w->cand_k, w->cand_v, w->box, w->mail_d, want);
     });
     if (int rc = wpartition3_sel(w, A, n, cap, p2, O0, O1, O2, live, n0, n1, n2, w->box)) return rc;
     if (int rc = wait_mail(w, want)) return rc;
     // passes after the last needed one, and a gather before the passes were
     // done, returned at once: they read nothing
-    for (int p = (int)w->mail_h->npass; p < 3; ++p) patch_kind(w, ip[p], WK_IDLE), patch_bytes(w, ip[p], 0);
+    for (int p = (int)w->mail_h->npass; p < passes; ++p) patch_kind(w, ip[p], WK_IDLE), patch_bytes(w, ip[p], 0);
     if (w->mail_h->sfail) patch_kind(w, ic, WK_IDLE), patch_bytes(w, ic, 0);
     if (w->mail_h->sbad) return E_INTERNAL;
     if (!w->mail_h->sfail) {
@@ -1435,27 +1547,31 @@ int wpartition3(WideScratch* w, Arr A, u32 n, KV p1, KV p2, Arr O0, Arr O1, Arr 
   return wpartition3_sel(w, A, n, p1, p2, O0, O1, O2, live, n0, n1, n2, nullptr);
 }
 
-// Sorts X[0, n) by (key, id) into D (n <= 4d; X is overwritten).
-int wsort(WideScratch* w, Arr X, u32 n, u64* dk, u32* dv) {
+// Sorts X[0, n) by (key, id) into D and marks the ids absent (n <= 4d; X is
+// overwritten).
+int wsort(WideScratch* w, Arr X, u32 n, u64* dk, u32* dv, u64* cur) {
   if (n == 0) return 0;
+  if (n <= RANK_SORT) {
+    plaunch(w, WK_SORT_TILE, 24ull * n, [&] {
+      hipLaunchKernelGGL(k_rank, dim3(cdiv(n, RW)), dim3(1024), 0, w->s, X.k, X.v, n, dk, dv, cur);
+    });
+    return launch_ok();
+  }
   const u32 nt = cdiv(n, TILE);
-  if (nt > w->maxtiles) return E_INTERNAL;
   int passes = 0;
-  for (u64 L = TILE; L < n; L *= 2) ++passes;
+  for (u64 L = STILE; L < n; L *= 2) ++passes;
   // ping-pong so that the last pass lands in D
   Arr bufs[2] = {X, Arr{w->tmp_k, w->tmp_v}};
-  Arr dst = passes == 0 ? Arr{dk, dv} : bufs[(passes & 1) ? 1 : 0];
+  Arr src = bufs[passes & 1];
   plaunch(w, WK_SORT_TILE, 24ull * n,
-          [&] { hipLaunchKernelGGL(k_tsort, dim3(nt), dim3(NT), 0, w->s, X.k, X.v, n, dst.k, dst.v); });
-  Arr src = dst;
-  u64 L = TILE;
+          [&] { hipLaunchKernelGGL(k_tsort, dim3(cdiv(n, STILE)), dim3(SORT_T), 0, w->s, X.k, X.v, n, src.k, src.v); });
+  u64 L = STILE;
   for (int p = 0; p < passes; ++p, L *= 2) {
-    Arr to = p == passes - 1 ? Arr{dk, dv} : (src.k == bufs[0].k ? bufs[1] : bufs[0]);
-    plaunch(w, WK_OTHER, 4ull * nt, [&] {
-      hipLaunchKernelGGL(k_spart, dim3(cdiv(nt, SPW)), dim3(NT), 0, w->s, src.k, src.v, n, (u32)L, nt, w->part);
-    });
+    const bool last = p == passes - 1;
+    Arr to = last ? Arr{dk, dv} : (src.k == bufs[0].k ? bufs[1] : bufs[0]);
     plaunch(w, WK_SORT_MERGE, 24ull * n, [&] {
-      hipLaunchKernelGGL(k_smerge, dim3(nt), dim3(NT), 0, w->s, src.k, src.v, n, (u32)L, w->part, to.k, to.v);
+      hipLaunchKernelGGL(k_smerge, dim3(nt), dim3(NT), 0, w->s, src.k, src.v, n, (u32)L, to.k, to.v,
+                         last ? cur : nullptr);
     });
     src = to;
   }
@@ -1658,9 +1774,9 @@ const char* wide_kernel_name(int kind) {
       "k_intake (atomicMin on current keys + marks)",
       "k_bits<false> (mark compaction, counting pass)",
       "k_bits<true> (mark compaction, writing pass)",
-      "k_tsort (tile sort of the extracted minima)",
+      "k_rank / k_tsort (sort of the extracted minima)",
       "k_smerge (merge pass of the extracted minima)",
-      "k_delete / k_absent (ids marked absent)",
+      "k_delete (ids marked absent)",
       "scans, reductions, result publishing",
       "Select passes and gathers that returned at once"};
   return kind >= 0 && kind < WK_COUNT ? names[kind] : nullptr;
@@ -1823,12 +1939,7 @@ int wide_extract_min(WideScratch* w, WideHeap* h, u64 k, u64* okeys, u32* oids, 
       return rc;
     }
     if (n0 != take) return E_INTERNAL;
-    if (int rc = wsort(w, X, take, okeys + out, oids + out)) return rc;
-    plaunch(w, WK_ABSENT, 12ull * take, [&] {
-      hipLaunchKernelGGL(k_absent, dim3(grid_for(take)), dim3(NT), 0, w->s, (const u32*)(oids + out), (u64)take,
-                         h->cur);
-    });
-    if (int rc = launch_ok()) return rc;
+    if (int rc = wsort(w, X, take, okeys + out, oids + out, h->cur)) return rc;
     st->L[0].bsel ^= 1;
     st->L[0].nB = n1;
     st->live -= take;
