@@ -541,8 +541,24 @@ int sssp_run(const uint64_t* offsets, const uint32_t* targets, const uint32_t* w
   u32 d = o.d ? o.d : (u32)(cc.maxdeg ? cc.maxdeg : 1) * (o.d_scale > 1 ? o.d_scale : 1u);
   if (cc.maxdeg > d) return fail(PBH_EINVAL, "sssp: opts.d %u below the maximum out-degree %llu", d,
                                  (unsigned long long)cc.maxdeg);
+  int dev = 0, max_lds = 0;
+  HIPCHK(hipGetDevice(&dev));
+  HIPCHK(hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+  const auto budget_of = [&](int team) { return (size_t)max_lds - sssp_static_lds(team) - 256; };
+  const auto fit = [&](int team) {  // levels of the heap that fit the team's LDS
+    int k = 0;
+    while (k < MAXL && lvl_off(d, k + 1) * 12ull <= budget_of(team)) ++k;
+    return k;
+  };
   int team = (int)o.team;
-  if (team == 0) team = d <= 256 ? 64 : (d <= 4096 ? 256 : 1024);
+  if (team == 0) {
+    // One wavefront is faster while the updates and levels of a round are
+    // small (ring lattices of degree 60: 29 ms against 44; of degree 100: 44
+    // against 46), four from there on (degree 128: 73 against 48; random
+    // graph of degree 112: 94 against 54).  Where four wavefronts' own LDS
+    // would cost a level its place (and the caller its scratch), one stays.
+    team = d <= 100 || (d <= 256 && fit(256) < fit(64)) ? 64 : (d <= 4096 ? 256 : 1024);
+  }
   if (team != 64 && team != 256 && team != 1024) return fail(PBH_EINVAL, "sssp: team must be 64, 256 or 1024");
   if (o.deep_level && o.schedule != 0) return fail(PBH_EINVAL, "sssp: deep-level workers need schedule 0");
   // Heap capacity: the arena is sized for hcap elements.  With the plain rule
@@ -555,14 +571,10 @@ int sssp_run(const uint64_t* offsets, const uint32_t* targets, const uint32_t* w
   // MAXL levels are reached.
   const u64 safe = m + 1;
   u64 hcap = o.heap_capacity ? o.heap_capacity : (safe < 4ull * n + 4096 ? safe : 4ull * n + 4096);
-  int dev = 0;
-  HIPCHK(hipGetDevice(&dev));
-  int max_lds = 0;
-  HIPCHK(hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
   bool first = true;
   for (;;) {
     int q = levels_for(d, hcap, 2);
-    size_t budget = (size_t)max_lds - sssp_static_lds(team) - 256;
+    size_t budget = budget_of(team);
     int qlds = 0;
     if (o.lds_levels == 0) {
       while (qlds < q && lvl_off(d, qlds + 1) * 12ull <= budget) ++qlds;
@@ -630,12 +642,13 @@ int sssp_run(const uint64_t* offsets, const uint32_t* targets, const uint32_t* w
       }
     }
     p.prof = o.profile ? 1u : 0u;
-    // deep_level selects the large-heap form of the round loop: LDS staging
-    // for merges of the HBM levels, after the LDS levels (it shares that
-    // room with the speculative rounds' list), and the deep-level workers
+    // deep_level selects the form of the round loop with deep-level workers.
+    // That form and teams of several wavefronts merge the HBM levels through
+    // LDS staging, after the LDS levels (it shares that room with the
+    // speculative rounds' list).
     p.full = o.deep_level ? 1u : 0u;
     p.stage = 0;
-    if (p.full && q > qlds) {
+    if ((p.full || team > 64) && q > qlds) {
       const u64 sb = stage_bytes(team, team == 64 ? 8 : 4);
       const size_t lvb = (size_t)lvl_off(d, qlds) * 12ull;
       if (lvb + sb <= budget) {

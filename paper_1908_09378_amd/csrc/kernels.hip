@@ -50,15 +50,20 @@ __global__ void k_check_update(const u64* keys, const u32* ids, u64 count, u32 i
   if (b) atomicOr(bad, 1ull);
 }
 
-// One query, one workgroup: the plain form of the round loop, with every k
-// rule (k_sssp) or the plain rule only (k_sssp_plain, lighter).
+// One query, one workgroup: the round loop with every k rule (SPEC) or the
+// plain rule only (lighter).  Teams of several wavefronts merge HBM levels
+// through the staging area: with d = 1,092 every level is there, and a search
+// per thread in HBM made a merge of 2,800 elements 10 us.  One wavefront's
+// heaps live in LDS but for levels that are rarely touched, and the staged
+// forms' code would only widen its loop.
 template <int NT, bool SPEC>
 __global__ __launch_bounds__(NT) void k_sssp(SsspParams p) {
   extern __shared__ __align__(16) unsigned char dyn[];
   __shared__ TeamShared<NT / 64> ts;
   __shared__ HeapState st_lds;
-  DevTeam<NT, false, false> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
-  sssp_query<NT, false, SPEC>(t, (HeapState PBH_LDS*)&st_lds, dyn, p);
+  constexpr bool FULL = NT > 64;
+  DevTeam<NT, FULL, false> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
+  sssp_query<NT, FULL, SPEC>(t, (HeapState PBH_LDS*)&st_lds, dyn, p);
 }
 
 // dist = INF except dist[src] = 0, for every query (blockIdx.y = query).

@@ -276,6 +276,22 @@ PBH_INL u32 merge_path(VA av, u32 na, VB bv, u32 nb, u32 diag) {
   return lo;
 }
 
+// The same split by one wavefront: every step tests as many split points as it
+// has lanes (the tests are true on a prefix, so their number narrows the range),
+// two or three dependent reads of HBM instead of a dozen.
+template <class T, class VA, class VB>
+PBH_INL u32 merge_path_lanes(const T& t, VA av, u32 na, VB bv, u32 nb, u32 diag) {
+  u32 lo = diag > nb ? diag - nb : 0u, hi = diag < na ? diag : na;
+  while (lo < hi) {
+    const u32 stride = (hi - lo + (u32)T::kW - 1) / (u32)T::kW, mid = lo + ((u32)t.lane() + 1u) * stride - 1u;
+    bool afirst = false;
+    if (mid < hi) afirst = av[mid] <= bv[diag - 1 - mid];
+    lo += (u32)__builtin_popcountll(t.ballot(afirst)) * stride;
+    hi = lo + stride - 1 < hi ? lo + stride - 1 : hi;
+  }
+  return lo < hi ? lo : hi;
+}
+
 // Merge + DeleteDuplicates (Algorithm 1; DeleteDuplicates by scan + prefix
 // sums as in Lemma 2's proof).  A and B are sorted by id with unique ids; the
 // output C (not aliasing A or B) is sorted by id with unique ids.  For a pair
@@ -379,18 +395,100 @@ struct CountLe {
   u32 n;
 };
 
+// E outputs of a merge from A's window [i, ea) and B's [j, eb) of one area in
+// LDS (A's begins at 0), with no branch but the one for pairs: a lone wavefront
+// pays 16 cycles and more for each.  A step reads one id; the keys follow at
+// the end, all at once.  The decisions are MergeWin's.
+template <int E>
+struct MergeArea {
+  typedef u64 VK __attribute__((ext_vector_type(E)));
+  typedef u32 VV __attribute__((ext_vector_type(E)));
+  VK ko;
+  VV vo;
+
+  template <class T, class AS>
+  PBH_INL u32 walk(const T& t, AS S, u32 i, u32 ea, u32 j, u32 eb, u32 valid, const u64* cur, bool filterB,
+                   int prefer) {
+    constexpr u32 LAST = (u32)T::kNT * E - 1;
+    // (a device's area is followed by more of the team's LDS)
+    auto in_area = [](u32 x) { return T::kW == 1 && x > LAST ? LAST : x; };
+    VV src, oth;
+    u32 keep = 0, pair = 0, askb = 0;
+    const u32 pv = S.v[i > 0 ? i - 1 : 0], v0 = S.v[in_area(i)], v1 = S.v[in_area(j)];
+    u32 prev = i > 0 ? pv : VINF, va = i < ea ? v0 : VINF, vb = j < eb ? v1 : VINF;
+#pragma unroll
+    for (int s = 0; s < E; ++s) {
+      const bool in = (u32)s < valid, takeA = va <= vb, kp = in & (takeA | (prev != vb));
+      src[s] = in_area(takeA ? i : j);
+      oth[s] = in_area(j);
+      vo[s] = takeA ? va : vb;
+      keep |= (u32)kp << s;
+      pair |= (u32)(in & (va == vb)) << s;
+      askb |= (u32)(kp & !takeA) << s;
+      prev = takeA ? va : prev;
+      i += takeA ? 1u : 0u;
+      j += takeA ? 0u : 1u;
+      if (s + 1 == E) continue;
+      const u32 x = takeA ? i : j, n = S.v[in_area(x)], nv = x < (takeA ? ea : eb) ? n : VINF;
+      va = takeA ? nv : va;
+      vb = takeA ? vb : nv;
+    }
+#pragma unroll
+    for (int s = 0; s < E; ++s) ko[s] = S.k[src[s]];
+    if (!filterB) askb = 0;
+    if (prefer == PREFER_A) pair = 0;
+    if (pair | askb) {
+      VK alt, c;
+#pragma unroll
+      for (int s = 0; s < E; ++s) {
+        alt[s] = S.k[oth[s]];
+        if (alt[s] == ko[s]) pair &= ~(1u << s);
+      }
+      const bool by_cur = prefer == PREFER_LIVE && cur;
+      if (!by_cur) {
+#pragma unroll
+        for (int s = 0; s < E; ++s) {
+          const bool other = ((pair >> s) & 1u) & ((prefer == PREFER_B) | (alt[s] < ko[s]));
+          ko[s] = other ? alt[s] : ko[s];
+        }
+        pair = 0;
+      }
+      if (pair | askb) {
+#pragma unroll
+        for (int s = 0; s < E; ++s) c[s] = t.load_cur(cur + (((pair | askb) >> s) & 1u ? vo[s] : 0u));
+#pragma unroll
+        for (int s = 0; s < E; ++s) {
+          const bool other = (((pair | askb) >> s) & 1u) & (ko[s] != c[s]);
+          const bool second = other & ((pair >> s) & 1u) & (alt[s] == c[s]);
+          ko[s] = second ? alt[s] : ko[s];
+          keep &= ~((u32)(other & !second) << s);
+        }
+      }
+    }
+    return keep;
+  }
+};
+
+// A thread's kept outputs, and above them those of them that are <= le->p (a
+// tile has at most 2^15 outputs).
+template <int E, class W>
+PBH_INL u32 merge_count(const W& w, u32 keep, const CountLe* le) {
+  u32 x = (u32)__builtin_popcount(keep);
+  if (le) {
+    u32 c = 0;
+#pragma unroll
+    for (int s = 0; s < E; ++s) c += ((keep >> s) & 1u) & (u32)kv_le(KV{w.ko[s], w.vo[s]}, le->p);
+    x |= c << 16;
+  }
+  return x;
+}
+
 // Places a thread's kept outputs (a prefix sum over the team) and counts those
 // <= le->p; returns the tile's output count.
 template <class T, int E, class AC>
 PBH_INL u32 merge_store(const T& t, const MergeWin<E>& w, u32 keep, AC C, u32 out, CountLe* le) {
-  u32 x = (u32)__builtin_popcount(keep), tot;
-  if (le) {
-    u32 c = 0;
-#pragma unroll
-    for (int s = 0; s < E; ++s) c += ((keep >> s) & 1u) && kv_le(KV{w.ko[s], w.vo[s]}, le->p) ? 1u : 0u;
-    x |= c << 16;  // a tile has at most 2^15 outputs
-  }
-  u32 o = out + (t.scan_excl(x, &tot) & 0xFFFFu);
+  u32 tot;
+  u32 o = out + (t.scan_excl(merge_count<E>(w, keep, le), &tot) & 0xFFFFu);
 #pragma unroll
   for (int s = 0; s < E; ++s)
     if ((keep >> s) & 1u) {
@@ -436,86 +534,130 @@ PBH_INL void stage_setup(T& t, BP base) {
 
 // Merge + DeleteDuplicates of arrays in HBM through the team's LDS staging
 // area, with the same result as merge_dedup_e.  The merge-path split of every
-// tile boundary is found first, a team-sized batch of boundaries at a time
-// (one binary search per thread, all in flight together), instead of one
-// search per thread per tile; then each tile's two input windows are loaded
-// into LDS with coalesced reads (plus A's element before the window and B's
-// element after it, which the duplicate checks look at), and the per-thread
-// merge-path searches and walks run on LDS.
-template <class T, class AA, class AB, class AC>
-PBH_INL u32 merge_dedup_staged(const T& t, AA A, u32 na, AB B, u32 nb, AC C, const u64* cur, bool filterB,
-                               int prefer, CountLe* le) {
-  constexpr int E = T::kE;
-  constexpr u32 TILE = (u32)T::kNT * E;
-  constexpr u32 W = TILE + 2u;
-  const u32 total = na + nb;
-  const auto ka = t.stk;  // window of A: keys ka[0..W), ids va[0..W)
-  const auto kb = ka + W;  // window of B
-  const auto va = t.stv;
-  const auto vb = va + W;
+// tile boundary is found first (a batch of boundaries at a time: one per
+// wavefront while they are few, one per thread otherwise); then each tile's
+// inputs are loaded into LDS with coalesced reads, A's and B's one after the
+// other, with A's element before them and the next one of each, which the
+// duplicate checks look at; and the per-thread merge-path searches and walks
+// run on LDS while the next tile's inputs are on their way.
+// Bound by the chain of each tile's steps (one wavefront per SIMD, nothing to
+// switch to), full or not.  256 threads take 8 outputs each rather than 4, so
+// that a tile's search and barriers serve twice as many (4,000 elements 25,600
+// -> 19,600 cycles), and a remainder of up to half a tile one of half the size;
+// a tile's windows share one area, of the size two apart would have for half
+// the tile.
+//
+// The outputs at merge positions [from, total) go to C from `out` on; the new
+// end of C is returned.
+template <int E, class T, class AA, class AB, class AC>
+PBH_INL u32 merge_tiles(const T& t, AA A, u32 na, AB B, u32 nb, AC C, u32 from, u32 total, u32 out, const u64* cur,
+                        bool filterB, int prefer, CountLe* le) {
+  // (with the three neighbours the inputs are at most E elements per thread)
+  constexpr u32 TILE = (u32)T::kNT * E - 4u;
+  const auto sk = t.stk;
+  const auto sv = t.stv;
   const auto sp = t.stp;
-  u32 out = 0;
-  for (u32 cbase = 0; cbase < total; cbase += TILE * (u32)T::kNT) {
+  u64 xk[E];
+  u32 xv[E];
+  for (u32 cbase = from; cbase < total; cbase += TILE * (u32)T::kNT) {
     u32 ntile = (total - cbase + TILE - 1) / TILE;
     ntile = ntile < (u32)T::kNT ? ntile : (u32)T::kNT;
-    for (u32 j = (u32)t.tid(); j <= ntile; j += (u32)T::kNT) {
-      const u64 dg = (u64)cbase + (u64)j * TILE;
-      sp[j] = merge_path<false>(A.v, na, B.v, nb, dg < total ? (u32)dg : total);
+    if (T::kW > 1 && ntile <= 4u * T::kNW) {
+      for (u32 j = t.uni((u32)t.wave()); j <= ntile; j += T::kNW) {
+        const u32 dg = total - cbase < j * TILE ? total : cbase + j * TILE;
+        const u32 i = merge_path_lanes(t, A.v, na, B.v, nb, dg);
+        if (t.lane() == 0) sp[j] = i;
+      }
+    } else {
+      for (u32 j = (u32)t.tid(); j <= ntile; j += (u32)T::kNT) {
+        const u64 dg = (u64)cbase + (u64)j * TILE;
+        sp[j] = merge_path<false>(A.v, na, B.v, nb, dg < total ? (u32)dg : total);
+      }
     }
     t.sync();
+    // tile k: its inputs A[a0, a1) and B[b0, b1), and the window A[abase, abase
+    // + la) and B[b0, b0 + lb)
+    u32 d0, d1, a0, a1, b0, b1, abase, la, lb;
+    auto tile = [&](u32 k) {
+      d0 = cbase + k * TILE;
+      d1 = total - d0 < TILE ? total : d0 + TILE;
+      a0 = t.uni(sp[k]);
+      a1 = t.uni(sp[k + 1]);
+      b0 = d0 - a0;
+      b1 = d1 - a1;
+      abase = a0 > 0 ? a0 - 1 : 0;
+      la = (a1 < na ? a1 + 1 : a1) - abase;
+      lb = (b1 < nb ? b1 + 1 : b1) - b0;
+      // (past the end, the last element again: no branches)
+#pragma unroll
+      for (int r = 0; r < E; ++r) {
+        u32 x = (u32)t.tid() + (u32)r * (u32)T::kNT;
+        x = x < la + lb ? x : la + lb - 1;
+        const bool fa = x < la;
+        const u32 y = fa ? abase + x : b0 + (x - la);
+        xk[r] = (fa ? A.k : B.k)[y];
+        xv[r] = (fa ? A.v : B.v)[y];
+      }
+    };
+    tile(0);
     for (u32 k = 0; k < ntile; ++k) {
-      const u32 d0 = cbase + k * TILE, d1 = total - d0 < TILE ? total : d0 + TILE;
-      const u32 a0 = sp[k], a1 = sp[k + 1], b0 = d0 - a0, b1 = d1 - a1;
-      // the windows reach one element past the tile's inputs (the walk
-      // compares with the next element of the other array) and A's one
-      // before (a B element is checked against A's previous id)
-      const u32 abase = a0 > 0 ? a0 - 1 : 0;
-      const u32 aend = a1 < na ? a1 + 1 : a1, bend = b1 < nb ? b1 + 1 : b1;
-      {
-        // every load of both windows in flight before the first LDS store
-        constexpr int R = (int)((W + T::kNT - 1) / T::kNT);
-        const u32 la = aend - abase, lb = bend - b0;
-        u64 xk[R], yk[R];
-        u32 xv[R], yv[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const u32 x = (u32)t.tid() + (u32)r * (u32)T::kNT;
-          if (x < la) {
-            xk[r] = A.k[abase + x];
-            xv[r] = A.v[abase + x];
-          }
-          if (x < lb) {
-            yk[r] = B.k[b0 + x];
-            yv[r] = B.v[b0 + x];
-          }
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const u32 x = (u32)t.tid() + (u32)r * (u32)T::kNT;
-          if (x < la) {
-            ka[x] = xk[r];
-            va[x] = xv[r];
-          }
-          if (x < lb) {
-            kb[x] = yk[r];
-            vb[x] = yv[r];
-          }
-        }
+      for (int r = 0; r < E; ++r) {
+        const u32 x = (u32)t.tid() + (u32)r * (u32)T::kNT;
+        sk[x] = xk[r];
+        sv[x] = xv[r];
       }
       t.sync();
-      // this thread's outputs of the tile, from e0 (relative to d0)
+      const u32 n = d1 - d0, wa = a1 - a0, wb = b1 - b0, skip = a0 - abase, ea = la, eb = lb;
+      if (k + 1 < ntile) tile(k + 1);
+      // this thread's outputs of the tile, from e0
       u32 e0 = (u32)t.tid() * E;
-      e0 = e0 < d1 - d0 ? e0 : d1 - d0;
-      const u32 i = merge_path<T::kNT == 64>(va + (a0 - abase), a1 - a0, vb, b1 - b0, e0), j = e0 - i;
-      // the windows as arrays that start at A[abase] and B[b0]
-      ArrT<decltype(t.stk), decltype(t.stv)> SA{ka, va}, SB{kb, vb};
-      MergeWin<E> w;
-      w.load(SA, a0 - abase + i, aend - abase, SB, j, bend - b0);
-      const u32 keep = w.walk(t, d1 - d0 - e0, cur, filterB, prefer);
-      out += merge_store<T, E>(t, w, keep, C, out, le);
+      e0 = e0 < n ? e0 : n;
+      const u32 i = merge_path<T::kNT == 64>(sv + skip, wa, sv + ea, wb, e0), j = e0 - i;
+      MergeArea<E> w;
+      const u32 keep = w.walk(t, ArrT<decltype(t.stk), decltype(t.stv)>{sk, sv}, skip + i, ea, ea + j, ea + eb, n - e0,
+                              cur, filterB, prefer);
+      // The outputs go to their places in the staging area (the scan's barrier
+      // ends the walks) and from there out in rows: a thread's outputs are
+      // consecutive, so stored from the registers each store would touch 64
+      // lines.  Eight consecutive places are permuted by the eight they lie
+      // in, or the threads' places would meet in a few banks.
+      u32 tot, x = merge_count<E>(w, keep, le);
+      u32 o = t.scan_excl(x, &tot) & 0xFFFFu;
+      if (le) le->n += tot >> 16;
+      tot &= 0xFFFFu;
+      auto place = [](u32 o) { return o ^ ((o >> 3) & 7u); };
+#pragma unroll
+      for (int s = 0; s < E; ++s) {  // (a dropped one goes past the outputs)
+        const u32 y = (keep >> s) & 1u ? place(o) : (u32)T::kNT * E;
+        sk[y] = w.ko[s];
+        sv[y] = w.vo[s];
+        o += (keep >> s) & 1u;
+      }
+      t.sync();
+#pragma unroll
+      for (int r = 0; r < E; ++r) {
+        const u32 y = (u32)t.tid() + (u32)r * (u32)T::kNT;
+        if ((u32)r * (u32)T::kNT < tot && y < tot) {
+          C.k[out + y] = sk[place(y)];
+          C.v[out + y] = sv[place(y)];
+        }
+      }
+      out += tot;
       t.sync();  // the next tile overwrites the windows
     }
   }
+  return out;
+}
+template <class T, class AA, class AB, class AC>
+PBH_INL u32 merge_dedup_staged(const T& t, AA A, u32 na, AB B, u32 nb, AC C, const u64* cur, bool filterB,
+                               int prefer, CountLe* le) {
+  constexpr int E = T::kME, H = T::kNT == 1 ? E : E / 2;
+  constexpr u32 TILE = (u32)T::kNT * E - 4u, HALF = (u32)T::kNT * H - 4u;
+  const u32 total = na + nb, rest = total % TILE, cut = rest <= HALF ? total - rest : total;
+  u32 out = 0;
+  if (cut) out = merge_tiles<E>(t, A, na, B, nb, C, 0u, cut, out, cur, filterB, prefer, le);
+  if (cut < total) out = merge_tiles<H>(t, A, na, B, nb, C, cut, total, out, cur, filterB, prefer, le);
   t.sync();
   return out;
 }
@@ -764,8 +906,10 @@ PBH_INL u32 merge_small(const T& t, AA A, u32 na, AB B, u32 nb, AC C, const u64*
 
 // Merge + DeleteDuplicates by whichever form suits the team and the sizes: one
 // wavefront takes a short array into registers (SmallMerge); otherwise every
-// thread walks from its merge-path split, for arrays in HBM of more than a
-// tile through the LDS staging area when the team has one.
+// thread walks from its merge-path split, for arrays in HBM of more than two
+// elements per thread through the LDS staging area when the team has one (256
+// threads: 500 elements 4,600 cycles as they are, 6,400 staged; 1,500 14,300
+// and 10,000; 4,000 30,000 and 19,900).
 template <class T, class AA, class AB, class AC>
 PBH_INL u32 merge_dedup(const T& t, AA A, u32 na_, AB B, u32 nb_, AC C, const u64* cur, bool filterB,
                         int prefer = PREFER_LIVE, CountLe* le = nullptr) {
@@ -776,7 +920,7 @@ PBH_INL u32 merge_dedup(const T& t, AA A, u32 na_, AB B, u32 nb_, AC C, const u6
     if (rows) return merge_small<4>(t, A, na, B, nb, C, cur, prefer, le);
   }
   if constexpr (T::kStage && !in_lds<AA>::v && !in_lds<AB>::v) {
-    if (t.stk && na + nb > (u32)T::kNT * T::kE)
+    if (t.stk && na + nb > 2u * (u32)T::kNT)
       return merge_dedup_staged(t, A, na, B, nb, C, cur, filterB, prefer, le);
   }
   if constexpr (T::kNT >= 256) {
@@ -996,6 +1140,9 @@ PBH_INL KV select_kth(const T& t, AA A, u32 n_, u32 r_) {
   if (n <= 4u * (u32)T::kNT) return select_hist<4>(t, A, n, r);
   if constexpr (!in_lds<AA>::v) {
     if (n <= 16u * (u32)T::kNT) return select_hist<16>(t, A, n, r);
+    if constexpr (T::kNT == 256) {
+      if (n <= 32u * (u32)T::kNT) return select_hist<32>(t, A, n, r);
+    }
   }
   u64 lo = KINF, hi = 0;
   for (u32 base = 0; base < n; base += (u32)T::kNT * T::kRU) {
@@ -1103,6 +1250,7 @@ PBH_INL void partition3(const T& t, AA A, u32 n_, KV p1, KV p2, A0 O0, A1 O1, A2
   constexpr int EW = ((T::kStage || T::kNT >= 256) && !in_lds<AA>::v) ? 2 * T::kE : T::kE;
   constexpr int E = (T::kNW > 1 && EW * T::kNW > 64) ? 64 / T::kNW : EW;
   const u32 n = t.uni(n_);
+  const bool three = t.uni((u32)kv_less(p2, kv_inf())) != 0;  // (else nothing lies beyond p2)
   u32 c0 = 0, c1 = 0, c2 = 0;
   u32 par = 0;
   for (u32 base = 0; base < n; base += (u32)T::kNT * E, par ^= 128u) {
@@ -1134,13 +1282,19 @@ PBH_INL void partition3(const T& t, AA A, u32 n_, KV p1, KV p2, A0 O0, A1 O1, A2
       cl[s] = 3u;
       at[s] = 0;
       if (base + (u32)s * (u32)T::kNT >= n) continue;
-      cl[s] = kv_le(e, p1) ? 0u : (kv_le(e, p2) ? 1u : 2u);
+      cl[s] = kv_le(e, p1) ? 0u : 1u;
+      if (three) cl[s] = cl[s] == 0u || kv_le(e, p2) ? cl[s] : 2u;
       if (live0 && cur[s] != kk[s]) cl[s] = 3u;
       if (x >= n) cl[s] = 3u;
-      const u64 b0 = t.ballot(cl[s] == 0u), b1 = t.ballot(cl[s] == 1u), b2 = t.ballot(cl[s] == 2u);
-      const u32 r0 = t.count_below(b0), r1 = t.count_below(b1), r2 = t.count_below(b2);
-      const u32 q0 = (u32)__builtin_popcountll(b0), q1 = (u32)__builtin_popcountll(b1),
-                q2 = (u32)__builtin_popcountll(b2);
+      const u64 b0 = t.ballot(cl[s] == 0u), b1 = t.ballot(cl[s] == 1u);
+      u32 q0 = (u32)__builtin_popcountll(b0), q1 = (u32)__builtin_popcountll(b1), q2 = 0;
+      const u32 r0 = t.count_below(b0), r1 = t.count_below(b1);
+      u32 r2 = 0;
+      if (three) {
+        const u64 b2 = t.ballot(cl[s] == 2u);
+        r2 = t.count_below(b2);
+        q2 = (u32)__builtin_popcountll(b2);
+      }
       if constexpr (T::kNW == 1) {
         at[s] = cl[s] == 0u ? c0 + r0 : (cl[s] == 1u ? c1 + r1 : c2 + r2);
         c0 += q0;
@@ -1176,6 +1330,16 @@ PBH_INL void partition3(const T& t, AA A, u32 n_, KV p1, KV p2, A0 O0, A1 O1, A2
 #pragma unroll
     for (int s = 0; s < E; ++s) {
       if (base + (u32)s * (u32)T::kNT >= n) continue;
+      if constexpr (same_arr<A0, A1>::v && same_arr<A0, A2>::v) {
+        // one store for whichever array it goes to
+        const auto pk = cl[s] == 0u ? O0.k : (cl[s] == 1u ? O1.k : O2.k);
+        const auto pv = cl[s] == 0u ? O0.v : (cl[s] == 1u ? O1.v : O2.v);
+        if (cl[s] < 3u) {
+          pk[at[s]] = kk[s];
+          pv[at[s]] = vv[s];
+        }
+        continue;
+      }
       if (cl[s] == 0u) {
         O0.k[at[s]] = kk[s];
         O0.v[at[s]] = vv[s];

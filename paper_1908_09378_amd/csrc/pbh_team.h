@@ -180,11 +180,12 @@ struct DevTeam {
   static constexpr int kW = 64;  // lanes of a wavefront
   static constexpr int kE = NT == 64 ? 8 : 4;  // elements per thread per tile
   static constexpr int kM = 4;                 // outputs per thread of a merge tile
+  static constexpr int kME = NT == 1024 ? 4 : 8;  // and of one through the staging area
   static constexpr bool kStage = FULL;  // merges of HBM arrays through the staging area
   static constexpr int kRU = FULL || NT >= 256 ? 4 : 1;  // loads in flight per thread in streaming loops
   TeamShared<kNW> PBH_LDS* sh;
-  // LDS staging area for merges of arrays in HBM (null: none): two windows of
-  // kNT * kE + 2 elements (keys, then ids) and kNT + 1 split points
+  // LDS staging area for merges of arrays in HBM (null: none): room for 2 (kNT
+  // * kE + 2) elements (keys, then ids) and kNT + 1 split points
   u64 PBH_LDS* stk = nullptr;
   u32 PBH_LDS* stv = nullptr;
   u32 PBH_LDS* stp = nullptr;
@@ -247,11 +248,19 @@ struct DevTeam {
       if (lane() == 63) sh->wsum[wave()] = inc;
       __syncthreads();
       u32 pre = 0, tot = 0;
+      if constexpr (kNW > 4) {
+        // the wavefronts' sums, one per lane (16 of them one after another by
+        // every thread: 2,500 cycles for the scan)
+        const u32 s = lane() < kNW ? sh->wsum[lane()] : 0u, all = wave_incl(s);
+        tot = __builtin_amdgcn_readlane(all, 63);
+        pre = __builtin_amdgcn_readlane(all - s, (int)uni((u32)wave()));
+      } else {
 #pragma unroll
-      for (int w = 0; w < kNW; ++w) {
-        u32 s = sh->wsum[w];
-        pre += (w < wave()) ? s : 0u;
-        tot += s;
+        for (int w = 0; w < kNW; ++w) {
+          u32 s = sh->wsum[w];
+          pre += (w < wave()) ? s : 0u;
+          tot += s;
+        }
       }
       __syncthreads();
       *total = uni(tot);
@@ -353,6 +362,7 @@ struct HostTeamT {
   static constexpr int kNT = 1;
   static constexpr int kNW = 1;
   static constexpr int kW = 1;
+  static constexpr int kME = 8;
   static constexpr int kE = 4;
   static constexpr int kM = 4;
   static constexpr bool kStage = STAGE;

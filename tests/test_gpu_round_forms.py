@@ -114,3 +114,28 @@ def test_batch_lists(nq):
         pkg.sssp_batch(qs, k_rule=pkg.K_FIXED, k_fixed=40, k_max=256, team=team)
         for q, ref in zip(qs, refs):
             assert np.array_equal(host64(q[6]), ref)
+
+
+@pytest.mark.parametrize("team", [256, 1024])
+@pytest.mark.parametrize("d", [101, 520, 1100, 4097])
+def test_staged_merges(team, d):
+    """Merges of HBM levels below, at and above whole and half tiles of the
+    staging area, and Select over up to 32 elements per thread."""
+    g = W.random_graph(4000, 90000, 0, 10 ** 6, d)
+    ref = oracle.dijkstra(g, 0)
+    dist, _ = run_sssp(pkg, g, 0, d=d, team=team, lds_levels=NO_LDS)
+    assert np.array_equal(dist, ref)
+    kseq = dev32(np.array([90, 1, 200, 7], np.uint32))
+    dist, _ = run_sssp(pkg, g, 0, d=d, team=team, lds_levels=NO_LDS, k_rule=pkg.K_SEQ, k_seq=kseq, k_max=256)
+    assert np.array_equal(dist, ref)
+
+
+@pytest.mark.parametrize("d", [100, 101, 159, 163, 167, 256, 257])
+def test_team_by_bulk_size(d):
+    g = W.ring_lattice(900, 30, 1, 1000, 3)
+    dist, st = run_sssp(pkg, g, 0, d=d)
+    assert np.array_equal(dist, oracle.dijkstra(g, 0))
+    _, one = run_sssp(pkg, g, 0, d=d, team=64)
+    assert st["lds_levels"] == one["lds_levels"] or d > 256
+    for s in SAME[:4]:
+        assert st[s] == one[s], s
