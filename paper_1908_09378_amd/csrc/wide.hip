@@ -651,23 +651,19 @@ __device__ __forceinline__ bool last_workgroup(u32* ctr, int* s_last) {
   return *s_last != 0;
 }
 
-// The workgroup-wide scratch of the Select kernels.
-struct SelShared {
-  u32 sw[ST / 64];
-  u64 swl[ST / 64], swh[ST / 64];
-  SelState q;
-};
+// The Select kernels' state is worked out by every wavefront for itself: a
+// barrier of 16 wavefronts costs about 0.4 us, and a gather that passed the
+// state through LDS had some twenty of them.
 
 // The start of a selection of rank r among n elements whose keys lie in the
-// given ranges: the bits the keys share are the prefix.  By the whole
-// workgroup, as sel_pick.
-__device__ __forceinline__ SelState sel_start(const Range* range, u32 nrange, u32 r, u32 n, SelShared& sh) {
+// given ranges: the bits the keys share are the prefix.
+__device__ __forceinline__ SelState sel_start(const Range* range, u32 nrange, u32 r, u32 n) {
   u64 lo = KINF, hi = 0;
-  for (u32 x = threadIdx.x; x < nrange; x += ST) {
+  for (u32 x = threadIdx.x & 63u; x < nrange; x += 64u) {
     lo = range[x].lo < lo ? range[x].lo : lo;
     hi = range[x].hi > hi ? range[x].hi : hi;
   }
-  block_minmax<ST>(lo, hi, sh.swl, sh.swh);
+  wave_minmax64(lo, hi);
   SelState q;
   if (lo == hi) {
     q.nb = 64;
@@ -685,46 +681,57 @@ __device__ __forceinline__ SelState sel_start(const Range* range, u32 nrange, u3
 }
 __device__ __forceinline__ int sel_width(const SelState& q) { return 96 - q.nb < SEL_BITS ? 96 - q.nb : SEL_BITS; }
 
-// The state after a pass over q's elements that counted hb of them in this
-// thread's bin (threads past SEL_BINS: 0): the bin that holds the rank goes
-// into the prefix.
-__device__ __forceinline__ SelState sel_pick(const SelState& q, u32 hb, u32 limit, SelShared& sh) {
+// The state after a pass over q's elements that counted h[b] of them in bin b
+// (four bins per lane): the bin that holds the rank goes into the prefix.
+template <class H>
+__device__ __forceinline__ SelState sel_pick(SelState q, H h, u32 limit) {
+  static_assert(SEL_BINS == 256, "four bins per lane");
   const int w = sel_width(q), p = 96 - q.nb - w;
-  u32 tot;
-  const u32 before = block_scan<ST>(hb, &tot, sh.sw);
-  SelState z = q;
-  if (threadIdx.x == 0 && (q.rank == 0 || q.rank > tot)) {
-    z.done = z.bad = 1;
-    sh.q = z;
+  const u32 lane = threadIdx.x & 63u;
+  u32 c[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) c[j] = h[4 * lane + j];
+  const u32 sum = c[0] + c[1] + c[2] + c[3], inc = wave_incl(sum);
+  const u64 m = __ballot(inc >= q.rank);
+  if (q.rank == 0 || m == 0) {
+    q.done = q.bad = 1;
+    return q;
   }
-  if (hb && before < q.rank && q.rank <= before + hb) {
-    const u32 b = threadIdx.x;
-    if (p >= 32) {
-      z.pk |= (u64)b << (p - 32);
-    } else {
-      u64 lo = ((z.pk & 0xFFFFFFFFull) << 32) | z.pv;
-      lo |= (u64)b << p;
-      z.pk = (z.pk & 0xFFFFFFFF00000000ull) | (lo >> 32);
-      z.pv = (u32)lo;
+  const int l = __builtin_ctzll(m);
+  u32 b = 0, before = 0, cnt = 0, run = __builtin_amdgcn_readlane(inc - sum, l);
+  bool found = false;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const u32 x = __builtin_amdgcn_readlane(c[j], l);
+    if (!found && q.rank <= run + x) {
+      b = 4u * (u32)l + (u32)j;
+      before = run;
+      cnt = x;
+      found = true;
     }
-    z.nb = q.nb + w;
-    z.rank = q.rank - before;
-    z.cnt = hb;
-    z.done = hb <= limit || z.nb == 96;
-    sh.q = z;
+    run += x;
   }
-  __syncthreads();
-  z = sh.q;
-  __syncthreads();
-  return z;
+  if (p >= 32) {
+    q.pk |= (u64)b << (p - 32);
+  } else {
+    u64 lo = ((q.pk & 0xFFFFFFFFull) << 32) | q.pv;
+    lo |= (u64)b << p;
+    q.pk = (q.pk & 0xFFFFFFFF00000000ull) | (lo >> 32);
+    q.pv = (u32)lo;
+  }
+  q.nb += w;
+  q.rank -= before;
+  q.cnt = cnt;
+  q.done = cnt <= limit || q.nb == 96;
+  return q;
 }
 
-// The state after `passes` passes of this step.  Every workgroup works it out
+// The state after `passes` passes of this step.  Every wavefront works it out
 // from the histograms (a pass whose last workgroup did so took 4 us more).
-__device__ __forceinline__ SelState sel_after(Ctl* c, SelState q, int passes, SelShared& sh, u32* npass) {
+__device__ __forceinline__ SelState sel_after(const Ctl* c, SelState q, int passes, u32* npass) {
   *npass = 0;
   for (int p = 0; p < passes && !q.done; ++p) {
-    q = sel_pick(q, threadIdx.x < SEL_BINS ? c->shist[p][threadIdx.x] : 0u, CANDMAX, sh);
+    q = sel_pick(q, &c->shist[p][0], CANDMAX);
     *npass += 1;
   }
   return q;
@@ -741,15 +748,14 @@ __device__ __forceinline__ SelState sel_after(Ctl* c, SelState q, int passes, Se
 __global__ __launch_bounds__(ST) void k_sel_pass(const u64* K, const u32* V, u32 n, Ctl* c, u32 r, int pass,
                                                  const Range* range, u32 nrange) {
   constexpr int CP = 4;
-  __shared__ SelShared sh;
   __shared__ u32 h[CP][SEL_BINS];
   SelState q;
   if (nrange) {
-    q = sel_start(range, nrange, r, n, sh);
+    q = sel_start(range, nrange, r, n);
     if (blockIdx.x == 0 && threadIdx.x == 0) c->q = q;
   } else {
     u32 np;
-    q = sel_after(c, c->q, pass, sh, &np);
+    q = sel_after(c, c->q, pass, &np);
   }
   if (q.done) return;
   const int w = sel_width(q), p = 96 - q.nb - w;
@@ -800,14 +806,13 @@ __device__ __forceinline__ void publish(Mail* mail, u32 seq) {
 __global__ __launch_bounds__(ST) void k_sel_collect(const u64* K, const u32* V, u32 n, Ctl* c, u32 r, int passes,
                                                     const Range* range, u32 nrange, u64* ck, u32* cv, Mail* box,
                                                     Mail* mail, u32 seq) {
-  __shared__ SelShared sh;
   __shared__ u64 sk[CANDMAX];
   __shared__ u32 sv[CANDMAX];
   __shared__ u32 h[SEL_BINS];
   __shared__ u32 s_n, s_base;
   __shared__ int s_last;
   u32 npass = 0;
-  SelState q = nrange ? sel_start(range, nrange, r, n, sh) : sel_after(c, c->q, passes, sh, &npass);
+  SelState q = nrange ? sel_start(range, nrange, r, n) : sel_after(c, c->q, passes, &npass);
   const bool go = q.done && !q.bad;
   if (threadIdx.x == 0) s_n = 0;
   __syncthreads();
@@ -881,8 +886,9 @@ __global__ __launch_bounds__(ST) void k_sel_collect(const u64* K, const u32* V, 
       if (sel_match(k, v, q.pk, q.pv, q.nb)) atomicAdd(&h[sel_digit(k, v, p, w)], 1u);
     }
     __syncthreads();
-    q = sel_pick(q, threadIdx.x < SEL_BINS ? h[threadIdx.x] : 0u, RANKED, sh);
+    q = sel_pick(q, &h[0], RANKED);
     bad = q.bad;
+    __syncthreads();  // (every wavefront has read the histogram)
   }
   __shared__ u64 fk[RANKED];
   __shared__ u32 fv[RANKED];
