@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <algorithm>
+#include <chrono>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -104,7 +105,10 @@ struct pbh {
   u64* ukeys = nullptr;
   u32* uids = nullptr;
   u64 ulist_cap = 0;
-  u64* flag = nullptr;
+  u64* flag = nullptr;      // device word of the batch check, zero between calls
+  u64* post_h = nullptr;    // its outcome in host-mapped memory
+  u64* post_d = nullptr;
+  u64 checks = 0;           // checks so far
   WideScratch* wide = nullptr;  // device-wide engine (state authoritative on the host)
 };
 
@@ -150,6 +154,26 @@ int pull_state(pbh* h) {
 int push_state(pbh* h) {
   if (h->wide) return PBH_OK;
   HIPCHK(hipMemcpy(h->gst, &h->host, sizeof(HeapState), hipMemcpyHostToDevice));
+  return PBH_OK;
+}
+
+// Checks a batch's ids (and keys, when given) on the device.  The outcome is
+// polled in host-mapped memory; should it not arrive within a second, the
+// stream is synchronised, which also reports a failed kernel.
+int check_batch(pbh* h, const u64* keys, const u32* ids, u64 count, bool* bad) {
+  const u64 seq = ++h->checks;
+  HIPCHK(launch_check_update(keys, ids, count, h->id_cap, h->flag, h->post_d, seq, 0));
+  u64 got = 0;
+  const auto ready = [&] { return ((got = __atomic_load_n(h->post_h, __ATOMIC_ACQUIRE)) >> 1) == seq; };
+  const auto t0 = std::chrono::steady_clock::now();
+  for (u32 spin = 1; !ready(); ++spin) {
+    if ((spin & 4095u) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::seconds(1)) {
+      HIPCHK(hipStreamSynchronize(0));
+      if (ready()) break;
+      return fail(PBH_EINTERNAL, "the check of a heap batch ended without publishing its outcome");
+    }
+  }
+  *bad = (got & 1u) != 0;
   return PBH_OK;
 }
 
@@ -248,13 +272,17 @@ int pbh_create_ex(pbh_t** out, uint32_t id_capacity, uint32_t d, const pbh_opts*
   if ((e = hipMalloc(&h->cur, (u64)id_capacity * sizeof(u64))) != hipSuccess ||
       (e = hipMalloc(&h->bitmap, (u64)h->nwords * sizeof(u32))) != hipSuccess ||
       (e = hipMalloc(&h->gst, sizeof(HeapState))) != hipSuccess ||
-      (e = hipMalloc(&h->flag, sizeof(u64))) != hipSuccess) {
+      (e = hipMalloc(&h->flag, sizeof(u64))) != hipSuccess ||
+      (e = hipHostMalloc(&h->post_h, sizeof(u64), hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess ||
+      (e = hipHostGetDevicePointer((void**)&h->post_d, h->post_h, 0)) != hipSuccess) {
     rc = fail(e == hipErrorOutOfMemory ? PBH_ENOMEM : PBH_EDEVICE, "pbh_create: %s", hipGetErrorString(e));
   }
   if (!rc) rc = arena_alloc(&h->arena, lvl_off(d, h->q));
   if (!rc) {
+    *h->post_h = 0;
     if (hipMemset(h->cur, 0xFF, (u64)id_capacity * sizeof(u64)) != hipSuccess ||
-        hipMemset(h->bitmap, 0, (u64)h->nwords * sizeof(u32)) != hipSuccess)
+        hipMemset(h->bitmap, 0, (u64)h->nwords * sizeof(u32)) != hipSuccess ||
+        hipMemset(h->flag, 0, sizeof(u64)) != hipSuccess)
       rc = fail(PBH_EDEVICE, "pbh_create: hipMemset failed");
   }
   if (!rc) {
@@ -281,6 +309,7 @@ int pbh_destroy(pbh_t* h) {
   if (h->ukeys) (void)hipFree(h->ukeys);
   if (h->uids) (void)hipFree(h->uids);
   if (h->flag) (void)hipFree(h->flag);
+  if (h->post_h) (void)hipHostFree(h->post_h);
   if (h->wide) wide_destroy(h->wide);
   arena_free(&h->arena);
   delete h;
@@ -292,10 +321,8 @@ int pbh_bulk_update(pbh_t* h, const uint64_t* keys, const uint32_t* ids, uint64_
   if (count == 0) return PBH_OK;
   if (!keys || !ids) return fail(PBH_EINVAL, "pbh_bulk_update: NULL arrays");
   if (h->host.err) return state_error(h->host);
-  HIPCHK(hipMemset(h->flag, 0, sizeof(u64)));
-  HIPCHK(launch_check_update((const u64*)keys, ids, count, h->id_cap, h->flag, 0));
-  u64 bad = 0;
-  HIPCHK(hipMemcpy(&bad, h->flag, sizeof(u64), hipMemcpyDeviceToHost));
+  bool bad = false;
+  if (int rc = check_batch(h, (const u64*)keys, ids, count, &bad)) return rc;
   if (bad) return fail(PBH_EINVAL, "pbh_bulk_update: id >= id_capacity or key == UINT64_MAX");
   u64 need = count < h->id_cap ? count : h->id_cap;
   if (need > h->ulist_cap) {
@@ -345,10 +372,8 @@ int pbh_delete(pbh_t* h, const uint32_t* ids, uint64_t count) {
   if (count == 0) return PBH_OK;
   if (!ids) return fail(PBH_EINVAL, "pbh_delete: NULL ids");
   if (h->host.err) return state_error(h->host);
-  HIPCHK(hipMemset(h->flag, 0, sizeof(u64)));
-  HIPCHK(launch_check_update(nullptr, ids, count, h->id_cap, h->flag, 0));
-  u64 bad = 0;
-  HIPCHK(hipMemcpy(&bad, h->flag, sizeof(u64), hipMemcpyDeviceToHost));
+  bool bad = false;
+  if (int rc = check_batch(h, nullptr, ids, count, &bad)) return rc;
   if (bad) return fail(PBH_EINVAL, "pbh_delete: id >= id_capacity");
   if (h->wide) {
     WideHeap w = wide_view(h);

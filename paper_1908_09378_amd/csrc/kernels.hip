@@ -43,11 +43,34 @@ __global__ void k_zero_u64(u64* p, u64 n) {
   for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (u64)gridDim.x * blockDim.x) p[i] = 0;
 }
 
-__global__ void k_check_update(const u64* keys, const u32* ids, u64 count, u32 id_cap, u64* bad) {
-  u64 b = 0;
-  for (u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (u64)gridDim.x * blockDim.x)
-    if (ids[i] >= id_cap || (keys && keys[i] == KINF)) b = 1;
-  if (b) atomicOr(bad, 1ull);
+// The batch's ids and keys checked, the outcome posted to the host: `word`
+// counts the workgroups that have ended (low half) and those that found
+// something bad (high half); the last one posts seq * 2 + (any bad) in
+// host-mapped memory and leaves the word zero.  (Cleared and read back by the
+// runtime, the flag cost a batch of 256 some 20 us; each workgroup's atomic on
+// the word takes about 10 ns, hence at most CHECK_WG of them.)
+constexpr u32 CHECK_T = 512, CHECK_WG = 256;
+__global__ __launch_bounds__(CHECK_T) void k_check_update(const u64* keys, const u32* ids, u64 count, u32 id_cap,
+                                                          u64* word, u64* post, u64 seq) {
+  constexpr int R = 4;
+  const u64 step = (u64)gridDim.x * CHECK_T;
+  int b = 0;
+  for (u64 i0 = (u64)blockIdx.x * CHECK_T + threadIdx.x; i0 < count; i0 += R * step) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const u64 i = i0 + r * step < count ? i0 + r * step : i0;
+      b |= ids[i] >= id_cap;
+      if (keys) b |= keys[i] == KINF;
+    }
+  }
+  b = __syncthreads_or(b);
+  if (threadIdx.x != 0) return;
+  const u64 mine = 1ull | (b ? 1ull << 32 : 0ull);
+  const u64 all =
+      __hip_atomic_fetch_add((u64 PBH_GLB*)word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + mine;
+  if ((u32)all != gridDim.x) return;
+  __hip_atomic_store((u64 PBH_GLB*)word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(post, seq * 2 + (all >> 32 != 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // One query, one workgroup: the round loop with every k rule (SPEC) or the
@@ -148,9 +171,11 @@ hipError_t launch_check_csr(const u64* off, const u32* tg, u32 n, u64 m, CsrChec
   return hipGetLastError();
 }
 
-hipError_t launch_check_update(const u64* keys, const u32* ids, u64 count, u32 id_cap, u64* bad,
+hipError_t launch_check_update(const u64* keys, const u32* ids, u64 count, u32 id_cap, u64* word, u64* post, u64 seq,
                                hipStream_t s) {
-  hipLaunchKernelGGL(k_check_update, dim3(grid_for(count, 256)), dim3(256), 0, s, keys, ids, count, id_cap, bad);
+  const u64 wg = (count + CHECK_T - 1) / CHECK_T;
+  hipLaunchKernelGGL(k_check_update, dim3(wg < CHECK_WG ? (u32)wg : CHECK_WG), dim3(CHECK_T), 0, s, keys, ids, count,
+                     id_cap, word, post, seq);
   return hipGetLastError();
 }
 

@@ -60,7 +60,7 @@ hipError_t launch_pbh_extract(const PbhParams& p, hipStream_t s);
 hipError_t launch_pbh_delete(const PbhParams& p, hipStream_t s);
 hipError_t launch_mlp_infer(int team, const float* X, u32 n, const float* blob, float* y, hipStream_t s);
 // keys may be NULL (a delete batch: ids only).
-hipError_t launch_check_update(const u64* keys, const u32* ids, u64 count, u32 id_cap, u64* bad,
+hipError_t launch_check_update(const u64* keys, const u32* ids, u64 count, u32 id_cap, u64* word, u64* post, u64 seq,
                                hipStream_t s);
 
 }  // namespace bkt

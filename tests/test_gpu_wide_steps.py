@@ -65,3 +65,26 @@ def test_growth_between_steps():
     """More elements than the first levels hold: the arena and the scratch grow
     while B_0 keeps its key range."""
     run(1 << 20, 1024, "crowded", [1 << 16, 1 << 18, 1 << 20, 5, 1 << 19], [2000, 1, 70000], 100, 9)
+
+
+@pytest.mark.parametrize("engine", [pkg.ENGINE_TEAM, pkg.ENGINE_WIDE])
+@pytest.mark.parametrize("n", [1, 511, 513, 131072, 524289])
+def test_batch_check(engine, n):
+    """One bad pair anywhere in a batch refuses it whole, and the next call is
+    judged by its own batch."""
+    h = pkg.Heap(n, 4096, engine)
+    keys, ids = np.arange(n, dtype=np.uint64), np.arange(n, dtype=np.uint32)
+    for at in sorted({0, n // 2, n - 1}):
+        bad = ids.copy()
+        bad[at] = n
+        low = keys.copy()
+        low[at] = (1 << 64) - 1
+        for call in (lambda: h.bulk_update(dev64(keys), dev32(bad)), lambda: h.bulk_update(dev64(low), dev32(ids)),
+                     lambda: h.delete(dev32(bad))):
+            with pytest.raises(pkg.PBHError) as e:
+                call()
+            assert e.value.code == pkg.PBH_EINVAL
+        h.delete(dev32(ids))
+        assert h.size() == 0
+    h.bulk_update(dev64(keys), dev32(ids))
+    assert h.size() == n
