@@ -314,8 +314,8 @@ struct MArgs {
 // at index o + o/8 so that the threads' runs of WE spread over the banks) and
 // stored coalesced.  Stored straight from the walk, each store instruction
 // would touch 64 cache lines (a thread's outputs are consecutive), which
-// measured 1.6x slower.  The key range goes into ctl by atomics, of which
-// nearly all are spared by a look at the range so far.
+// measured 1.6x slower.  The key range goes into the group's Range by atomics,
+// of which nearly all are spared by a look at the range so far.
 template <bool WRITE, bool KEYS = WRITE>
 __global__ __launch_bounds__(NT) void k_merge(MArgs a, u32* part, Pass ps) {
   static_assert(KEYS || !WRITE, "the writing pass stages keys");
