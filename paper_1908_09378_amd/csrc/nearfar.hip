@@ -40,426 +40,75 @@
 #include <mutex>
 
 #include "../../include/pbh.h"
+#include "nearfar_core.h"
 #include "pbh_team.h"
 
 namespace bkt {
 namespace nf {
 
-constexpr u64 KINF = ~0ull;
-constexpr u32 NONE = ~0u;
 constexpr int NT = 512;          // threads per workgroup
 constexpr u32 HEAVY = 1024;      // out-degree above which a vertex is scanned by the whole grid
-constexpr u32 PUSHES = 4096;     // near / far pushes gathered per workgroup before they are written out
-constexpr u64 TIMEOUT_TICKS = 2000000000ull;  // 20 s of the 100 MHz real-time clock
-constexpr u64 RUN_LIMIT_TICKS = 12000000000ull;  // 120 s: a run that long is stopped
 
-enum { RELAX = 0, SPLIT = 1, DONE = 2 };
-enum { ERR_TIMEOUT = 1, ERR_OVERFLOW = 2, ERR_PHASES = 4 };
-
-// Phase descriptor, written by the barrier's leader.
-struct Phase {
-  u32 mode;
-  u32 src, dst;     // near queues read (relax) and written
-  u32 nl, nh;       // relax: light and heavy vertices in queue src
-  u32 fsrc, fdst;   // far piles: split reads fsrc; relax and split append to fdst
-  u32 nf;           // split: entries of fsrc
-  u32 phase;        // stamp of near pushes in this phase
-  u32 epoch;        // stamp of far pushes
-  u64 T;            // threshold
-  u64 t0;           // real-time clock at the first barrier
+// The GPU's grid: agent-scope accesses, since the XCDs' L2 caches are not
+// coherent for plain ones.
+struct DevGrid {
+  static constexpr int NT = nf::NT, W = 64;
+  static constexpr u32 HEAVY = nf::HEAVY;
+  static constexpr u32 PUSHES = 4096;  // near / far pushes gathered per workgroup before they are written out
+  using Word = u32;
+  __device__ __forceinline__ u32 tid() const { return threadIdx.x; }
+  __device__ __forceinline__ u32 wg() const { return blockIdx.x; }
+  __device__ __forceinline__ u32 nwg() const { return gridDim.x; }
+  __device__ __forceinline__ void sync() const { __syncthreads(); }
+  __device__ __forceinline__ void wait_mem() const { __builtin_amdgcn_s_waitcnt(0); }
+  __device__ __forceinline__ void nap() const { __builtin_amdgcn_s_sleep(2); }
+  __device__ __forceinline__ u64 clock() const { return __builtin_amdgcn_s_memrealtime(); }
+  __device__ __forceinline__ u32 ld32(const u32* p) const {
+    return __hip_atomic_load((const u32 PBH_GLB*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ u64 ld64(const u64* p) const {
+    return __hip_atomic_load((const u64 PBH_GLB*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ void st32(u32* p, u32 v) const {
+    __hip_atomic_store((u32 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ void st64(u64* p, u64 v) const {
+    __hip_atomic_store((u64 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ u32 xchg32(u32* p, u32 v) const {
+    return __hip_atomic_exchange((u32 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ u32 add32(u32* p, u32 v) const {
+    return __hip_atomic_fetch_add((u32 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ u32 or32(u32* p, u32 v) const {
+    return __hip_atomic_fetch_or((u32 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ u64 min64(u64* p, u64 v) const {
+    return __hip_atomic_fetch_min((u64 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // *p++ and *p = min(*p, v) in LDS
+  __device__ __forceinline__ u32 lds_next(u32* p) const {
+    return __hip_atomic_fetch_add((u32 PBH_LDS*)p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __device__ __forceinline__ void lds_min(u64* p, u64 v) const {
+    __hip_atomic_fetch_min((u64 PBH_LDS*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  __device__ __forceinline__ u32 wave_max(u32 x) const {
+    for (int o = 32; o > 0; o >>= 1) {
+      const u32 y = (u32)__shfl_xor((int)x, o, 64);
+      x = y > x ? y : x;
+    }
+    return x;
+  }
 };
-
-// Words that different workgroups update at the same time are lines apart.
-struct alignas(128) Line {
-  u32 w;
-  u32 pad_[31];
-};
-struct Ctl {
-  Line arrive[9], gen, err;  // arrivals at a barrier: per group of workgroups, then of the groups
-  Line cl[2], ch[2];  // near queue sizes (light, heavy)
-  Line cf[2];         // far pile sizes
-  alignas(128) u64 fmin[2];  // smallest key filed in each far pile
-  alignas(128) u64 relax;    // edges scanned
-  alignas(128) u32 phases;   // phases ended (also a sign of life)
-  Phase ph;
-};
-
-struct Args {
-  const u64* off;
-  const u32* tg;
-  const u32* wt;
-  u64* dist;
-  u32 n;
-  u64 delta;
-  u32 glog;         // light vertices: groups of 2^glog lanes
-  u32* ql[2];       // near queues, light vertices
-  u32* qh[2];       // near queues, heavy vertices
-  u32* far[2];      // far piles
-  u32* nstamp;      // per vertex: phase of its last near push
-  u32* fstamp;      // per vertex: epoch of its last far filing
-  u64* done_at;     // per vertex: the distance at which its edges were last scanned
-  u32 cap;          // capacity of every queue and pile
-  u32 heavy;        // some vertex has more than HEAVY out-edges
-  u32 solo;         // frontiers of at most this many vertices are one workgroup's
-  u32 max_phases;
-  Ctl* c;
-};
-
-__device__ __forceinline__ u32 ld32(const u32* p) {
-  return __hip_atomic_load((const u32 PBH_GLB*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ u64 ld64(const u64* p) {
-  return __hip_atomic_load((const u64 PBH_GLB*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st32(u32* p, u32 v) {
-  __hip_atomic_store((u32 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st64(u64* p, u64 v) {
-  __hip_atomic_store((u64 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ u32 xchg32(u32* p, u32 v) {
-  return __hip_atomic_exchange((u32 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ u64 xchg64(u64* p, u64 v) {
-  return __hip_atomic_exchange((u64 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ u32 add32(u32* p, u32 v) {
-  return __hip_atomic_fetch_add((u32 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ u64 min64(u64* p, u64 v) {
-  return __hip_atomic_fetch_min((u64 PBH_GLB*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Pushes gathered in LDS: light near vertices from the front, far ones from
-// the back, and the smallest far key (heavy vertices, rare, go out one by one).
-struct Gather {
-  u32 buf[PUSHES];
-  u32 nn, nf, slot_n, slot_f;
-  u64 fmin;
-};
-
-__device__ __forceinline__ void overflow(const Args& a) {
-  __hip_atomic_fetch_or((u32 PBH_GLB*)&a.c->err.w, (u32)ERR_OVERFLOW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Writes the gathered pushes out (every thread of the workgroup calls it).
-__device__ __forceinline__ void flush(const Args& a, const Phase& ph, Gather* q) {
-  __syncthreads();
-  const u32 nn = q->nn, nf = q->nf;
-  if (nn + nf) {
-    if (threadIdx.x == 0) {
-      q->slot_n = nn ? add32(&a.c->cl[ph.dst].w, nn) : 0u;
-      q->slot_f = nf ? add32(&a.c->cf[ph.fdst].w, nf) : 0u;
-      if (nf) min64(&a.c->fmin[ph.fdst], q->fmin);
-    }
-    __syncthreads();
-    const u32 sn = q->slot_n, sf = q->slot_f;
-    for (u32 x = threadIdx.x; x < nn; x += NT) {
-      if (sn + x < a.cap)
-        st32(a.ql[ph.dst] + sn + x, q->buf[x]);
-      else
-        overflow(a);
-    }
-    for (u32 x = threadIdx.x; x < nf; x += NT) {
-      if (sf + x < a.cap)
-        st32(a.far[ph.fdst] + sf + x, q->buf[PUSHES - 1 - x]);
-      else
-        overflow(a);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      q->nn = q->nf = 0;
-      q->fmin = KINF;
-    }
-  }
-  __syncthreads();
-}
-
-// Files vertex v with key `key` (improved in this phase): near (below T) or
-// far, each at most once per phase / epoch.  Between two flushes a workgroup
-// files at most PUSHES vertices (room()).
-__device__ __forceinline__ void file(const Args& a, const Phase& ph, Gather* q, bool imp, u32 v, u64 key) {
-  const bool near = imp && key < ph.T;
-  const bool fresh_near = near && xchg32(a.nstamp + v, ph.phase) != ph.phase;
-  const bool fresh_far = imp && !near && xchg32(a.fstamp + v, ph.epoch) != ph.epoch;
-  bool heavy = false;
-  if (a.heavy && fresh_near) heavy = a.off[v + 1] - a.off[v] > HEAVY;
-  if (heavy) {
-    const u32 s = add32(&a.c->ch[ph.dst].w, 1u);
-    if (s < a.cap)
-      st32(a.qh[ph.dst] + s, v);
-    else
-      overflow(a);
-  } else if (fresh_near) {
-    q->buf[__hip_atomic_fetch_add((u32 PBH_LDS*)&q->nn, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] = v;
-  }
-  if (fresh_far) {
-    q->buf[PUSHES - 1 -
-           __hip_atomic_fetch_add((u32 PBH_LDS*)&q->nf, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] = v;
-    __hip_atomic_fetch_min((u64 PBH_LDS*)&q->fmin, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  }
-}
-
-// Makes sure the next file() of every thread finds room (each files at most
-// one vertex).  `left` counts the calls that are sure to fit; every thread of
-// the workgroup has the same value and makes the same calls, so the barriers
-// are only passed when it runs out, by all of them.
-__device__ __forceinline__ void room(const Args& a, const Phase& ph, Gather* q, u32& left) {
-  if (left == 0) {
-    __syncthreads();
-    const u32 used = q->nn + q->nf;
-    __syncthreads();  // (no push before every thread has read it)
-    if (used + NT > PUSHES) {
-      flush(a, ph, q);
-      left = PUSHES / NT;
-    } else {
-      left = (PUSHES - used) / NT;
-    }
-  }
-  --left;
-}
-
-// Relaxes edge e out of a vertex at distance du; files an improved target.
-__device__ __forceinline__ void relax_edge(const Args& a, const Phase& ph, Gather* q, bool in, u64 e, u64 du) {
-  u32 v = 0;
-  u64 cand = 0;
-  bool imp = false;
-  if (in) {
-    v = a.tg[e];
-    cand = du + (u64)a.wt[e];
-    imp = cand < min64(a.dist + v, cand);
-  }
-  file(a, ph, q, imp, v, cand);
-}
-
-// Leader of a grid barrier: turns the queue sizes of the phase that ended
-// into the next phase's descriptor (every other workgroup is waiting).
-__device__ void lead(const Args& a, Phase& ph) {
-  // The phase that ended tells where its results are, so everything read
-  // here is read at once: one round trip.
-  Ctl* c = a.c;
-  const u32 d = ph.dst, f = ph.fdst;
-  const u32 nl = ld32(&c->cl[d].w), nh = ld32(&c->ch[d].w), nf = ld32(&c->cf[f].w);
-  const u64 fm = ld64(&c->fmin[f]);
-  const u32 phases = ph.phase + 1;
-  st32(&c->phases, phases);
-  const u64 now = __builtin_amdgcn_s_memrealtime();
-  if (ph.t0 == 0) ph.t0 = now;
-  if (phases > a.max_phases || now - ph.t0 > RUN_LIMIT_TICKS) {
-    __hip_atomic_fetch_or((u32 PBH_GLB*)&c->err.w, (u32)ERR_PHASES, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    ph.mode = DONE;
-    return;
-  }
-  ph.phase += 1;
-  if (nl + nh > 0) {
-    ph.mode = RELAX;
-    ph.src = d;
-    ph.dst = d ^ 1;
-    ph.nl = nl < a.cap ? nl : a.cap;
-    ph.nh = nh < a.cap ? nh : a.cap;
-    st32(&c->cl[d ^ 1].w, 0u);
-    st32(&c->ch[d ^ 1].w, 0u);
-    return;
-  }
-  if (nf == 0) {
-    ph.mode = DONE;
-    return;
-  }
-  // Next threshold: one Delta further, or the first multiple of Delta past
-  // the smallest key filed in the far pile if that is further.
-  u64 t = ph.T + a.delta < ph.T ? KINF : ph.T + a.delta;
-  if (fm != KINF) {
-    const u64 j = (fm / a.delta + 1) * a.delta;
-    const u64 jt = j < fm ? KINF : j;  // saturate
-    t = jt > t ? jt : t;
-  }
-  ph.T = t;
-  ph.mode = SPLIT;
-  ph.dst = d;  // empty: the relax phase that ended filed nothing near
-  ph.fsrc = f;
-  ph.fdst = f ^ 1;
-  ph.nf = nf < a.cap ? nf : a.cap;
-  ph.epoch += 1;
-  st32(&c->cf[f ^ 1].w, 0u);
-  st64(&c->fmin[f ^ 1], KINF);
-}
-
-// One phase's work by `nwg` workgroups, this one being number `wg` of them.
-__device__ __forceinline__ void do_phase(const Args& a, const Phase& ph, Gather* q, u32 wg, u32 nwg, u64& scanned) {
-  const u32 G = 1u << a.glog;
-  const u32 gtid = wg * NT + threadIdx.x;
-  const u32 nthreads = nwg * NT;
-  const u32 sub = gtid >> a.glog, nsub = nthreads >> a.glog, lig = threadIdx.x & (G - 1);
-  u32 left = PUSHES / NT;  // the gather starts empty
-  if (ph.mode == RELAX) {
-    // light vertices: one group of G lanes per vertex, striding its edges
-    const u32 rounds_l = (ph.nl + nsub - 1) / nsub;
-    for (u32 r = 0; r < rounds_l; ++r) {
-      const u32 j = r * nsub + sub;
-      bool have = j < ph.nl;
-      const u32 u = have ? ld32(a.ql[ph.src] + j) : 0u;
-      // a vertex is in the queue once, so its last-scan mark is this group's
-      // alone in this phase (no exchange needed)
-      const u64 du = have ? ld64(a.dist + u) : 0ull, seen = have ? ld64(a.done_at + u) : 0ull;
-      const u64 r0 = have ? a.off[u] : 0ull, r1 = have ? a.off[u + 1] : 0ull;
-      have = have && seen != du;  // already scanned at this distance (filed twice): skipped
-      if (have && lig == 0) st64(a.done_at + u, du);
-      const u64 e0 = have ? r0 : 0ull, e1 = have ? r1 : 0ull;
-      const u64 deg = e1 - e0;
-      scanned += lig == 0 ? deg : 0;
-      // every wavefront of the workgroup runs the same number of steps (the
-      // largest degree in it): room() counts them
-      u32 steps = (u32)((deg + G - 1) / G);
-      for (int o = 32; o > 0; o >>= 1) {
-        const u32 s2 = (u32)__shfl_xor((int)steps, o, 64);
-        steps = s2 > steps ? s2 : steps;
-      }
-      __shared__ u32 ws[NT / 64];
-      if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = steps;
-      __syncthreads();
-#pragma unroll
-      for (int w = 0; w < NT / 64; ++w) steps = ws[w] > steps ? ws[w] : steps;
-      for (u32 s = 0; s < steps; ++s) {
-        room(a, ph, q, left);
-        const u64 e = e0 + (u64)s * G + lig;
-        relax_edge(a, ph, q, e < e1, e, du);
-      }
-      __syncthreads();
-    }
-    // heavy vertices: every workgroup takes a share of each one's edges
-    // (always scanned: every workgroup would have to agree on a skip)
-    for (u32 h = 0; h < ph.nh; ++h) {
-      const u32 u = ld32(a.qh[ph.src] + h);
-      const u64 du = ld64(a.dist + u);
-      const u64 e0 = a.off[u], e1 = a.off[u + 1];
-      if (gtid == 0) scanned += e1 - e0;
-      const u64 span = e1 - e0;
-      const u64 steps = (span + nthreads - 1) / nthreads;
-      for (u64 s = 0; s < steps; ++s) {
-        room(a, ph, q, left);
-        const u64 e = e0 + s * nthreads + gtid;
-        relax_edge(a, ph, q, e < e1, e, du);
-      }
-    }
-  } else {  // SPLIT: far vertices now below T become the near frontier
-    const u32 rounds_f = (ph.nf + nthreads - 1) / nthreads;
-    for (u32 r = 0; r < rounds_f; ++r) {
-      room(a, ph, q, left);
-      const u32 j = r * nthreads + gtid;
-      const bool have = j < ph.nf;
-      const u32 v = have ? ld32(a.far[ph.fsrc] + j) : 0u;
-      const u64 dv = have ? ld64(a.dist + v) : KINF;
-      file(a, ph, q, have, v, dv);
-    }
-  }
-  flush(a, ph, q);
-}
-
-// Is the phase one workgroup's work?
-__device__ __forceinline__ bool solo(const Args& a, const Phase& ph) {
-  return ph.mode == RELAX ? ph.nh == 0 && ph.nl <= a.solo : ph.mode == SPLIT && ph.nf <= NT;
-}
-
-// Grid barrier.  Every thread first waits for its own memory operations;
-// one arrival per workgroup; the last one runs lead(), then the small phases
-// that follow, and bumps the generation the others spin on.  Returns false
-// once the run has failed.
-__device__ bool grid_sync(const Args& a, Phase& ph, Phase* sph, u32* sflag, Gather* q, u64& scanned) {
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  Ctl* c = a.c;
-  if (threadIdx.x == 0) {
-    const u32 g = ld32(&c->gen.w);
-    // one word takes about 10 ns per arrival: eight groups, then their last
-    // ones (workgroups go round the dies, so a group is a die's)
-    const u32 grp = blockIdx.x & 7u, ngrp = gridDim.x < 8u ? gridDim.x : 8u;
-    bool last = add32(&c->arrive[grp].w, 1u) == (gridDim.x - grp + 7u) / 8u - 1u;
-    if (last) {
-      st32(&c->arrive[grp].w, 0u);
-      last = add32(&c->arrive[8].w, 1u) == ngrp - 1u;
-    }
-    if (last) {
-      st32(&c->arrive[8].w, 0u);
-      lead(a, ph);
-      *sph = ph;
-      *sflag = 2;
-    } else {
-      u64 t0 = __builtin_amdgcn_s_memrealtime();
-      u32 at = ld32(&c->phases);
-      while (ld32(&c->gen.w) == g) {
-        if (ld32(&c->err.w)) break;
-        if (__builtin_amdgcn_s_memrealtime() - t0 > TIMEOUT_TICKS) {
-          // the last workgroup may be at small phases of its own: it is alive
-          // while it counts them
-          const u32 now = ld32(&c->phases);
-          if (now != at) {
-            at = now;
-            t0 = __builtin_amdgcn_s_memrealtime();
-            continue;
-          }
-          __hip_atomic_fetch_or((u32 PBH_GLB*)&c->err.w, (u32)ERR_TIMEOUT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          break;
-        }
-        __builtin_amdgcn_s_sleep(2);
-      }
-      const u32* gp = reinterpret_cast<const u32*>(&c->ph);
-      u32* d = reinterpret_cast<u32*>(&ph);
-      for (u32 i = 0; i < sizeof(Phase) / 4; ++i) d[i] = ld32(gp + i);
-      *sph = ph;
-      *sflag = ld32(&c->err.w) ? 1 : 0;
-    }
-  }
-  __syncthreads();
-  ph = *sph;
-  if (*sflag == 2) {
-    u32 bad = 0;
-    while (solo(a, ph)) {
-      do_phase(a, ph, q, 0u, 1u, scanned);
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        *sflag = ld32(&c->err.w);
-        if (!*sflag) lead(a, ph);
-        *sph = ph;
-      }
-      __syncthreads();
-      ph = *sph;
-      bad = *sflag;
-      __syncthreads();
-      if (bad) break;
-    }
-    if (threadIdx.x == 0) {
-      u32* src = reinterpret_cast<u32*>(&ph);
-      u32* dstp = reinterpret_cast<u32*>(&c->ph);
-      for (u32 i = 0; i < sizeof(Phase) / 4; ++i) st32(dstp + i, src[i]);
-      __builtin_amdgcn_s_waitcnt(0);
-      st32(&c->gen.w, ld32(&c->gen.w) + 1u);
-      *sflag = ld32(&c->err.w) ? 1 : 0;
-    }
-    __syncthreads();
-  }
-  return *sflag == 0;
-}
 
 __global__ __launch_bounds__(NT) void k_nearfar(Args a) {
   __shared__ Phase sph;
   __shared__ u32 sflag;
-  __shared__ Gather q;
-  Phase ph;
-  if (threadIdx.x == 0) {
-    const u32* gp = reinterpret_cast<const u32*>(&a.c->ph);
-    u32* d = reinterpret_cast<u32*>(&sph);
-    for (u32 i = 0; i < sizeof(Phase) / 4; ++i) d[i] = ld32(gp + i);
-    q.nn = q.nf = 0;
-    q.fmin = KINF;
-  }
-  __syncthreads();
-  ph = sph;
-  u64 scanned = 0;
-  while (ph.mode != DONE) {
-    do_phase(a, ph, &q, blockIdx.x, gridDim.x, scanned);
-    if (!grid_sync(a, ph, &sph, &sflag, &q, scanned)) break;
-  }
+  __shared__ Gather<DevGrid> q;
+  const DevGrid t;
+  u64 scanned = phases(t, a, &sph, &sflag, &q);
   for (int o = 32; o > 0; o >>= 1) scanned += __shfl_xor(scanned, o, 64);
   if (scanned && (threadIdx.x & 63) == 0)
     __hip_atomic_fetch_add((u64 PBH_GLB*)&a.c->relax, scanned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -1,5 +1,6 @@
-"""ctypes driver for tests/hostmodel/hostmodel.hip: the GPU kernels' heap and
-parDijkstra logic instantiated with a one-thread team on the CPU (tests only)."""
+"""ctypes drivers of the CPU models of the GPU kernels' code (tests only):
+hostmodel.hip (heap and parDijkstra logic, a one-thread team) and
+nearfar_model.hip (Near-Far's phases, workgroups of fibers)."""
 import ctypes as C
 import os
 import subprocess
@@ -8,23 +9,32 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _SRC = os.path.join(_HERE, "hostmodel.hip")
-_CORE = [os.path.join(_HERE, "..", "..", "paper_1908_09378_amd", "csrc", f) for f in ("pbh_core.h", "pbh_team.h")]
+_CSRC = os.path.join(_HERE, "..", "..", "paper_1908_09378_amd", "csrc")
+_CORE = [os.path.join(_CSRC, f) for f in ("pbh_core.h", "pbh_team.h")]
 INF = np.uint64(0xFFFFFFFFFFFFFFFF)
 _lib = {}
 
 
-def build(sanitize: bool = False) -> str:
-    out = os.path.join(_HERE, "libhostmodel_asan.so" if sanitize else "libhostmodel.so")
-    newest = max(os.path.getmtime(p) for p in [_SRC] + _CORE)
+def _compile(src, deps, out, flags=()):
+    newest = max(os.path.getmtime(p) for p in [src] + deps)
     if not os.path.exists(out) or os.path.getmtime(out) < newest:
         cmd = ["hipcc", "-O2", "-g", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",
-               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-        if sanitize:
-            cmd += ["-Xarch_host", "-fsanitize=address,undefined"]
+               "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", *flags]
         tmp = out + f".tmp{os.getpid()}"
-        subprocess.check_call(cmd + [_SRC, "-o", tmp], stderr=subprocess.DEVNULL)
+        subprocess.check_call(cmd + [src, "-o", tmp], stderr=subprocess.DEVNULL)
         os.replace(tmp, out)
     return out
+
+
+def build(sanitize: bool = False) -> str:
+    out = os.path.join(_HERE, "libhostmodel_asan.so" if sanitize else "libhostmodel.so")
+    return _compile(_SRC, _CORE, out, ["-Xarch_host", "-fsanitize=address,undefined"] if sanitize else [])
+
+
+def build_nearfar() -> str:
+    return _compile(os.path.join(_HERE, "nearfar_model.hip"),
+                    [os.path.join(_HERE, "fibers.h"), os.path.join(_CSRC, "nearfar_core.h")],
+                    os.path.join(_HERE, "libnearfar_model.so"))
 
 
 def _asan_runtime_loaded() -> bool:
@@ -155,3 +165,29 @@ def sssp(g, src, d=0, sched=0, hcap=0, qlds=0, rule=0, kfix=0, kmax=0, kseq=None
                           first_bad=int(st[22].astype(np.int64)), violation=st[23:26].tolist(),
                           last_key=int(st[26]), stopped=bool(st[27]), worker_runs=int(st[28]),
                           deep_lim=int(st[29]))
+
+
+_nf = None
+ROUND_ROBIN, PRIORITY = 0, 1       # schedules of the fibers
+MISMATCH, HANG = -100, -101        # barrier passed out of step / no end
+
+
+def nearfar(g, src, delta, glog=0, workgroups=3, schedule=ROUND_ROBIN, late_stores=False, seed=1, max_steps=3_000_000):
+    """A Near-Far run on workgroups of 4 threads (wavefronts of 2) whose
+    accesses to shared memory interleave as `schedule` and `seed` say; vertices
+    are scanned by groups of 2^glog lanes.  Returns (0, MISMATCH, HANG or the
+    run's error word, distances)."""
+    global _nf
+    if _nf is None:
+        _nf = C.CDLL(build_nearfar())
+        u64p, u32p = C.POINTER(C.c_uint64), C.POINTER(C.c_uint32)
+        _nf.nfm_run.restype = C.c_int
+        _nf.nfm_run.argtypes = [u64p, u32p, u32p, C.c_uint32, C.c_uint32, C.c_uint64, C.c_uint32, C.c_uint32, C.c_int,
+                                C.c_int, C.c_uint64, C.c_uint64, u64p]
+    off = np.ascontiguousarray(g.offsets, np.uint64)
+    tg = np.ascontiguousarray(g.targets, np.uint32)
+    wt = np.ascontiguousarray(g.weights, np.uint32)
+    dist = np.zeros(g.n, np.uint64)
+    rc = _nf.nfm_run(_p(off, C.c_uint64), _p(tg, C.c_uint32), _p(wt, C.c_uint32), g.n, src, delta, glog, workgroups,
+                     schedule, int(late_stores), seed, max_steps, _p(dist, C.c_uint64))
+    return rc, dist

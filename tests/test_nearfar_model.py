@@ -1,0 +1,23 @@
+"""Near-Far's phases and grid barrier on the CPU (tests/hostmodel/
+nearfar_model.hip): the kernel's code on workgroups of 4 threads, interleaved
+at every access to shared memory."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+import hostmodel as hm
+
+# light and heavy vertices (more than 6 out-edges), frontiers of one and of
+# several workgroups, more pushes than a workgroup gathers (8)
+GRAPHS = [W.grid4(6, 6, 1, 5, 3), W.random_graph(40, 160, 0, 9, 3), W.random_graph(60, 600, 1, 20, 4), W.path_graph(12)]
+
+
+@pytest.mark.parametrize("gi", range(len(GRAPHS)))
+@pytest.mark.parametrize("workgroups", [1, 3, 10])
+@pytest.mark.parametrize("glog", [0, 1])
+@pytest.mark.parametrize("delta", [1, 4, 1 << 40])
+def test_threads_in_turn(gi, workgroups, glog, delta):
+    g = GRAPHS[gi]
+    rc, dist = hm.nearfar(g, 0, delta, glog, workgroups)
+    assert rc == 0 and np.array_equal(dist, oracle.dijkstra(g, 0))
