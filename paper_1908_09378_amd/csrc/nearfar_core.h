@@ -364,7 +364,11 @@ __host__ __device__ inline bool grid_sync(const E& t, const Args& a, Phase& ph, 
   }
   t.sync();
   ph = *sph;
-  if (*sflag == 2) {
+  const u32 flag = *sflag;
+  if (flag == 2) {
+    // (every wavefront has read the flag before thread 0 writes it again: one
+    // that read it late would pass by this block and its barriers)
+    t.sync();
     u32 bad = 0;
     while (solo<E>(a, ph)) {
       do_phase(t, a, ph, q, 0u, 1u, scanned);
@@ -390,8 +394,9 @@ __host__ __device__ inline bool grid_sync(const E& t, const Args& a, Phase& ph, 
       *sflag = t.ld32(&c->err.w) ? 1 : 0;
     }
     t.sync();
+    return *sflag == 0;
   }
-  return *sflag == 0;
+  return flag == 0;
 }
 
 // The run: phase after phase until the leader says DONE or the run has failed;

@@ -21,3 +21,17 @@ def test_threads_in_turn(gi, workgroups, glog, delta):
     g = GRAPHS[gi]
     rc, dist = hm.nearfar(g, 0, delta, glog, workgroups)
     assert rc == 0 and np.array_equal(dist, oracle.dijkstra(g, 0))
+
+
+@pytest.mark.parametrize("gi", range(len(GRAPHS)))
+@pytest.mark.parametrize("workgroups", [2, 3, 10])
+def test_a_late_thread_stays_in_step(gi, workgroups):
+    """Any thread may be late at any point: the threads of a workgroup still
+    meet at the same barriers, and the run ends with the right distances.
+    (Thread 0 of the barrier's leader once wrote the flag again that the
+    others had yet to read.)"""
+    g = GRAPHS[gi]
+    ref = oracle.dijkstra(g, 0)
+    for seed in range(60):
+        rc, dist = hm.nearfar(g, 0, 4, 0, workgroups, hm.PRIORITY, seed=seed)
+        assert rc == 0 and np.array_equal(dist, ref), seed
