@@ -46,7 +46,7 @@ struct alignas(128) Line {
   u32 pad_[31];
 };
 struct Ctl {
-  Line arrive[9], gen, err;  // arrivals at a barrier: per group of workgroups, then of the groups
+  Line arrive[9], gen, err;  // arrivals at barriers so far: per group of workgroups, then of the groups
   Line cl[2], ch[2];  // near queue sizes (light, heavy)
   Line cf[2];         // far pile sizes
   alignas(128) u64 fmin[2];  // smallest key filed in each far pile
@@ -311,35 +311,33 @@ NF_INL bool solo(const Args& a, const Phase& ph) {
   return ph.mode == RELAX ? ph.nh == 0 && ph.nl <= a.solo : ph.mode == SPLIT && ph.nf <= E::NT;
 }
 
-// Grid barrier.  Every thread first waits for its own memory operations;
-// one arrival per workgroup; the last one runs lead(), then the small phases
-// that follow, and bumps the generation the others spin on.  Returns false
-// once the run has failed.
+// Grid barrier, the `nth` of the run (from 0).  Every thread first waits for
+// its own memory operations; one arrival per workgroup; the last one runs
+// lead(), then the small phases that follow, and sets the generation that the
+// others spin on to nth + 1.  The arrivals are counted on from barrier to
+// barrier: a reset would have to reach memory before the next barrier's first
+// arrival, and the thread that makes it is not the one that lets the others go.
+// Returns false once the run has failed.
 template <class E>
 __host__ __device__ inline bool grid_sync(const E& t, const Args& a, Phase& ph, Phase* sph, typename E::Word* sflag,
-                                          Gather<E>* q, u64& scanned) {
+                                          Gather<E>* q, u64& scanned, u32 nth) {
   t.wait_mem();
   t.sync();
   Ctl* c = a.c;
   if (t.tid() == 0) {
-    const u32 g = t.ld32(&c->gen.w);
     // one word takes about 10 ns per arrival: eight groups, then their last
     // ones (workgroups go round the dies, so a group is a die's)
     const u32 grp = t.wg() & 7u, ngrp = t.nwg() < 8u ? t.nwg() : 8u;
-    bool last = t.add32(&c->arrive[grp].w, 1u) == (t.nwg() - grp + 7u) / 8u - 1u;
+    bool last = t.add32(&c->arrive[grp].w, 1u) + 1u == (nth + 1u) * ((t.nwg() - grp + 7u) / 8u);
+    if (last) last = t.add32(&c->arrive[8].w, 1u) + 1u == (nth + 1u) * ngrp;
     if (last) {
-      t.st32(&c->arrive[grp].w, 0u);
-      last = t.add32(&c->arrive[8].w, 1u) == ngrp - 1u;
-    }
-    if (last) {
-      t.st32(&c->arrive[8].w, 0u);
       lead(t, a, ph);
       *sph = ph;
       *sflag = 2;
     } else {
       u64 t0 = t.clock();
       u32 at = t.ld32(&c->phases);
-      while (t.ld32(&c->gen.w) == g) {
+      while (t.ld32(&c->gen.w) == nth) {
         if (t.ld32(&c->err.w)) break;
         if (t.clock() - t0 > TIMEOUT_TICKS) {
           // the last workgroup may be at small phases of its own: it is alive
@@ -390,7 +388,7 @@ __host__ __device__ inline bool grid_sync(const E& t, const Args& a, Phase& ph, 
       u32* dstp = reinterpret_cast<u32*>(&c->ph);
       for (u32 i = 0; i < sizeof(Phase) / 4; ++i) t.st32(dstp + i, src[i]);
       t.wait_mem();
-      t.st32(&c->gen.w, t.ld32(&c->gen.w) + 1u);
+      t.st32(&c->gen.w, nth + 1u);
       *sflag = t.ld32(&c->err.w) ? 1 : 0;
     }
     t.sync();
@@ -414,9 +412,9 @@ NF_INL u64 phases(const E& t, const Args& a, Phase* sph, typename E::Word* sflag
   t.sync();
   ph = *sph;
   u64 scanned = 0;
-  while (ph.mode != DONE) {
+  for (u32 nth = 0; ph.mode != DONE; ++nth) {
     do_phase(t, a, ph, q, t.wg(), t.nwg(), scanned);
-    if (!grid_sync(t, a, ph, sph, sflag, q, scanned)) break;
+    if (!grid_sync(t, a, ph, sph, sflag, q, scanned, nth)) break;
   }
   return scanned;
 }

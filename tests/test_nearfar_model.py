@@ -35,3 +35,17 @@ def test_a_late_thread_stays_in_step(gi, workgroups):
     for seed in range(60):
         rc, dist = hm.nearfar(g, 0, 4, 0, workgroups, hm.PRIORITY, seed=seed)
         assert rc == 0 and np.array_equal(dist, ref), seed
+
+
+@pytest.mark.parametrize("gi", range(len(GRAPHS)))
+@pytest.mark.parametrize("workgroups", [9, 10, 17])
+def test_stores_may_land_late(gi, workgroups):
+    """A store may reach the other workgroups at any time until its thread
+    waits for its own operations.  (The reset of a group's arrivals was not
+    waited for: with several workgroups to a group, it could undo an arrival
+    at the next barrier.)"""
+    g = GRAPHS[gi]
+    ref = oracle.dijkstra(g, 0)
+    for seed in range(150):
+        rc, dist = hm.nearfar(g, 0, 4, 0, workgroups, hm.PRIORITY, True, seed)
+        assert rc == 0 and np.array_equal(dist, ref), seed
