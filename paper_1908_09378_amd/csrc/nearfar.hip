@@ -94,6 +94,8 @@ struct DevGrid {
   __device__ __forceinline__ void lds_min(u64* p, u64 v) const {
     __hip_atomic_fetch_min((u64 PBH_LDS*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
+  // x of thread `from` of this wavefront
+  __device__ __forceinline__ u64 from_lane(u64 x, u32 from) const { return __shfl(x, (int)(from & 63u), 64); }
   __device__ __forceinline__ u32 wave_max(u32 x) const {
     for (int o = 32; o > 0; o >>= 1) {
       const u32 y = (u32)__shfl_xor((int)x, o, 64);

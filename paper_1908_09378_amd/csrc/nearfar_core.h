@@ -253,9 +253,12 @@ NF_INL void do_phase(const E& t, const Args& a, const Phase& ph, Gather<E>* q, u
       bool have = j < ph.nl;
       const u32 u = have ? t.ld32(a.ql[ph.src] + j) : 0u;
       // a vertex is in the queue once, so its last-scan mark is this group's
-      // alone in this phase (no exchange needed)
-      const u64 du = have ? t.ld64(a.dist + u) : 0ull, seen = have ? t.ld64(a.done_at + u) : 0ull;
+      // alone in this phase (no exchange needed); its distance may fall
+      // meanwhile, so the group goes by what its first lane has read
+      u64 du = have ? t.ld64(a.dist + u) : 0ull, seen = have ? t.ld64(a.done_at + u) : 0ull;
       const u64 r0 = have ? a.off[u] : 0ull, r1 = have ? a.off[u + 1] : 0ull;
+      du = t.from_lane(du, t.tid() & ~(G - 1));
+      seen = t.from_lane(seen, t.tid() & ~(G - 1));
       have = have && seen != du;  // already scanned at this distance (filed twice): skipped
       if (have && lig == 0) t.st64(a.done_at + u, du);
       const u64 e0 = have ? r0 : 0ull, e1 = have ? r1 : 0ull;

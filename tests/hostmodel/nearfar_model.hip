@@ -29,7 +29,7 @@ struct Machine {
   bool late_stores;
   std::vector<fibers::Barrier> wgb, waveb;
   std::vector<Store> pending;      // in order of issue
-  std::vector<u32> lane_value[2];  // exchanged between the lanes of a wavefront
+  std::vector<u64> lane_value[2];  // exchanged between the lanes of a wavefront
   std::vector<u32> turn;           // of each thread, which of the two
 
   static void land(const Store& s) { std::memcpy(s.p, &s.v, (size_t)s.bytes); }
@@ -131,18 +131,19 @@ struct FiberGrid {
     if (v < *p) *p = v;
   }
   // Puts x where the wavefront's other lanes find it, once all have.
-  const std::vector<u32>& exchange(u32 x, int line) const {
+  const std::vector<u64>& exchange(u64 x, int line) const {
     const u32 t = me();
-    std::vector<u32>& a = g_m->lane_value[g_m->turn[t]++ & 1];
+    std::vector<u64>& a = g_m->lane_value[g_m->turn[t]++ & 1];
     a[t] = x;
     g_m->pool->wait(g_m->waveb[t / W], line);
     return a;
   }
   u32 wave_max(u32 x, int line = __builtin_LINE()) const {
-    const std::vector<u32>& a = exchange(x, line);
-    for (u32 l = 0; l < W; ++l) x = a[me() / W * W + l] > x ? a[me() / W * W + l] : x;
+    const std::vector<u64>& a = exchange(x, line);
+    for (u32 l = 0; l < W; ++l) x = a[me() / W * W + l] > x ? (u32)a[me() / W * W + l] : x;
     return x;
   }
+  u64 from_lane(u64 x, u32 from, int line = __builtin_LINE()) const { return exchange(x, line)[wg() * NT + from]; }
 };
 
 }  // namespace

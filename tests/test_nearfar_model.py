@@ -49,3 +49,16 @@ def test_stores_may_land_late(gi, workgroups):
     for seed in range(150):
         rc, dist = hm.nearfar(g, 0, 4, 0, workgroups, hm.PRIORITY, True, seed)
         assert rc == 0 and np.array_equal(dist, ref), seed
+
+
+@pytest.mark.parametrize("gi", range(len(GRAPHS)))
+@pytest.mark.parametrize("workgroups", [2, 9])
+def test_a_group_of_lanes_scans_at_one_distance(gi, workgroups):
+    """The lanes that share a vertex agree on its distance, also when it falls
+    while they read it.  (Each decided by its own read: the mark could name a
+    smaller distance than the one that a lane relaxed its edges with.)"""
+    g = GRAPHS[gi]
+    ref = oracle.dijkstra(g, 0)
+    for seed in range(60):
+        rc, dist = hm.nearfar(g, 0, 4, 1, workgroups, hm.PRIORITY, bool(seed & 1), seed)
+        assert rc == 0 and np.array_equal(dist, ref), seed
