@@ -2709,7 +2709,7 @@ PBH_INL float mlp_forward(const T& t, const float* m, const float* f, const MlpR
     static_assert(MLP_H == 64, "one output term per lane");
     float z = t.sh->mlp_z[t.lane()];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) z += __shfl_xor(z, o, 64);
+    for (int o = 32; o > 0; o >>= 1) z += t.wave_xor(z, o);
     y += z;
   } else {
     for (int j = 0; j < MLP_H; ++j) y += t.sh->mlp_z[j];

@@ -215,6 +215,8 @@ struct DevTeam {
     const u32 lo = (u32)__shfl((int)(u32)x, (int)from, 64), hi = (u32)__shfl((int)(u32)(x >> 32), (int)from, 64);
     return ((u64)hi << 32) | lo;
   }
+  // x of lane (this lane ^ o).
+  __device__ __forceinline__ float wave_xor(float x, int o) const { return __shfl_xor(x, o, 64); }
   // Orders the LDS accesses of one wavefront (the hardware keeps their order).
   __device__ __forceinline__ void wsync() const {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

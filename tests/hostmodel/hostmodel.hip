@@ -8,6 +8,10 @@
 // operation scripts through the exact schedule, capacity and growth logic.
 // It is not part of the library and the library never calls it; results from
 // here are checked against the oracle like any other implementation.
+//
+// With PBH_LANES = 64 or 256 defined, the team is of that many threads in
+// wavefronts of 64 lanes (lanes.h), which runs the forms of the primitives that
+// one thread has no use for; no deep-level workers then.
 #include <algorithm>
 #include <cmath>
 #include <new>
@@ -16,11 +20,39 @@
 #include <vector>
 
 #include "../../paper_1908_09378_amd/csrc/pbh_core.h"
+#ifdef PBH_LANES
+#include "lanes.h"
+#endif
 
 using namespace bkt;
 typedef long long i64;
 
 namespace {
+
+#ifdef PBH_LANES
+using PlainTeam = LaneTeam<PBH_LANES, false>;
+using FullTeam = LaneTeam<PBH_LANES, true>;
+using Shared = TeamShared<PBH_LANES / 64>;
+constexpr bool kLanes = true;
+#else
+using PlainTeam = HostTeamPlain;
+using FullTeam = HostTeam;
+using Shared = TeamShared<1>;
+constexpr bool kLanes = false;
+template <class T, class F>
+int run_team(T& t, F&& body) {
+  body(t);
+  return 0;
+}
+#endif
+// One thread of the team looks at its state while the others wait (true: this one).
+template <class T>
+struct Gate {
+  const T& t;
+  explicit Gate(const T& team) : t(team) { t.sync(); }
+  ~Gate() { t.sync(); }
+  operator bool() const { return t.tid() == 0; }
+};
 
 int levels_for(u32 d, u64 elems, int qmin) {
   int q = qmin;
@@ -50,7 +82,7 @@ struct TracePolicy {
   using G = Arr;
   using SP = HeapState*;
   static void on_resolve(const Geom& g, HeapState* st, int i, bool after) {
-    if (!g_log) return;
+    if (!g_log || kLanes) return;
     ResolveRec r;
     r.lvl = i;
     r.after = after ? 1 : 0;
@@ -71,7 +103,7 @@ struct HM {
   std::vector<u64> cur, ak, uk;
   std::vector<u32> bitmap, av, ui;
   HeapState st;
-  TeamShared<1> ts;
+  Shared ts;
   std::vector<ResolveRec> log;
 };
 
@@ -144,9 +176,9 @@ int hm_update(void* hp, const u64* keys, const u32* ids, u64 count) {
     p.count = count;
     p.ukeys = h->uk.data();
     p.uids = h->ui.data();
-    HostTeamPlain t{&h->ts};
+    PlainTeam t{&h->ts};
     LogScope ls(h);
-    pbh_update_body<HostTeamPlain, TracePolicy>(t, p.g, &h->st, p);
+    if (int rc = run_team(t, [&](PlainTeam& tt) { pbh_update_body<PlainTeam, TracePolicy>(tt, p.g, &h->st, p); })) return rc;
     if (h->st.err) return h->st.err;
     if (h->st.aux[3] == 0) return 0;
     if (h->q >= MAXL) return -2;
@@ -169,9 +201,9 @@ int hm_delete(void* hp, const u32* ids, u64 count) {
     p.idbits = ceil_log2(h->id_cap);
     p.ids = ids;
     p.count = count;
-    HostTeamPlain t{&h->ts};
+    PlainTeam t{&h->ts};
     LogScope ls(h);
-    pbh_delete_body<HostTeamPlain, TracePolicy>(t, p.g, &h->st, p);
+    if (int rc = run_team(t, [&](PlainTeam& tt) { pbh_delete_body<PlainTeam, TracePolicy>(tt, p.g, &h->st, p); })) return rc;
     if (h->st.err) return h->st.err;
     if (h->st.aux[3] == 0) return 0;
     if (h->q >= MAXL) return -2;
@@ -194,9 +226,9 @@ int hm_extract(void* hp, u64 k, u64* ko, u32* io, u64* count) {
     p.k = k;
     p.okeys = ko;
     p.oids = io;
-    HostTeamPlain t{&h->ts};
+    PlainTeam t{&h->ts};
     LogScope ls(h);
-    pbh_extract_body<HostTeamPlain, TracePolicy>(t, p.g, &h->st, p);
+    if (int rc = run_team(t, [&](PlainTeam& tt) { pbh_extract_body<PlainTeam, TracePolicy>(tt, p.g, &h->st, p); })) return rc;
     if (h->st.err) return h->st.err;
     if (h->st.aux[3] == 0) break;
     if (h->q >= MAXL) return -2;
@@ -395,6 +427,26 @@ struct LiveCheck {
   }
 };
 
+// A team that goes from query to query, as those of a batch do: every query
+// has its levels at the start of one block of LDS, and the staging area after
+// them if there is room.
+struct KeptTeam {
+  Shared ts;
+  std::vector<u64> lds;
+  FullTeam t{&ts};
+};
+static KeptTeam* g_kept = nullptr;
+
+// The hm_sssp calls that follow run on one team with `lds_bytes` of LDS (0:
+// each on a team of its own again).
+void hm_keep_team(u64 lds_bytes) {
+  delete g_kept;
+  g_kept = nullptr;
+  if (!lds_bytes) return;
+  g_kept = new KeptTeam;
+  g_kept->lds.resize(lds_bytes / 8);
+}
+
 // parDijkstra with the kernel's round loop.  qlds levels are placed in a
 // separate buffer, standing in for LDS.  stats: rounds, relaxations, updates,
 // heap element touches, levels, resolves[0..15].
@@ -422,12 +474,23 @@ int hm_sssp(const u64* off, const u32* tg, const u32* wt, u32 n, u64 m, u32 src,
   g.lv = lv.data();
   HeapState st;
   state_init(&st, d, q);
-  TeamShared<1> ts;
-  HostTeam t{&ts};
+  Shared ts;
+  FullTeam own{&ts};
+  FullTeam& team = g_kept ? g_kept->t : own;
   // the kernel's LDS staging for merges of HBM levels (here: every merge of
   // more than one tile goes through it)
-  std::vector<u64> stage_buf(stage_bytes(1, HostTeam::kE) / 8 + 1);
-  stage_setup(t, reinterpret_cast<unsigned char*>(stage_buf.data()));
+  const u64 sb = stage_bytes(FullTeam::kNT, FullTeam::kE), nl = lvl_off(d, qlds);
+  std::vector<u64> stage_buf(sb / 8 + 1);
+  if (g_kept) {
+    unsigned char* lds = reinterpret_cast<unsigned char*>(g_kept->lds.data());
+    const u64 size = g_kept->lds.size() * 8;
+    if (nl * 12u > size) return E_INVAL;
+    g.lk = g_kept->lds.data();
+    g.lv = reinterpret_cast<u32*>(lds + nl * 8u);
+    if (nl * 12u + sb <= size) stage_setup(team, lds + nl * 12u);
+  } else {
+    stage_setup(team, reinterpret_cast<unsigned char*>(stage_buf.data()));
+  }
   for (u32 v = 0; v < n; ++v) dist[v] = KINF;
   dist[src] = 0;
   SpecCfg sc;
@@ -455,7 +518,7 @@ int hm_sssp(const u64* off, const u32* tg, const u32* wt, u32 n, u64 m, u32 src,
   int lim = deep_lim > 0 ? std::max(std::max(deep_lim, 2), qlds) : MAXL;
   SimDeep* sim = nullptr;
   std::vector<char> simbuf;
-  if (lim < q) {
+  if (!kLanes && lim < q) {
     simbuf.assign(sizeof(SimDeep), 0);
     sim = new (simbuf.data()) SimDeep();
     std::memset(&sim->c, 0, sizeof sim->c);
@@ -471,29 +534,44 @@ int hm_sssp(const u64* off, const u32* tg, const u32* wt, u32 n, u64 m, u32 src,
   } else {
     lim = MAXL;
   }
+  if (g_kept) {  // the rounds' list, in what the levels leave
+    const u64 lcap = std::min<u64>((g_kept->lds.size() * 8 - nl * 12u) / 24u, (u64)sc.kmax * d);
+    sc.lcap = lcap >= 256 ? (u32)lcap : 0u;
+  }
   // The plain rule runs the plain-rule-only instantiation (as the kernel
   // does), the other rules the general one.
-  auto run = [&](auto spec_tag) {
+  auto run = [&](auto& t, auto spec_tag) {
     constexpr bool SPEC = decltype(spec_tag)::value;
-    if (check_live) {
-      LiveCheck hk{dist, n, rule == 0, &first_bad, info, sim};
-      if (sim)
-        sssp_rounds<HostTeam, HostPolicy, LiveCheck, SimDeep, SPEC>(t, g, &st, off, tg, wt, dist, n, src, sched, sc,
-                                                                    &c, hk, sim, lim);
-      else
-        sssp_rounds<HostTeam, HostPolicy, LiveCheck, NoDeepSync, SPEC>(t, g, &st, off, tg, wt, dist, n, src, sched,
-                                                                       sc, &c, hk);
-    } else if (sim) {
-      sssp_rounds<HostTeam, HostPolicy, NoHook, SimDeep, SPEC>(t, g, &st, off, tg, wt, dist, n, src, sched, sc, &c,
-                                                               NoHook(), sim, lim);
-    } else {
-      sssp_rounds<HostTeam, HostPolicy, NoHook, NoDeepSync, SPEC>(t, g, &st, off, tg, wt, dist, n, src, sched, sc, &c);
-    }
+    using T = std::decay_t<decltype(t)>;
+    auto check = [&](const Geom& gg, HeapState* ss, const SsspCounters& cc) {
+      Gate<T> gate(t);
+      if (gate) LiveCheck{dist, n, rule == 0, &first_bad, info, sim}(gg, ss, cc);
+    };
+    auto rounds = [&](const auto& hook) {
+      using H = std::decay_t<decltype(hook)>;
+      SsspCounters mine;
+      if constexpr (!kLanes) {
+        if (sim) {
+          sssp_rounds<T, HostPolicy, H, SimDeep, SPEC>(t, g, &st, off, tg, wt, dist, n, src, sched, sc, &mine, hook,
+                                                       sim, lim);
+          c = mine;
+          return;
+        }
+      }
+      sssp_rounds<T, HostPolicy, H, NoDeepSync, SPEC>(t, g, &st, off, tg, wt, dist, n, src, sched, sc, &mine, hook);
+      if (t.tid() == 0) c = mine;
+    };
+    if (check_live)
+      rounds(check);
+    else
+      rounds(NoHook());
   };
+  int trc;
   if (rule == 0)
-    run(std::false_type());
+    trc = run_team(team, [&](auto& t) { run(t, std::false_type()); });
   else
-    run(std::true_type());
+    trc = run_team(team, [&](auto& t) { run(t, std::true_type()); });
+  if (trc) st.err = trc;
   stats[28] = sim ? sim->runs : 0;
   stats[29] = sim ? (u64)sim->lim : 0;
   if (sim) sim->~SimDeep();
