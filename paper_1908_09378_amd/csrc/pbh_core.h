@@ -523,10 +523,18 @@ PBH_HD inline u64 stage_bytes(int nt, int e) {
   const u64 w = (u64)nt * (u64)e + 2u;
   return ((2u * w * 12u + ((u64)nt + 1u) * 4u) + 7u) & ~7ull;
 }
-// Carves the staging area out of `base` (8-byte aligned).
+// Carves the staging area out of `base` (8-byte aligned); !on: the team has
+// none, also if an earlier query of its had one (this query's levels may lie
+// there now).
 template <class T, class BP>
-PBH_INL void stage_setup(T& t, BP base) {
+PBH_INL void stage_setup(T& t, BP base, bool on) {
   const u64 w = (u64)T::kNT * T::kE + 2u;
+  if (!on) {
+    t.stk = nullptr;
+    t.stv = nullptr;
+    t.stp = nullptr;
+    return;
+  }
   t.stk = (decltype(t.stk))base;
   t.stv = (decltype(t.stv))(base + 2u * w * 8u);
   t.stp = (decltype(t.stp))(base + 2u * w * 12u);

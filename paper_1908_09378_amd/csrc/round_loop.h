@@ -178,7 +178,7 @@ __device__ __attribute__((always_inline)) void deep_worker(DevTeam<NT, true>& t,
   Geom g = p.g;
   g.lk = nullptr;  // worker levels are never in LDS
   g.lv = nullptr;
-  if (p.stage) stage_setup(t, (unsigned char PBH_LDS*)dyn);
+  stage_setup(t, (unsigned char PBH_LDS*)dyn, p.stage != 0);
   t.prof = p.prof;
   if (threadIdx.x == 0) {
     state_init(st, g.d, g.q);
@@ -209,8 +209,7 @@ __device__ __attribute__((always_inline)) void sssp_query(DevTeam<NT, FULL, SHAR
   g.lv = reinterpret_cast<u32*>(dyn + nl * sizeof(u64));
   // the LDS after the levels: staging for merges of HBM levels (between
   // Resolves it also holds a speculative round's list for its sort)
-  if constexpr (FULL)
-    if (p.stage) stage_setup(t, (unsigned char PBH_LDS*)(dyn + nl * 12u));
+  if constexpr (FULL) stage_setup(t, (unsigned char PBH_LDS*)(dyn + nl * 12u), p.stage != 0);
   t.prof = p.prof;
   if (threadIdx.x == 0) {
     state_init(st, g.d, g.q);

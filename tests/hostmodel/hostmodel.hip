@@ -309,7 +309,7 @@ struct SimDeep {
   void run(int j) {
     HostTeam wt{&wts[j]};
     static_assert(sizeof(wstage[0]) >= 2 * 6 * 12 + 8, "worker staging (one thread, 4 outputs)");
-    stage_setup(wt, reinterpret_cast<unsigned char*>(wstage[j]));
+    stage_setup(wt, reinterpret_cast<unsigned char*>(wstage[j]), true);
     ++depth;
     ++runs;
     deep_step<HostTeam, HostPolicy>(wt, g, &wst[j], cur, j, *this);
@@ -487,9 +487,9 @@ int hm_sssp(const u64* off, const u32* tg, const u32* wt, u32 n, u64 m, u32 src,
     if (nl * 12u > size) return E_INVAL;
     g.lk = g_kept->lds.data();
     g.lv = reinterpret_cast<u32*>(lds + nl * 8u);
-    if (nl * 12u + sb <= size) stage_setup(team, lds + nl * 12u);
+    stage_setup(team, lds + nl * 12u, nl * 12u + sb <= size);
   } else {
-    stage_setup(team, reinterpret_cast<unsigned char*>(stage_buf.data()));
+    stage_setup(team, reinterpret_cast<unsigned char*>(stage_buf.data()), true);
   }
   for (u32 v = 0; v < n; ++v) dist[v] = KINF;
   dist[src] = 0;

@@ -116,6 +116,32 @@ def test_batch_lists(nq):
             assert np.array_equal(host64(q[6]), ref)
 
 
+@pytest.mark.parametrize("team,scale", [(64, 18), (256, 15)])
+def test_batch_teams_go_from_staged_queries_to_others(team, scale):
+    """More queries than resident teams, the larger ones with a staging area
+    after their LDS levels (8 edges a vertex: one level of d = 144 or 120) and
+    the others, taken by the same teams later, with LDS levels in its place (4
+    edges: two levels of d = 72 or 60) and merges in HBM that are large enough
+    for one."""
+    import torch
+    from gpu_util import DEV, graph_to_dev, host64
+    n, each = 6000, 700
+    rng = np.random.default_rng(team)
+    qs, refs = [], []
+    for deg in (8, 4):
+        g = W.csr_from_edges(n, np.repeat(np.arange(n), deg), rng.integers(0, n, n * deg),
+                             rng.integers(0, 10 ** 6, n * deg).astype(np.uint32), f"out{deg}")
+        assert g.max_degree() == deg
+        dg = graph_to_dev(g)
+        ref = [oracle.dijkstra(g, s) for s in range(5)]
+        for i in range(each):
+            qs.append((*dg, n, g.m, i % 5, torch.empty(n, dtype=torch.int64, device=DEV)))
+            refs.append(ref[i % 5])
+    pkg.sssp_batch(qs, d_scale=scale, team=team, k_rule=pkg.K_FIXED, k_fixed=64, k_max=256)
+    for q, ref in zip(qs, refs):
+        assert np.array_equal(host64(q[6]), ref)
+
+
 @pytest.mark.parametrize("team", [256, 1024])
 @pytest.mark.parametrize("d", [101, 520, 1100, 4097])
 def test_staged_merges(team, d):

@@ -18,7 +18,7 @@ import pytest
 
 import oracle
 import workloads as W
-from hostmodel import INF, HostHeap, sssp as hm_sssp
+from hostmodel import INF, HostHeap, kept_team, sssp as hm_sssp
 
 
 def check_structure(h: HostHeap, cur: np.ndarray, d: int):
@@ -271,6 +271,23 @@ def test_trial_limits_settle_everything_below_the_frontier(rule):
     rc, dist, st = hm_sssp(g, 0, stop_key=1 << 62)
     assert rc == 0 and not st["stopped"] and st["last_key"] == 2 ** 64 - 1
     assert np.array_equal(dist, ref)
+
+
+@pytest.mark.parametrize("rule", [0, 1])
+def test_a_team_goes_from_query_to_query(rule):
+    """Of queries that one team runs in turn, some have a staging area after
+    their LDS levels (here after none or one of 6,144 bytes, of 30,800) and
+    some have not (two levels: 30,720): a query without one merges without, and
+    not through the place where the last one's was, which is its own level 0 or
+    1 now."""
+    gs = [W.random_graph(300, 2000, 0, 50, 40 + s) for s in range(3)]
+    d = 32
+    with kept_team(30_800):
+        for s, qlds in [(0, 1), (1, 2), (2, 0), (0, 2), (1, 1), (2, 2)]:
+            g = gs[s]
+            assert g.max_degree() <= d
+            rc, dist, _ = hm_sssp(g, s, d=d, qlds=qlds, rule=rule, kfix=5, check_live=True)
+            assert rc == 0 and np.array_equal(dist, oracle.dijkstra(g, s)), (s, qlds)
 
 
 # ------------------------------------------------- Algorithm 1 and Theorem 1

@@ -76,3 +76,17 @@ def test_speculative_rounds(lanes, gi, lds):
 def test_merges_of_several_tiles(lanes):
     both(W.random_graph(3000, 30000, 0, 10 ** 6, 5), 0, lanes, rule=1, kfix=200, kmax=256, d=150, qlds=0)
     both(W.random_graph(1500, 9000, 0, 10 ** 6, 5), 0, lanes, d=40, qlds=1)
+
+
+@pytest.mark.parametrize("lanes", LANES)
+def test_a_team_goes_from_query_to_query(lanes):
+    """As the test of this name with one thread: queries with a staging area
+    after their one LDS level, then queries with two levels in its place, and
+    merges in HBM that are large enough for one."""
+    d = 32
+    gs = [W.random_graph(n, 5 * n, 0, 10 ** 6, 7 + n) for n in (14 * lanes, 16 * lanes)]
+    with kept_team(32_000, lanes):
+        for i, qlds in enumerate([1, 2, 2, 1, 2]):
+            g = gs[i % 2]
+            rc, dist, st = hm_sssp(g, i, d=d, qlds=qlds, rule=1, kfix=20, check_live=True, lanes=lanes)
+            assert rc == 0 and st["first_bad"] == -1 and np.array_equal(dist, oracle.dijkstra(g, i)), (i, qlds)
