@@ -1765,7 +1765,7 @@ PBH_INL bool resolve0_wave(const T& t, const Geom& g, typename P::SP st, const u
   KV pi{a.pk, a.pv};
   if (a.nS > 0 || a.nB > cB) {
     const u32 rows = small_rows<T>(a.nS, a.nB);
-    if (rows == 0 || a.nS + a.nB > 4u * d) return false;
+    if (rows == 0 || a.nS + a.nB > 4u * d) return false;  // (resolve_t reports what does not fit)
     u32 m = 0;
     KV p1 = pi;
     bool fit = true;
@@ -1814,7 +1814,8 @@ PBH_INL bool resolve0_wave(const T& t, const Geom& g, typename P::SP st, const u
   }
   bool whole = true;
   if (a.nB < cB && 0 < ell) {
-    const u32 rows = small_rows<T>(b.nB, b.nS);
+    // (what does not fit B_1's buffers is left to resolve_t as well)
+    const u32 rows = b.nB + b.nS <= 16u * d ? small_rows<T>(b.nB, b.nS) : 0u;
     whole = rows != 0;
     if (whole) {
       u32 m = 0;

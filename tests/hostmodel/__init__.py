@@ -66,6 +66,8 @@ def lib(lanes=0):
         L.hm_level_items.argtypes = [C.c_void_p, C.c_int, u64p, u32p, u64p, u32p]
         L.hm_resolve_log.restype = C.c_uint64
         L.hm_resolve_log.argtypes = [C.c_void_p, C.POINTER(C.c_longlong), C.c_uint64]
+        L.hm_fill.restype = C.c_int
+        L.hm_fill.argtypes = [C.c_uint32, C.c_uint32, C.c_uint32, C.POINTER(C.c_int)]
         L.hm_keep_team.argtypes = [C.c_uint64]
         L.hm_sssp.restype = C.c_int
         L.hm_sssp.argtypes = [u64p, u32p, u32p, C.c_uint32, C.c_uint64, C.c_uint32, u64p, C.c_uint32,
@@ -171,6 +173,13 @@ def sssp(g, src, d=0, sched=0, hcap=0, qlds=0, rule=0, kfix=0, kmax=0, kseq=None
                           first_bad=int(st[22].astype(np.int64)), violation=st[23:26].tolist(),
                           last_key=int(st[26]), stopped=bool(st[27]), worker_runs=int(st[28]),
                           deep_lim=int(st[29]))
+
+
+def fill(d, nB, nS, lanes=0):
+    """Resolve(0) of an empty level 0 over a level 1 of nB and nS elements, both
+    in LDS: (the heap's error, was level 1's temporary buffer written)."""
+    touched = C.c_int(0)
+    return lib(lanes).hm_fill(d, nB, nS, C.byref(touched)), bool(touched.value)
 
 
 class kept_team:

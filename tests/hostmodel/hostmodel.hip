@@ -282,6 +282,34 @@ int hm_level_items(void* hp, int i, u64* bk, u32* bv, u64* sk, u32* sv) {
   return 0;
 }
 
+// Resolve(0) of a heap of two levels, both in LDS, whose level 0 is empty and
+// whose level 1 holds nB and nS elements (at most the sizes of the buffers);
+// returns the state's error, *touched = did it write to level 1's temporary
+// buffer (which such a Resolve has no use for)?
+int hm_fill(u32 d, u32 nB, u32 nS, int* touched) {
+  std::vector<u64> k(lvl_off(d, 2), 7);
+  std::vector<u32> v(lvl_off(d, 2), 7);
+  Geom g{};
+  g.d = d, g.q = g.qlds = 2, g.lk = k.data(), g.lv = v.data();
+  HeapState st;
+  state_init(&st, d, 2);
+  std::vector<u64> cur(nB + nS);
+  Arr B = lbuf(g, 1, 0), S = lbuf(g, 1, 3), T = lbuf(g, 1, 2);
+  for (u32 x = 0; x < nB + nS; ++x) {
+    const Arr& A = x < nB ? B : S;
+    const u32 at = x < nB ? x : x - nB;
+    A.k[at] = cur[x] = 1000 + x;
+    A.v[at] = x;
+  }
+  st.L[1].nB = nB, st.L[1].nS = nS, st.ell = 1;
+  Shared ts;
+  PlainTeam t{&ts};
+  if (int rc = run_team(t, [&](PlainTeam& tt) { resolve<PlainTeam, HostPolicy>(tt, g, &st, cur.data(), 0); })) return rc;
+  *touched = 0;
+  for (u64 x = 0; x < capB(d, 1); ++x) *touched |= T.k[x] != 7 || T.v[x] != 7;
+  return st.err;
+}
+
 // The deep-level service of the SSSP kernel with the workers simulated on one
 // thread: a worker's Resolve runs when a team waits for its level (mode 1,
 // lazy: the workers are as slow as they may be), as soon as it is posted

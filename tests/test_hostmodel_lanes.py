@@ -9,7 +9,7 @@ import pytest
 
 import oracle
 import workloads as W
-from hostmodel import HostHeap, kept_team, sssp as hm_sssp
+from hostmodel import HostHeap, fill, kept_team, sssp as hm_sssp
 from test_hostmodel import NGRAPHS, _graphs, check_structure
 
 LANES = [64, 256]
@@ -90,3 +90,15 @@ def test_a_team_goes_from_query_to_query(lanes):
             g = gs[i % 2]
             rc, dist, st = hm_sssp(g, i, d=d, qlds=qlds, rule=1, kfix=20, check_live=True, lanes=lanes)
             assert rc == 0 and st["first_bad"] == -1 and np.array_equal(dist, oracle.dijkstra(g, i)), (i, qlds)
+
+
+@pytest.mark.parametrize("lanes", [0] + LANES)
+@pytest.mark.parametrize("d", [1, 4])
+def test_a_level_that_does_not_fit_is_reported(lanes, d):
+    """B_1 and S_1 merge into a buffer of 16 d elements.  More than that breaks
+    the heap's invariants: E_INTERNAL (-6), and nothing past the buffer is
+    written.  (The form of one wavefront took it and wrote on.)"""
+    for nB, nS in [(16 * d, 0), (12 * d, 4 * d), (16 * d - 1, 1), (8 * d, 8 * d)]:
+        assert fill(d, nB, nS, lanes) == (0, False), (nB, nS)
+    for nB, nS in [(16 * d, 1), (14 * d, 6 * d), (16 * d, 8 * d)]:
+        assert fill(d, nB, nS, lanes) == (-6, False), (nB, nS)
