@@ -51,9 +51,15 @@ __global__ __launch_bounds__(NT) void k_prim(int op, u64* ak, u32* av, u32 na, u
       res[2] = lo;
       res[3] = hi;
     }
-  } else if (op == 2) {  // merge + dedup
-    u32 m = merge_dedup(t, A, na, B, nb, C, cur, cur != nullptr);
-    if (threadIdx.x == 0) res[0] = m;
+  } else if (op == 2) {  // merge + dedup, prefer = res[0]; outputs <= (res[1], res[2]) counted
+    CountLe le{KV{res[1], (u32)res[2]}, 0};
+    const int prefer = (int)res[0];
+    t.sync();
+    u32 m = merge_dedup(t, A, na, B, nb, C, cur, false, prefer, &le);
+    if (threadIdx.x == 0) {
+      res[0] = m;
+      res[1] = le.n;
+    }
   } else if (op == 3) {  // partition3 by res[0..3] = (p1k, p1v, p2k, p2v)
     KV p1{res[0], (u32)res[1]}, p2{res[2], (u32)res[3]};
     t.sync();

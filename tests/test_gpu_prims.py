@@ -60,47 +60,57 @@ def test_min_max(nt, n):
     assert (r[0], r[1]) == (k[i], v[i]) and r[2] == k.min() and r[3] == k.max()
 
 
+LIVE, PREFER_A, PREFER_B = 0, 1, 2
+
+
+def merged(ka, ia, kb, ib, cur, prefer):
+    """What merge_dedup keeps of two id-sorted arrays: of two copies with
+    different keys the preferred one, or the one whose key is cur[id] (neither:
+    both go), or without cur the smaller."""
+    a, b = dict(zip(ia.tolist(), ka.tolist())), dict(zip(ib.tolist(), kb.tolist()))
+    exp = []
+    for i in sorted(a.keys() | b.keys()):
+        if i not in a or i not in b or a[i] == b[i]:
+            exp.append((a.get(i, b.get(i)), i))
+        elif prefer != LIVE:
+            exp.append((a[i] if prefer == PREFER_A else b[i], i))
+        elif cur is None:
+            exp.append((min(a[i], b[i]), i))
+        elif cur[i] in (a[i], b[i]):
+            exp.append((int(cur[i]), i))
+    return exp
+
+
+# (the edges of the form that one wavefront keeps in registers: up to 16
+# elements in the shorter array, 256 in the longer, and 24 times 64 of both)
 @pytest.mark.parametrize("nt", TEAMS)
-@pytest.mark.parametrize("na,nb", [(0, 0), (2, 0), (0, 3), (5, 7), (64, 64), (300, 17), (1000, 3000), (513, 4100)])
-@pytest.mark.parametrize("mode", ["min", "live"])
+@pytest.mark.parametrize("na,nb", [(0, 0), (2, 0), (0, 3), (5, 7), (64, 64), (300, 17), (1000, 3000), (513, 4100),
+                                   (1, 1), (15, 64), (16, 64), (17, 64), (16, 65), (12, 128), (13, 128), (8, 192),
+                                   (9, 192), (6, 256), (7, 256), (6, 257), (16, 16), (1, 256), (0, 257)])
+@pytest.mark.parametrize("mode", ["min", "live", "a", "b"])
 def test_merge_dedup(nt, na, nb, mode):
     rng = np.random.default_rng(na * 7 + nb)
-    cap = 3 * (na + nb) + 10
-    ia, ib = sorted_ids(rng, na, cap), sorted_ids(rng, nb, cap)
-    ka = rng.integers(0, 100, size=na).astype(np.uint64)
-    kb = rng.integers(0, 100, size=nb).astype(np.uint64)
-    cur = None
-    if mode == "live":
-        cur = rng.integers(0, 100, size=cap).astype(np.uint64)
-        # make some elements live
-        cur[ia[::2]] = ka[::2]
-        cur[ib[::3]] = kb[::3]
-    (ck, cv, r, *_) = run(nt, 2, a=(ka, ia), b=(kb, ib), nc=na + nb, cur=cur)
-    m = int(r[0])
-    # expected
-    d = {}
-    for k, i in zip(kb.tolist(), ib.tolist()):
-        d.setdefault(i, []).append(("B", k))
-    for k, i in zip(ka.tolist(), ia.tolist()):
-        d.setdefault(i, []).insert(0, ("A", k))
-    exp = []
-    for i in sorted(d):
-        c = d[i]
-        if cur is None:
-            exp.append((min(k for _, k in c), i))
-        else:
-            live = [k for _, k in c if k == cur[i]]
-            if len(c) == 2:
-                if c[0][1] == c[1][1]:
-                    exp.append((c[0][1], i))
-                elif live:
-                    exp.append((live[0], i))
-            else:
-                src, k = c[0]
-                if src == "A" or k == cur[i]:   # filterB drops dead B-only elements
-                    exp.append((k, i))
-    got = list(zip(ck[0][:m].tolist(), cv[0][:m].tolist()))
-    assert got == exp
+    prefer = {"a": PREFER_A, "b": PREFER_B}.get(mode, LIVE)
+    for na, nb in {(na, nb), (nb, na)}:
+        cap = max(na, nb) + min(na, nb) // 2 + 3  # (half of the ids or more in both)
+        ia, ib = sorted_ids(rng, na, cap), sorted_ids(rng, nb, cap)
+        ka = rng.integers(0, 100, size=na).astype(np.uint64)
+        kb = rng.integers(0, 100, size=nb).astype(np.uint64)
+        kb[::5] = 7
+        ka[::7] = 7
+        cur = None
+        if mode != "min":
+            cur = rng.integers(0, 100, size=cap).astype(np.uint64)
+            # make some elements live
+            cur[ia[::2]] = ka[::2]
+            cur[ib[::3]] = kb[::3]
+        exp = merged(ka, ia, kb, ib, cur, prefer)
+        for pk, pv in [(50, cap // 2), (0, 0), (2 ** 64 - 1, 2 ** 32 - 1)]:
+            (ck, cv, r, *_) = run(nt, 2, a=(ka, ia), b=(kb, ib), nc=na + nb, cur=cur,
+                                  res=np.array([prefer, pk, pv, 0, 0, 0, 0, 0], np.uint64))
+            m = int(r[0])
+            assert list(zip(ck[0][:m].tolist(), cv[0][:m].tolist())) == exp
+            assert int(r[1]) == sum(e <= (pk, pv) for e in exp)
 
 
 @pytest.mark.parametrize("nt", TEAMS)

@@ -51,7 +51,7 @@ def test_steps(kind, d):
     run(cap, d, kind, [cap, d, 1, d - 1, 2 * d + 1, cap], [d // 2, 3, d, 2 * d], 0, d)
 
 
-@pytest.mark.parametrize("take", [1, 31, 33, 4095, 4097, 16384, 16385, 40000])
+@pytest.mark.parametrize("take", [1, 31, 33, 4095, 4096, 4097, 12287, 12288, 12289, 16384, 16385, 40000])
 def test_extract_sorts(take):
     run(120000, 30000, "even", [120000, 30000, 5000], [take], 900, take)
 
