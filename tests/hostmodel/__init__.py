@@ -182,6 +182,20 @@ def fill(d, nB, nS, lanes=0):
     return lib(lanes).hm_fill(d, nB, nS, C.byref(touched)), bool(touched.value)
 
 
+class lane_order:
+    """The lanes of the calls within are scheduled at random (0: in turn)."""
+
+    def __init__(self, seed, lanes):
+        self.seed, self.set = seed, lib(lanes).hm_lane_seed
+        self.set.argtypes = [C.c_uint64]
+
+    def __enter__(self):
+        self.set(self.seed)
+
+    def __exit__(self, *exc):
+        self.set(0)
+
+
 class kept_team:
     """The sssp() calls within run one after another on one team with this
     many bytes of LDS: the levels first, then the staging area if it fits."""

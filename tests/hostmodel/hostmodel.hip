@@ -136,6 +136,10 @@ void grow(HM* h) {
 
 extern "C" {
 
+#ifdef PBH_LANES
+void hm_lane_seed(u64 seed) { g_lane_seed = seed; }
+#endif
+
 void* hm_create(u32 id_cap, u32 d, int sched) {
   HM* h = new HM;
   h->id_cap = id_cap;

@@ -189,11 +189,16 @@ struct LaneTeam {
 };
 #undef LINE_
 
+// How the lanes are scheduled between the operations that they take part in
+// together: in turn (seed 0), or at random, so that what one lane writes and
+// another reads without such an operation between them comes out differently.
+static u64 g_lane_seed = 0;
+
 // body(t) by every lane of a team (its shared memory and staging area as t's):
 // 0, or fibers::MISMATCH or HANG.
 template <int NT, bool STAGE, class F>
 int run_team(const LaneTeam<NT, STAGE>& t, F&& body) {
-  fibers::Pool pool(fibers::ROUND_ROBIN, 1, ~0ull);
+  fibers::Pool pool(g_lane_seed ? fibers::PRIORITY : fibers::ROUND_ROBIN, g_lane_seed, ~0ull);
   LaneMachine m(&pool, NT);
   auto one = [&](u32) {
     LaneTeam<NT, STAGE> mine = t;

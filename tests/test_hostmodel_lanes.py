@@ -9,7 +9,7 @@ import pytest
 
 import oracle
 import workloads as W
-from hostmodel import HostHeap, fill, kept_team, sssp as hm_sssp
+from hostmodel import HostHeap, fill, kept_team, lane_order, sssp as hm_sssp
 from test_hostmodel import NGRAPHS, _graphs, check_structure
 
 LANES = [64, 256]
@@ -102,3 +102,27 @@ def test_a_level_that_does_not_fit_is_reported(lanes, d):
         assert fill(d, nB, nS, lanes) == (0, False), (nB, nS)
     for nB, nS in [(16 * d, 1), (14 * d, 6 * d), (16 * d, 8 * d)]:
         assert fill(d, nB, nS, lanes) == (-6, False), (nB, nS)
+
+
+@pytest.mark.parametrize("lanes", LANES)
+@pytest.mark.parametrize("seed", range(1, 5))
+def test_the_order_of_the_lanes_does_not_show(lanes, seed):
+    """Between the operations that all lanes (of a wavefront, of the team) take
+    part in, they may run in any order: no lane reads what another writes in
+    the same stretch."""
+    with lane_order(seed, lanes):
+        both(W.grid4(8, 9, 1, 100, 2), 0, lanes, qlds=2 * (seed % 2))
+        both(W.random_graph(60, 900, 0, 5, 3), 0, lanes, qlds=1)
+        both(W.random_graph(400, 4000, 0, 50, 3), 0, lanes, rule=1, kfix=100, kmax=256, d=40, qlds=seed % 2)
+        with kept_team(60_000, lanes):
+            rc, dist, st = hm_sssp(W.grid8(12, 12, 10000, 4), 0, rule=3, kseq=[7, 1, 40], kmax=256, d=32, qlds=1,
+                                   lanes=lanes, check_live=True)
+        assert rc == 0 and st["first_bad"] == -1
+        assert np.array_equal(dist, oracle.dijkstra(W.grid8(12, 12, 10000, 4), 0))
+        h, o = HostHeap(300, 7, 0, lanes), oracle.PQ(300)
+        for op in W.random_script(12, 300, 60, 50, seed, deletes=True):
+            a, b = getattr(h, {"update": "bulk_update", "extract": "extract_min"}.get(op[0], op[0])), \
+                getattr(o, {"update": "bulk_update", "extract": "extract_min"}.get(op[0], op[0]))
+            x, y = a(*op[1:]), b(*op[1:])
+            if op[0] == "extract":
+                assert all(np.array_equal(p, q) for p, q in zip(x, y))
