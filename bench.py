@@ -50,7 +50,7 @@ METRIC = "SSSP GTEPS (m/time) on 1 MI355X: learned-threshold & batched vs plain 
 HBM_PEAK_GBS = 8000.0
 CSRC = os.path.join(ROOT, "paper_1908_09378_amd", "csrc")
 KERNEL_SOURCES = ["pbh_core.h", "pbh_team.h", "pbh_launch.h", "round_loop.h", "kernels.hip", "kernels_full.hip",
-                  "wide.h", "wide.hip", "learn.hip", "nearfar.hip"]
+                  "wide.h", "wide.hip", "learn.hip", "nearfar_core.h", "nearfar.hip"]
 
 RING_DESC = "ring lattice n=2^20, 16 neighbours per side, w~U[1,1000], source 0"
 GRID64_DESC = "4-neighbour grid 64x64, w~U[1,100], source 0"
@@ -71,7 +71,7 @@ KERNEL_FAMILIES = {
     "k_sssp": _CORE + ["pbh_launch.h", "round_loop.h", "kernels.hip"],
     "k_sssp_full": _CORE + ["pbh_launch.h", "round_loop.h", "kernels_full.hip"],
     "k_sssp_multi": _CORE + ["pbh_launch.h", "round_loop.h", "kernels_full.hip"],
-    "k_nearfar": ["pbh_team.h", "nearfar.hip"],
+    "k_nearfar": ["pbh_team.h", "nearfar_core.h", "nearfar.hip"],
     "heap": _CORE + ["wide.h", "wide.hip"],
 }
 

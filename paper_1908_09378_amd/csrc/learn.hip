@@ -107,12 +107,11 @@ __global__ void k_feat_stats(const float* X, u32 n, float* blob) {
 // consecutive elements over all 64 banks.  Each share is a sum over at most
 // B / gridDim samples, so a parameter's sum is a tree and not one chain of B.
 //
-// Before, one workgroup ran the whole batch, one sample per thread, with the
-// activations in global memory and one chain of B additions per parameter:
-// 2.9 ms per step of 1,024 samples on one of the 256 compute units, against
-// 24 us now (32 workgroups; 15 us here, 5 us in k_mlp_sum, the rest between
-// the launches); the gradient's error against float64 fell from 2e-7 - 9e-7 to
-// 3e-8 - 6e-8.
+// Bound by the chain of a chunk's steps and the launches: 24 us a step of 1,024
+// samples (32 workgroups; 15 us here, 5 us in k_mlp_sum, the rest between the
+// launches), 2.9 ms by one workgroup with a sample per thread and activations
+// in global memory.  The gradient's error against float64 is 3e-8 - 6e-8; one
+// chain of B additions per parameter has 2e-7 - 9e-7.
 constexpr int MS = 32;   // samples per chunk
 constexpr int LD = 68;   // LDS row stride of the 64-wide arrays
 constexpr u32 GRAD_GRID = 256;             // most workgroups of k_mlp_grad
