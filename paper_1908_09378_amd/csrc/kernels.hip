@@ -85,7 +85,7 @@ __global__ __launch_bounds__(NT) void k_sssp(SsspParams p) {
   __shared__ TeamShared<NT / 64> ts;
   __shared__ HeapState st_lds;
   constexpr bool FULL = NT > 64;
-  DevTeam<NT, FULL, false> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
+  DevTeam<NT, FULL, false, SPEC && NT == 256 ? 32 : 16> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
   sssp_query<NT, FULL, SPEC>(t, (HeapState PBH_LDS*)&st_lds, dyn, p);
 }
 

@@ -16,7 +16,7 @@ __global__ __launch_bounds__(NT) void k_sssp_full(SsspParams p) {
   extern __shared__ __align__(16) unsigned char dyn[];
   __shared__ TeamShared<NT / 64> ts;
   __shared__ HeapState st_lds;
-  DevTeam<NT, true, true> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
+  DevTeam<NT, true, true, NT == 256 ? 32 : 16> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
   if (blockIdx.x == 0)
     sssp_query<NT, true, true, true>(t, (HeapState PBH_LDS*)&st_lds, dyn, p);
   else if (p.deep && p.deep_lim + (int)blockIdx.x - 1 < p.g.q)

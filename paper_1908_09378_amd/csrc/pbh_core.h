@@ -1141,7 +1141,12 @@ PBH_INL KV select_hist(const T& t, AA A, u32 n, u32 r) {
 // paper sorted with a radix sort to select (Section 4.1); a radix select reads
 // the candidates once per byte and sorts nothing.  Ranks within two of either
 // end of a small array use select_small; other ranks in arrays of at most four
-// elements per thread (in HBM: 16, by 256 threads 32) use select_hist.
+// elements per thread use select_hist, in HBM of at most kHeld: 16, or 32 for
+// the single queries of 256 threads that also run speculative rounds (learned,
+// 200,000 vertices, d = 256: 597 ms; 613 with 16).  The registers for 32 cost
+// every round of the kernels that run plain rounds only more than large Selects
+// gain (DAGs of 3,382 and 8,000 vertices, d = 705 and 3,143: 80.0 and 284 ms; 77.1
+// and 268 with 16), and of the batches (96 learned queries 15.0 ms; 14.7).
 template <class T, class AA>
 PBH_INL KV select_kth(const T& t, AA A, u32 n_, u32 r_) {
   const u32 n = t.uni(n_);
@@ -1150,8 +1155,8 @@ PBH_INL KV select_kth(const T& t, AA A, u32 n_, u32 r_) {
   if (n <= 4u * (u32)T::kNT) return select_hist<4>(t, A, n, r);
   if constexpr (!in_lds<AA>::v) {
     if (n <= 16u * (u32)T::kNT) return select_hist<16>(t, A, n, r);
-    if constexpr (T::kNT == 256) {
-      if (n <= 32u * (u32)T::kNT) return select_hist<32>(t, A, n, r);
+    if constexpr (T::kHeld > 16) {
+      if (n <= (u32)T::kHeld * (u32)T::kNT) return select_hist<T::kHeld>(t, A, n, r);
     }
   }
   u64 lo = KINF, hi = 0;

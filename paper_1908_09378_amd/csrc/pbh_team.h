@@ -172,8 +172,11 @@ __device__ __forceinline__ void wave_sort_pairs(u32& a, u32& p) {
 // launch, so their atomics and coherent loads have agent scope and go to the
 // memory side.  A team whose keys nobody else touches uses workgroup scope,
 // which the L2 of its die serves.
-template <int NT, bool FULL = false, bool SHARED = true>
+// HELD: elements per thread that Select holds in registers from HBM (see
+// select_kth).
+template <int NT, bool FULL = false, bool SHARED = true, int HELD = 16>
 struct DevTeam {
+  static constexpr int kHeld = HELD;
   static constexpr int kScope = SHARED ? __HIP_MEMORY_SCOPE_AGENT : __HIP_MEMORY_SCOPE_WORKGROUP;
   static constexpr int kNT = NT;
   static constexpr int kNW = NT / 64;
@@ -367,6 +370,7 @@ struct HostTeamT {
   static constexpr int kME = 8;
   static constexpr int kE = 4;
   static constexpr int kM = 4;
+  static constexpr int kHeld = 16;
   static constexpr bool kStage = STAGE;
   static constexpr int kRU = STAGE ? 4 : 1;
   TeamShared<1>* sh;

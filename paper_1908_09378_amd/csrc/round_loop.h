@@ -171,10 +171,10 @@ struct DevDeepSync {
 
 // A deep-level worker: Resolve(lvl) whenever the level above asks, until the
 // front has finished (or any team has failed).
-template <int NT>
-__device__ __attribute__((always_inline)) void deep_worker(DevTeam<NT, true>& t, HeapState PBH_LDS* st,
-                                                          unsigned char* dyn, const SsspParams& p,
-                            int lvl) {
+template <int NT, int HELD>
+__device__ __attribute__((always_inline)) void deep_worker(DevTeam<NT, true, true, HELD>& t, HeapState PBH_LDS* st,
+                                                          unsigned char* dyn, const SsspParams& p, int lvl) {
+  using TT = DevTeam<NT, true, true, HELD>;
   Geom g = p.g;
   g.lk = nullptr;  // worker levels are never in LDS
   g.lv = nullptr;
@@ -184,9 +184,9 @@ __device__ __attribute__((always_inline)) void deep_worker(DevTeam<NT, true>& t,
     state_init(st, g.d, g.q);
   }
   t.sync();
-  DevDeepSync<DevTeam<NT, true>> sy{p.deep, p.deep_lim};
+  DevDeepSync<TT> sy{p.deep, p.deep_lim};
   while (sy.wait_request(t, lvl)) {
-    deep_step<DevTeam<NT, true>, DevPolicy>(t, g, st, p.dist, lvl, sy);
+    deep_step<TT, DevPolicy>(t, g, st, p.dist, lvl, sy);
     if (sy.error(t)) break;
   }
 }
@@ -200,8 +200,8 @@ __device__ __attribute__((always_inline)) void deep_worker(DevTeam<NT, true>& t,
 // loop, and the call's register conventions left 248-256 VGPRs and a 350-byte
 // stack frame per lane (inlined: 126-193 VGPRs, no stack; learned ring 1.58
 // -> 1.37 s, the paper's DAG 2.08 -> 1.68 s, plain ring 11.56 -> 10.56 s).
-template <int NT, bool FULL, bool SPEC = true, bool SHARED = false>
-__device__ __attribute__((always_inline)) void sssp_query(DevTeam<NT, FULL, SHARED>& t, HeapState PBH_LDS* st,
+template <int NT, bool FULL, bool SPEC = true, bool SHARED = false, int HELD = 16>
+__device__ __attribute__((always_inline)) void sssp_query(DevTeam<NT, FULL, SHARED, HELD>& t, HeapState PBH_LDS* st,
                                                          unsigned char* dyn, const SsspParams& p) {
   Geom g = p.g;
   const u64 nl = lvl_off(g.d, g.qlds);
@@ -216,7 +216,7 @@ __device__ __attribute__((always_inline)) void sssp_query(DevTeam<NT, FULL, SHAR
   }
   t.sync();
   SsspCounters c;
-  using TT = DevTeam<NT, FULL, SHARED>;
+  using TT = DevTeam<NT, FULL, SHARED, HELD>;
   if constexpr (FULL && SHARED) {
     // the deep-level service is off when it gets no sync object
     DevDeepSync<TT> sy{p.deep, p.deep_lim};

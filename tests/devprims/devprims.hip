@@ -16,7 +16,7 @@ __global__ __launch_bounds__(NT) void k_prim(int op, u64* ak, u32* av, u32 na, u
                                              u64* ck, u32* cv, u64* c2k, u32* c2v, u64* c3k, u32* c3v,
                                              const u64* cur, u64* res) {
   __shared__ TeamShared<NT / 64> ts;
-  DevTeam<NT> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
+  DevTeam<NT, false, true, NT == 256 ? 32 : 16> t{(TeamShared<NT / 64> PBH_LDS*)&ts};
   GA A{(u64 PBH_GLB*)ak, (u32 PBH_GLB*)av}, B{(u64 PBH_GLB*)bk, (u32 PBH_GLB*)bv};
   GA C{(u64 PBH_GLB*)ck, (u32 PBH_GLB*)cv}, C2{(u64 PBH_GLB*)c2k, (u32 PBH_GLB*)c2v},
       C3{(u64 PBH_GLB*)c3k, (u32 PBH_GLB*)c3v};

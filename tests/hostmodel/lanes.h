@@ -67,6 +67,7 @@ struct LaneTeam {
   static constexpr int kNT = NT, kNW = NT / 64, kW = 64;
   static constexpr int kE = NT == 64 ? 8 : 4, kM = 4, kME = NT == 1024 ? 4 : 8;  // as DevTeam's
   static constexpr bool kStage = STAGE;
+  static constexpr int kHeld = STAGE && NT == 256 ? 32 : 16;
   static constexpr int kRU = STAGE || NT >= 256 ? 4 : 1;
   static constexpr u32 prof = 0;
   TeamShared<kNW>* sh;

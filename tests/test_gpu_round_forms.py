@@ -45,7 +45,7 @@ def test_speculative_rounds(gi, team, k):
 @pytest.mark.parametrize("spread", [1, 2, 200, 1 << 20, 1 << 63])
 def test_select_edges(nt, spread):
     rng = np.random.default_rng(nt + spread % 1000)
-    for n in (1, 3, nt - 1, nt + 1, 4 * nt, 4 * nt + 1, 16 * nt, 16 * nt + 1):
+    for n in (1, 3, nt - 1, nt + 1, 4 * nt, 4 * nt + 1, 16 * nt, 16 * nt + 1, 32 * nt, 32 * nt + 1):
         ids = rng.permutation(4 * n)[:n].astype(np.uint32)
         keys = rng.integers(0, spread, n, dtype=np.uint64) + np.uint64(7)
         order = np.lexsort((ids, keys))
