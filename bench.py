@@ -187,7 +187,7 @@ class Query:
                 "us_per_round": kern_ms * 1e3 / max(1, st["rounds"]), "exact": exact,
                 "roofline": roofline(kernel, workload, sssp_bytes(st), kern_ms)}
 
-    def nearfar(self, steps, factors=(1.0,)):
+    def nearfar(self, steps, factors=(1.0,), workload="nearfar"):
         """The Near-Far (Delta-stepping) baseline on the same graph: delta =
         f x Davidson et al.'s choice for each f, one untimed and `steps` timed
         runs each; the fastest delta is the record, the others are listed."""
@@ -219,7 +219,7 @@ class Query:
                 "delta": best["delta"], "exact": all(r["exact"] for r in tried),
                 "method": "Near-Far (Delta-stepping), one cooperative launch over every CU; the fastest of "
                           "delta = f x (mean weight x 64 / mean degree), f in " + str(list(factors)),
-                "roofline": roofline("k_nearfar", "nearfar", abytes, best["kernel_ms"]),
+                "roofline": roofline("k_nearfar", workload, abytes, best["kernel_ms"]),
                 "tried": tried}
 
     def tune(self, **kw):
@@ -342,7 +342,7 @@ def run_grid8(args):
           "us_per_round": kern_s * 1e6 / st["rounds"], "edges_per_s": st["relaxations"] / kern_s,
           "estimated_full_s": kern_s / st["rounds"] * g.n,
           "roofline": roofline("k_sssp_full", "grid8_plain", sssp_bytes(st), st["kernel_ms"])}
-    nfr = q.nearfar(args.base_steps, args.nearfar_factors)
+    nfr = q.nearfar(args.base_steps, args.nearfar_factors, "grid8_nearfar")
     rec = {"metric": "SSSP GTEPS (m/time), learned threshold", **lr,
            "config": {"workload": GRID8_DESC, "n": g.n, "m": g.m}, "plain": pl,
            "speedup_vs_plain_estimate": pl["estimated_full_s"] / (lr["ms_per_step"] * 1e-3), "nearfar": nfr,
@@ -377,7 +377,7 @@ def run_batch(args):
     def exact():
         return all(np.array_equal(q[6].cpu().numpy().view(np.uint64), r) for q, r in zip(qs, refs))
 
-    def timed(steps, warmup, label, **kw):
+    def timed(steps, warmup, label, workload, **kw):
         torch.cuda.synchronize()
         for _ in range(warmup):
             pkg.sssp_batch(qs, **kw)
@@ -395,7 +395,7 @@ def run_batch(args):
         return {"value": sum_m / sec / 1e9, "unit": "GTEPS", "steps": steps, "warmup": warmup,
                 "ms_per_step": sec * 1e3, "rounds": st["rounds"], "relaxations": st["relaxations"],
                 "extracted": st["extracted"], "team": st["team"], "exact": ex,
-                "roofline": roofline("k_sssp_multi", "batch", sssp_bytes(st), kern_ms)}
+                "roofline": roofline("k_sssp_multi", workload, sssp_bytes(st), kern_ms)}
 
     blob = load_blob()
     t0 = time.perf_counter()
@@ -404,8 +404,8 @@ def run_batch(args):
     log(f"batch autotune: {tuned}")
     kw = dict(k_rule=2, k_model=blob, d_scale=tuned["d_scale"], k_max=tuned["k_max"], team=tuned["team"],
               k_scale=tuned["k_scale"])
-    lr = timed(args.steps, args.warmup, "batch learned", **kw)
-    pr = timed(args.base_steps, 0, "batch plain")
+    lr = timed(args.steps, args.warmup, "batch learned", "batch", **kw)
+    pr = timed(args.base_steps, 0, "batch plain", "batch_plain")
     # the same settings, the first queries of the batch's order one launch each:
     # what batching itself gains over running queries one after another
     ns = 16
